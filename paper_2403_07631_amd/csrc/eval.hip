@@ -639,27 +639,6 @@ pct_status launch_eval_r(const float* ground, const float* ceil, const EvalParam
 // then runs over these N x N bits (one wavefront for a single map, one
 // thread per job in a batch).
 
-// Reductions over a whole wavefront (every lane active) by DPP moves:
-// row_shr 1, 2, 4, 8 leave each row's result in its lane 15, row_bcast:15
-// into rows 1 and 3 and row_bcast:31 into rows 2 and 3 leave the
-// wavefront's in lane 63.  Lanes whose source is outside their row, and
-// rows outside the row mask, take the identity `id` instead.
-template <class Op>
-__device__ __forceinline__ int wave_reduce_dpp(int v, int id, Op op) {
-    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x111, 0xf, 0xf, false));   // row_shr:1
-    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x112, 0xf, 0xf, false));   // row_shr:2
-    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x114, 0xf, 0xf, false));   // row_shr:4
-    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x118, 0xf, 0xf, false));   // row_shr:8
-    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x142, 0xa, 0xf, false));   // row_bcast:15
-    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x143, 0xc, 0xf, false));   // row_bcast:31
-    return __builtin_amdgcn_readlane(v, 63);
-}
-__device__ __forceinline__ int wave_max_i(int v) {
-    return wave_reduce_dpp(v, INT_MIN, [](int a, int b) { return max(a, b); });
-}
-__device__ __forceinline__ int wave_min_i(int v) {
-    return wave_reduce_dpp(v, INT_MAX, [](int a, int b) { return min(a, b); });
-}
 __device__ __forceinline__ unsigned wave_or(unsigned v) {
     return (unsigned)wave_reduce_dpp((int)v, 0, [](int a, int b) { return a | b; });
 }

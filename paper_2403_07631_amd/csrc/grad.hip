@@ -38,10 +38,21 @@ __device__ __forceinline__ float gval(const float* __restrict__ gk, int nx, int 
     return (x >= 0 && y >= 0 && x < nx && y < ny) ? gk[(long long)y * nx + x] : -INFINITY;
 }
 
-__device__ bool gentle_at(const float* __restrict__ gk, int nx, int ny, int x, int y, const EvalParams& p) {
-    const float G = gval(gk, nx, ny, x, y);
-    const float l = gval(gk, nx, ny, x - 1, y), r = gval(gk, nx, ny, x + 1, y);
-    const float d = gval(gk, nx, ny, x, y - 1), u = gval(gk, nx, ny, x, y + 1);
+// Where a cell's e^G and e^C come from: the map itself (off-grid cells have
+// no ground), or a wavefront's staged box.
+struct MapCells {
+    const float* __restrict__ gk;
+    const float* __restrict__ ck;
+    int nx, ny;
+    __device__ __forceinline__ float G(int x, int y) const { return gval(gk, nx, ny, x, y); }
+    __device__ __forceinline__ float C(int x, int y) const { return ck[(long long)y * nx + x]; }
+};
+
+template <class Cells>
+__device__ __forceinline__ bool gentle_at(const Cells& m, int x, int y, const EvalParams& p) {
+    const float G = m.G(x, y);
+    const float l = m.G(x - 1, y), r = m.G(x + 1, y);
+    const float d = m.G(x, y - 1), u = m.G(x, y + 1);
     if (!(isfinite(G) && isfinite(l) && isfinite(r) && isfinite(d) && isfinite(u))) return false;
     return sumsq(r - l, u - d) < p.Ts2;
 }
@@ -55,22 +66,19 @@ struct Cinit {
 
 // c^init of cell (x, y) of one slice, Eqs. (1)-(5), with the values needed
 // by its adjoint.  Same FP32 operation sequence as the forward kernels.
-__device__ Cinit cinit_at(const float* __restrict__ gk, const float* __restrict__ ck, int x, int y,
-                          const EvalParams& p) {
-    const int nx = p.nx, ny = p.ny;
+template <class Cells>
+__device__ __forceinline__ Cinit cinit_of(const Cells& m, int x, int y, float G, float C, const EvalParams& p) {
     Cinit o{};
-    const float G = gk[(long long)y * nx + x];
     if (!isfinite(G)) {
         o.ci = p.cB;
         o.branch = 0;
         return o;
     }
-    const float C = ck[(long long)y * nx + x];
     o.dI = C - G;
     const float cI = o.dI < p.d_min ? p.cB : fmaxf(0.0f, p.alpha_d * (p.d_ref - o.dI));
     o.ipos = !(o.dI < p.d_min) && p.alpha_d * (p.d_ref - o.dI) > 0.0f;
-    const float l = gval(gk, nx, ny, x - 1, y), r = gval(gk, nx, ny, x + 1, y);
-    const float d = gval(gk, nx, ny, x, y - 1), u = gval(gk, nx, ny, x, y + 1);
+    const float l = m.G(x - 1, y), r = m.G(x + 1, y);
+    const float d = m.G(x, y - 1), u = m.G(x, y + 1);
     float cG = p.cB;
     o.branch = 1;
     if (isfinite(l) && isfinite(r) && isfinite(d) && isfinite(u)) {
@@ -85,7 +93,7 @@ __device__ Cinit cinit_at(const float* __restrict__ gk, const float* __restrict_
                 int cnt = 0;
                 for (int dyp = -p.rp; dyp <= p.rp; ++dyp)
                     for (int dxp = -p.rp; dxp <= p.rp; ++dxp)
-                        if (dxp | dyp) cnt += gentle_at(gk, nx, ny, x + dxp, y + dyp, p) ? 1 : 0;
+                        if (dxp | dyp) cnt += gentle_at(m, x + dxp, y + dyp, p) ? 1 : 0;
                 if (cnt > p.kp) {
                     cG = p.Ab * fmaxf(o.dx * o.dx, o.dy * o.dy);
                     o.branch = 3;
@@ -99,6 +107,13 @@ __device__ Cinit cinit_at(const float* __restrict__ gk, const float* __restrict_
     o.pass = s < p.cB;
     o.ci = fminf(p.cB, s);
     return o;
+}
+
+__device__ __forceinline__ Cinit cinit_at(const float* __restrict__ gk, const float* __restrict__ ck, int x, int y,
+                          const EvalParams& p) {
+    const MapCells m{gk, ck, p.nx, p.ny};
+    const float G = gk[(long long)y * p.nx + x];
+    return cinit_of(m, x, y, G, isfinite(G) ? m.C(x, y) : 0.0f, p);
 }
 
 // A contribution in fixed point: v * 2^32 rounded to the nearest integer
@@ -147,12 +162,11 @@ __device__ __forceinline__ void add_ceil(const Sink& s, long long i, float v) {
 
 // c^T of cell (x, y) of one slice, evaluated on demand: the maximum over
 // the Eq. (6) window of K * c^init (first maximum in row-major window
-// order), with the maximising cell and its c^init details.  The same FP32
+// order), with the maximising cell and its weight.  The same FP32
 // products and maxima as the full-map kernels, so the same value.
 struct WinMax {
     float v, k;
     int qx, qy;
-    Cinit q;
 };
 
 // The window maxima of the four bilinear corners of a waypoint at once:
@@ -187,57 +201,13 @@ __device__ void window_max4(const float* __restrict__ gk, const float* __restric
                 need |= m <= R && n <= R && p.K[m][n] > 0.0f;
             }
             if (!need) continue;
-            const Cinit q = cinit_at(gk, ck, qx, qy, p);
+            const float ci = cinit_at(gk, ck, qx, qy, p).ci;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const int m = abs(qx - cx[c]), n = abs(qy - cy[c]);
                 if (m > R || n > R) continue;
                 const float kw = p.K[m][n];
-                if (kw <= 0.0f) continue;
-                const float v = kw * q.ci;
-                if (v > o[c].v) {
-                    o[c].v = v;
-                    o[c].k = kw;
-                    o[c].qx = qx;
-                    o[c].qy = qy;
-                    o[c].q = q;
-                }
-            }
-        }
-    }
-}
-
-// window_max4 over c^init values already in `box` (rows of bw cells from
-// column bx0, row by0, covering every window): the same row-major walk,
-// products and first maxima; the maximising cells' c^init details (o[c].q)
-// are recomputed when `details` is set.
-__device__ void window_max4_box(const float* __restrict__ box, int bx0, int by0, int bw,
-                                const float* __restrict__ gk, const float* __restrict__ ck, const int (&cx)[4],
-                                const int (&cy)[4], const EvalParams& p, bool details, WinMax (&o)[4]) {
-    const int nx = p.nx, ny = p.ny, R = p.R;
-    int xlo = cx[0], xhi = cx[0], ylo = cy[0], yhi = cy[0];
-#pragma unroll
-    for (int c = 1; c < 4; ++c) {
-        xlo = min(xlo, cx[c]);
-        xhi = max(xhi, cx[c]);
-        ylo = min(ylo, cy[c]);
-        yhi = max(yhi, cy[c]);
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        o[c] = WinMax{};
-        o[c].v = -INFINITY;
-    }
-    for (int qy = max(0, ylo - R); qy <= min(ny - 1, yhi + R); ++qy) {
-        const float* row = box + (qy - by0) * bw - bx0;
-        for (int qx = max(0, xlo - R); qx <= min(nx - 1, xhi + R); ++qx) {
-            const float ci = row[qx];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int m = abs(qx - cx[c]), n = abs(qy - cy[c]);
-                if (m > R || n > R) continue;
-                const float kw = p.K[m][n];
-                if (kw <= 0.0f) continue;
+                if (!(kw > 0.0f)) continue;
                 const float v = kw * ci;
                 if (v > o[c].v) {
                     o[c].v = v;
@@ -248,19 +218,6 @@ __device__ void window_max4_box(const float* __restrict__ box, int bx0, int by0,
             }
         }
     }
-    if (details) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) o[c].q = cinit_at(gk, ck, o[c].qx, o[c].qy, p);
-    }
-}
-
-__device__ __forceinline__ int wave_min_int(int v) {
-    for (int m = 32; m >= 1; m >>= 1) v = min(v, __shfl_xor(v, m, 64));
-    return v;
-}
-__device__ __forceinline__ int wave_max_int(int v) {
-    for (int m = 32; m >= 1; m >>= 1) v = max(v, __shfl_xor(v, m, 64));
-    return v;
 }
 
 // LDS written by some lanes of a wavefront, then read by others.
@@ -270,18 +227,406 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// c^init cells a wavefront shares per round of 64 waypoints (8 KB each).
-constexpr int kTrajBox = 2048;
+// ---------------------------------------------------------------- boxes
+//
+// A wavefront's box: the cells that the windows of its waypoints can touch
+// on one slice.  e^G is staged in LDS with a halo of patch radius + 1 (one
+// coalesced read per cell, -inf off the grid), c^init is evaluated from
+// there once per cell (NaN off the grid), and the window maxima read only
+// c^init.  With fixed-point sums the box also holds the ground gradients of
+// its cells (integers, so the order of the additions does not matter), which
+// go out in one atomic per touched cell when the wavefront leaves the box:
+// atomics on device memory are what an adjoint that sends each contribution
+// there by itself waits for.  64 profiles x 1024 walks x 256 waypoints on
+// the 1000 x 1000 building, values and gradients: 12.5 ms with c^init
+// evaluated from global memory and every contribution an atomic, 9.3 ms with
+// boxes (7.7 ms of it the atomics), 2.8 ms with the box's sums and boxes kept
+// from profile to profile; values alone 1.2 ms, bound by vector issue
+// (3300 instructions per round of 64 waypoints).  LDS of 13 KB instead of
+// 10 KB per wavefront cuts fewer groups but leaves three workgroups per CU:
+// 3.1 ms, and 1.8 ms for the values alone.
+constexpr int kBoxFloats = 2472;     // 4 workgroups of 4 wavefronts per CU
+constexpr int kBoxR = 8;             // largest inflation radius of the box path
+constexpr int kBoxWeights = (kBoxR + 1) * (kBoxR + 1);
+struct BoxLds {
+    alignas(8) float v[kBoxFloats];  // gradient sums, e^G with halo, c^init
+    float K[kBoxWeights];            // K[a * (R + 1) + j]; NaN for zero weights
+    float pad[1];
+};
+static_assert(4 * sizeof(BoxLds) * 4 <= 160 * 1024, "four workgroups per CU");
 
-// Eq. (1)-(5) adjoint at the maximising cell of a window, for gradient gq
-// of its c^init.
-__device__ void cinit_adjoint(const Cinit& q, long long iq, int nx, float gq, const EvalParams& p, const Sink& s) {
+struct Box {
+    unsigned long long* acc;   // ground gradients, rows of w + 2 cells, first cell (x0 - 1, y0 - 1)
+    float* g;                  // e^G, rows of wg cells, first cell (x0 - halo, y0 - halo)
+    float* c;                  // c^init, rows of w cells, first cell (x0, y0)
+    int x0, y0, w, h, wg, halo;
+    int k;                     // slice; -1: nothing staged
+    __device__ __forceinline__ float G(int x, int y) const { return g[(y - y0 + halo) * wg + x - x0 + halo]; }
+};
+
+// Whether a box of w x h cells fits (halo: patch radius + 1).
+__device__ __forceinline__ bool box_fits(int w, int h, int halo, bool sums) {
+    if (w > kBoxFloats || h > kBoxFloats) return false;
+    const int e = 2 * halo;
+    return (sums ? 2 * (w + 2) * (h + 2) : 0) + (w + e) * (h + e) + w * h <= kBoxFloats;
+}
+
+// Cells lane, lane + 64, ... of a row-major box `W` wide, without a division
+// per cell.
+struct BoxWalk {
+    int u, v, du, dv, W;
+    __device__ __forceinline__ BoxWalk(int lane, int W_) : W(W_) {
+        v = lane / W;
+        u = lane - v * W;
+        dv = 64 / W;
+        du = 64 - dv * W;
+    }
+    __device__ __forceinline__ void next() {
+        u += du;
+        v += dv;
+        if (u >= W) {
+            u -= W;
+            ++v;
+        }
+    }
+};
+
+// The wavefront (all lanes) moves its box to the w x h cells at (x0, y0) of
+// slice k: e^G staged four cells per lane and step, so that their loads are
+// in flight together, gradient sums cleared.
+__device__ __forceinline__ void stage_box(Box& b, BoxLds& lds, const float* __restrict__ gk, int k, int x0, int y0,
+                                          int w, int h, const EvalParams& p, bool sums) {
+    const int lane = threadIdx.x & 63, nx = p.nx, ny = p.ny;
+    b.k = k;
+    b.halo = p.rp + 1;
+    b.x0 = x0;
+    b.y0 = y0;
+    b.w = w;
+    b.h = h;
+    b.wg = w + 2 * b.halo;
+    const int ns = sums ? (w + 2) * (h + 2) : 0, n = b.wg * (h + 2 * b.halo);
+    b.acc = (unsigned long long*)lds.v;
+    b.g = lds.v + 2 * ns;
+    b.c = b.g + n;
+    for (int i = lane; i < ns; i += 64) b.acc[i] = 0ull;
+    BoxWalk q(lane, b.wg);
+    for (int i = lane; i < n; i += 256) {
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[e] = i + 64 * e < n ? gval(gk, nx, ny, x0 - b.halo + q.u, y0 - b.halo + q.v) : 0.0f;
+            q.next();
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (i + 64 * e < n) b.g[i + 64 * e] = v[e];
+    }
+    wave_lds_sync();
+}
+
+// c^init of the box's cells for parameters p.
+__device__ __forceinline__ void fill_cinit(const Box& b, const float* __restrict__ ck, const EvalParams& p) {
+    const int lane = threadIdx.x & 63, nx = p.nx, ny = p.ny;
+    BoxWalk q(lane, b.w);
+    const int n = b.w * b.h;
+    for (int i = lane; i < n; i += 256) {
+        float C[4];
+        int x[4], y[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            x[e] = b.x0 + q.u;
+            y[e] = b.y0 + q.v;
+            const bool in = i + 64 * e < n && x[e] >= 0 && y[e] >= 0 && x[e] < nx && y[e] < ny;
+            C[e] = in ? ck[(long long)y[e] * nx + x[e]] : 0.0f;
+            if (!in) x[e] = INT_MIN;
+            q.next();
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (i + 64 * e >= n) continue;
+            float ci = __builtin_nanf("");
+            if (x[e] != INT_MIN) ci = cinit_of(b, x[e], y[e], b.G(x[e], y[e]), C[e], p).ci;
+            b.c[i + 64 * e] = ci;
+        }
+    }
+    wave_lds_sync();
+}
+
+// The box's gradient sums to the sink (fixed point).
+__device__ __forceinline__ void flush_box(const Box& b, const Sink& s, long long plane, int nx) {
+    if (b.k < 0) return;
+    wave_lds_sync();
+    BoxWalk q(threadIdx.x & 63, b.w + 2);
+    const int n = (b.w + 2) * (b.h + 2);
+    for (int i = threadIdx.x & 63; i < n; i += 64) {
+        const unsigned long long v = b.acc[i];
+        if (v != 0ull) {
+            const long long cell = (long long)b.k * plane + (long long)(b.y0 - 1 + q.v) * nx + (b.x0 - 1 + q.u);
+            if (s.gG) atomicAdd((unsigned long long*)s.gG + cell, v);
+            if (s.gz) {
+                const int id = s.aG[cell];
+                if (id >= 0 && id < s.n_points) atomicAdd((unsigned long long*)s.gz + id, v);
+            }
+        }
+        q.next();
+    }
+    wave_lds_sync();
+}
+
+// Window maxima of the four corners (x, y), (x+1, y), (x, y+1), (x+1, y+1)
+// from the box's c^init: per corner the first maximum of K * c^init in
+// row-major window order, as a walk over its own window gives it.  Taps off
+// the grid or of weight zero are NaN products, which fmaxf passes over and
+// no comparison selects.  Each window row is reduced to its maximum and the
+// first row with a greater one is remembered; the tap is then found in that
+// row alone.  RT: the inflation radius when known at compile time (the
+// weights are then uniform operands and the row is unrolled), 0: p.R.
+// The maximising tap is only looked for when `taps` is set.
+template <int RT>
+__device__ __forceinline__ void window_max4_box(const Box& b, const float* __restrict__ sK,
+                                                int x, int y, const EvalParams& p, bool taps, WinMax (&o)[4]) {
+    const int R = RT > 0 ? RT : p.R, K1 = R + 1;
+    const float* base = b.c + (y - R - b.y0) * b.w + (x - R - b.x0);
+    float best[4];
+    int brow[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        best[c] = -INFINITY;
+        brow[c] = 0;
+    }
+    if constexpr (RT > 0) {
+#pragma unroll
+        for (int n = 0; n <= 2 * RT + 1; ++n) {
+            float v[2 * RT + 2];
+#pragma unroll
+            for (int m = 0; m <= 2 * RT + 1; ++m) v[m] = base[n * b.w + m];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {       // corners on row y (n - R) and y + 1 (n - R - 1)
+                const int dy = n - RT - r;
+                if (dy < -RT || dy > RT) continue;
+                const int j = dy < 0 ? -dy : dy;
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    float rm = -INFINITY;
+#pragma unroll
+                    for (int m = 0; m <= 2 * RT; ++m) {
+                        const int a = m < RT ? RT - m : m - RT;
+                        rm = fmaxf(rm, sK[a * (RT + 1) + j] * v[m + q]);
+                    }
+                    const int c = 2 * r + q;
+                    if (rm > best[c]) {
+                        best[c] = rm;
+                        brow[c] = n;
+                    }
+                }
+            }
+        }
+    } else {
+        for (int n = 0; n <= 2 * R + 1; ++n) {
+            float rm[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+            const int j0 = abs(n - R), j1 = abs(n - R - 1);
+            for (int m = 0; m <= 2 * R + 1; ++m) {
+                const float v = base[n * b.w + m];
+                const int a0 = abs(m - R), a1 = abs(m - R - 1);
+                if (a0 <= R && j0 <= R) rm[0] = fmaxf(rm[0], sK[a0 * K1 + j0] * v);
+                if (a1 <= R && j0 <= R) rm[1] = fmaxf(rm[1], sK[a1 * K1 + j0] * v);
+                if (a0 <= R && j1 <= R) rm[2] = fmaxf(rm[2], sK[a0 * K1 + j1] * v);
+                if (a1 <= R && j1 <= R) rm[3] = fmaxf(rm[3], sK[a1 * K1 + j1] * v);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (rm[c] > best[c]) {
+                    best[c] = rm[c];
+                    brow[c] = n;
+                }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        o[c] = WinMax{};
+        o[c].v = best[c];
+    }
+    if (!taps) return;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int q = c & 1, r = c >> 1;
+        const int j = abs(brow[c] - R - r);
+        const float* row = base + brow[c] * b.w + q;
+        int bm = 0;
+        float bk = 0.0f;
+        for (int m = 2 * R; m >= 0; --m) {      // the last hit is the row's first maximum
+            const float kw = sK[abs(m - R) * K1 + j];
+            if (kw * row[m] == best[c]) {
+                bm = m;
+                bk = kw;
+            }
+        }
+        o[c].k = bk;
+        o[c].qx = x + q + bm - R;
+        o[c].qy = y - R + brow[c];
+    }
+}
+
+// The common radii have unrolled windows; p.R is uniform over the wavefront.
+__device__ __forceinline__ void window_max4_any(const Box& b, const float* __restrict__ sK,
+                                                int x, int y, const EvalParams& p, bool taps, WinMax (&o)[4]) {
+    switch (p.R) {
+    case 5: window_max4_box<5>(b, sK, x, y, p, taps, o); break;
+    case 4: window_max4_box<4>(b, sK, x, y, p, taps, o); break;
+    case 2: window_max4_box<2>(b, sK, x, y, p, taps, o); break;
+    default: window_max4_box<0>(b, sK, x, y, p, taps, o); break;
+    }
+}
+
+// The wavefront's weight table for the parameters it works with.
+__device__ __forceinline__ void fill_weights(BoxLds& lds, const EvalParams& p) {
+    const int lane = threadIdx.x & 63, K1 = p.R + 1;
+    for (int i = lane; i < K1 * K1; i += 64) lds.K[i] = p.K[i / K1][i % K1];
+    wave_lds_sync();
+}
+
+// The window maxima of one waypoint's corners by the whole wavefront, from a
+// box of its windows alone: every lane takes cells of the box, the maxima
+// and their first taps are reduced over the lanes.
+__device__ __forceinline__ void window_max4_one(const Box& b, const float* __restrict__ sK, const EvalParams& p,
+                                                bool taps, WinMax (&o)[4]) {
+    const int lane = threadIdx.x & 63, R = p.R, K1 = R + 1, n = b.w * b.h;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int q = c & 1, r = c >> 1;
+        float best = -INFINITY, bk = 0.0f;
+        int bi = INT_MAX;
+        BoxWalk u(lane, b.w);
+        for (int i = lane; i < n; i += 64) {
+            const int m = abs(u.u - R - q), j = abs(u.v - R - r);
+            const float kw = m <= R && j <= R ? sK[m * K1 + j] : __builtin_nanf("");
+            const float v = kw * b.c[i];
+            if (v > best) {
+                best = v;
+                bk = kw;
+                bi = i;
+            }
+            u.next();
+        }
+        // c^init >= 0: the maximum is not negative, and the order of such
+        // floats is that of their encodings
+        const int top = wave_max_i(bi == INT_MAX ? -1 : __builtin_bit_cast(int, best));
+        o[c] = WinMax{};
+        o[c].v = __builtin_bit_cast(float, top);
+        if (!taps) continue;
+        const int first = wave_min_i(bi != INT_MAX && __builtin_bit_cast(int, best) == top ? bi : INT_MAX);
+        o[c].k = __shfl(bk, first & 63, 64);      // cell i belongs to lane i % 64
+        o[c].qy = b.y0 + first / b.w;
+        o[c].qx = b.x0 + first % b.w;
+    }
+}
+
+// Where a waypoint's gradients go: ground gradients to the box's sums when
+// it has them, all others to the sink.
+struct BoxSink {
+    const Sink* s;
+    const Box* b;      // null: no box sums
+    long long base;    // first cell of the slice
+    int nx;
+    __device__ __forceinline__ void ground(int x, int y, float v) const {
+        if (b) {
+            if (v != 0.0f) atomicAdd(&b->acc[(y - b->y0 + 1) * (b->w + 2) + x - b->x0 + 1], to_fixed(v));
+        } else {
+            add_ground(*s, base + (long long)y * nx + x, v);
+        }
+    }
+    __device__ __forceinline__ void ceil(int x, int y, float v) const {
+        add_ceil(*s, base + (long long)y * nx + x, v);
+    }
+};
+
+// The wavefront's waypoints in groups that share a box: `ok` lanes on slice
+// k with corners (x, y) .. (x + 1, y + 1).  The lanes of the first waiting
+// lane's slice, from it on, form a group; while their box does not fit, the
+// group is cut to half its reach.  Groups of fewer than eight lanes would
+// spend most of the wavefront on one window after another: those waypoints
+// are taken one by one, the whole wavefront on each.  A group whose box lies
+// in the one staged already (the next profile on the same walk) keeps it,
+// with the gradients summed there; SUMS: the box sums ground gradients
+// (fixed point), which leave with the box.  Radius at most kBoxR, and a map
+// more than one cell wide and tall.
+// body(wm, detail, sink) runs once per lane, where detail(wm[c]) is the
+// c^init of the maximising cell with what its adjoint needs.
+template <bool SUMS, class Body>
+__device__ __forceinline__ void for_box_groups(Box& b, BoxLds& lds, const float* __restrict__ ground,
+                                               const float* __restrict__ ceil, const EvalParams& p, bool ok, int k,
+                                               int x, int y, bool taps, const Sink& s, Body body) {
+    const int lane = threadIdx.x & 63, R = p.R;
+    unsigned long long rem = __ballot(ok);
+    while (rem != 0ull) {
+        const int l0 = (int)__builtin_ctzll(rem);
+        const int kb = __builtin_amdgcn_readlane(k, l0);
+        const float* gk = ground + (long long)kb * p.plane;
+        const float* ck = ceil + (long long)kb * p.plane;
+        const bool cand = ((rem >> lane) & 1ull) != 0ull && k == kb;
+        bool mine = false, fits = false;
+        int xlo = 0, ylo = 0, w = 0, h = 0;
+        for (int reach = 64; reach >= 8 && !fits; reach >>= 1) {
+            mine = cand && lane < l0 + reach;
+            xlo = wave_min_i(mine ? x : INT_MAX) - R;
+            ylo = wave_min_i(mine ? y : INT_MAX) - R;
+            w = wave_max_i(mine ? x : INT_MIN) + 2 + R - xlo;
+            h = wave_max_i(mine ? y : INT_MIN) + 2 + R - ylo;
+            fits = box_fits(w, h, p.rp + 1, SUMS);
+        }
+        WinMax wm[4];
+        if (fits) {
+            const bool staged = b.k == kb && b.halo == p.rp + 1 && xlo >= b.x0 && ylo >= b.y0 &&
+                                xlo + w <= b.x0 + b.w && ylo + h <= b.y0 + b.h;
+            if (!staged) {
+                if (SUMS) flush_box(b, s, p.plane, p.nx);
+                stage_box(b, lds, gk, kb, xlo, ylo, w, h, p, SUMS);
+            }
+            fill_cinit(b, ck, p);
+            if (mine) window_max4_any(b, lds.K, x, y, p, taps, wm);
+        } else {
+            if (SUMS) flush_box(b, s, p.plane, p.nx);
+            unsigned long long left = __ballot(mine);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) wm[c] = WinMax{};
+            while (left != 0ull) {
+                const int l = (int)__builtin_ctzll(left);
+                WinMax one[4];
+                stage_box(b, lds, gk, kb, __builtin_amdgcn_readlane(x, l) - R, __builtin_amdgcn_readlane(y, l) - R,
+                          2 + 2 * R, 2 + 2 * R, p, false);
+                fill_cinit(b, ck, p);
+                window_max4_one(b, lds.K, p, taps, one);
+                wave_lds_sync();
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (lane == l) wm[c] = one[c];
+                left &= left - 1;
+            }
+            b.k = -1;
+        }
+        if (mine) {
+            const BoxSink to{&s, SUMS && fits ? &b : nullptr, (long long)kb * p.plane, p.nx};
+            body(wm, [&](const WinMax& m) {
+                const float C = ck[(long long)m.qy * p.nx + m.qx];
+                if (fits) return cinit_of(b, m.qx, m.qy, b.G(m.qx, m.qy), C, p);
+                return cinit_at(gk, ck, m.qx, m.qy, p);
+            }, to);
+        }
+        wave_lds_sync();   // the next group refills the box
+        rem &= ~__ballot(mine);
+    }
+}
+
+// Eq. (1)-(5) adjoint at the maximising cell (x, y) of a window, for
+// gradient gq of its c^init.
+__device__ __forceinline__ void cinit_adjoint(const Cinit& q, int x, int y, float gq, const EvalParams& p,
+                                              const BoxSink& to) {
     if (q.branch == 0 || !q.pass) return;
     if (q.ipos) {
-        add_ground(s, iq, p.alpha_d * gq);
-        add_ceil(s, iq, -p.alpha_d * gq);
+        to.ground(x, y, p.alpha_d * gq);
+        to.ceil(x, y, -p.alpha_d * gq);
     }
-    float ddx = 0.0f, ddy = 0.0f;
+    float ddx = 0.0f, ddy = 0.0f;   // dL/d(dx), dL/d(dy) for the raw differences
     if (q.branch == 2) {
         ddx = 2.0f * p.As * q.dx * gq;
         ddy = 2.0f * p.As * q.dy * gq;
@@ -290,12 +635,12 @@ __device__ void cinit_adjoint(const Cinit& q, long long iq, int nx, float gq, co
         else ddy = 2.0f * p.Ab * q.dy * gq;
     }
     if (ddx != 0.0f) {
-        add_ground(s, iq + 1, ddx);
-        add_ground(s, iq - 1, -ddx);
+        to.ground(x + 1, y, ddx);
+        to.ground(x - 1, y, -ddx);
     }
     if (ddy != 0.0f) {
-        add_ground(s, iq + nx, ddy);
-        add_ground(s, iq - nx, -ddy);
+        to.ground(x, y + 1, ddy);
+        to.ground(x, y - 1, -ddy);
     }
 }
 
@@ -314,7 +659,7 @@ __device__ void eval_adjoint_cell(const float* __restrict__ ground, const float*
         for (int m = -R; m <= R; ++m) {
             const int qx = x + m;
             const float kw = p.K[abs(m)][abs(n)];
-            if (kw <= 0.0f || qx < 0 || qx >= nx) continue;
+            if (!(kw > 0.0f) || qx < 0 || qx >= nx) continue;
             const float v = kw * cinit_at(gk, ck, qx, qy, p).ci;
             if (v > best) {
                 best = v;
@@ -324,30 +669,7 @@ __device__ void eval_adjoint_cell(const float* __restrict__ ground, const float*
             }
         }
     }
-    const Cinit q = cinit_at(gk, ck, bx, by, p);
-    if (q.branch == 0 || !q.pass) return;
-    const float gq = bk * gc;
-    const long long iq = base + (long long)by * nx + bx;
-    if (q.ipos) {
-        add_ground(s, iq, p.alpha_d * gq);
-        add_ceil(s, iq, -p.alpha_d * gq);
-    }
-    float ddx = 0.0f, ddy = 0.0f;   // dL/d(dx), dL/d(dy) for the raw differences
-    if (q.branch == 2) {
-        ddx = 2.0f * p.As * q.dx * gq;
-        ddy = 2.0f * p.As * q.dy * gq;
-    } else if (q.branch == 3) {
-        if (fabsf(q.dx) >= fabsf(q.dy)) ddx = 2.0f * p.Ab * q.dx * gq;
-        else ddy = 2.0f * p.Ab * q.dy * gq;
-    }
-    if (ddx != 0.0f) {
-        add_ground(s, iq + 1, ddx);
-        add_ground(s, iq - 1, -ddx);
-    }
-    if (ddy != 0.0f) {
-        add_ground(s, iq + nx, ddy);
-        add_ground(s, iq - nx, -ddy);
-    }
+    cinit_adjoint(cinit_at(gk, ck, bx, by, p), bx, by, bk * gc, p, BoxSink{&s, nullptr, base, nx});
 }
 
 // ----------------------------------------------------------------- sampling
@@ -360,6 +682,7 @@ struct SampleArgs {
 
 struct Bil {
     bool ok, hterm;
+    int i0, j0;       // cell of c00; the other corners are one further (the same cell on an axis of one cell)
     long long c00, c10, c01, c11;
     float fu, fv, du, dv;
 };
@@ -423,6 +746,8 @@ __device__ Bil bilinear(const float* __restrict__ ground, const SampleArgs& a, f
     axis(iv, fv, a.ny, j0, j1, b.fv, b.dv);
     b.du *= a.inv_res;
     b.dv *= a.inv_res;
+    b.i0 = i0;
+    b.j0 = j0;
     const long long base = (long long)k * a.plane;
     b.c00 = base + (long long)j0 * a.nx + i0;
     b.c10 = base + (long long)j0 * a.nx + i1;
@@ -458,23 +783,32 @@ __global__ __launch_bounds__(kBlock) void k_sample_fwd(const float* __restrict__
 }
 
 // Per waypoint: dL/dwp (written), the bilinear scatter of dL/dC to c^T
-// (dense gcost and/or, with `eval`, straight through the traversability
-// adjoint into the sink) and of the height term to e^G.
-__global__ __launch_bounds__(kBlock) void k_sample_bwd(const float* __restrict__ cost, const float* __restrict__ ground,
+// (dense gcost) or, with EVAL, straight through the traversability adjoint
+// into the sink, and of the height term to e^G.  With EVAL = kBoxes a
+// wavefront's 64 waypoints share boxes of c^init as in k_traj_value_grad;
+// kWindows walks each corner's window over the map (radii and maps that
+// boxes do not take).
+enum { kDense, kBoxes, kWindows };
+template <int EVAL>
+__global__ __launch_bounds__(kBlock, 4) void k_sample_bwd(const float* __restrict__ cost, const float* __restrict__ ground,
                                                        const float* __restrict__ ceil, const float* __restrict__ wp,
                                                        const int* __restrict__ slice, SampleArgs a,
                                                        const float* __restrict__ gf, float* __restrict__ gwp,
-                                                       float* __restrict__ gcost, const EvalParams ep, int eval,
-                                                       Sink s) {
-    const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= (long long)a.T * a.W) return;
+                                                       float* __restrict__ gcost, const EvalParams ep, Sink s) {
+    const long long n = (long long)a.T * a.W;
+    const long long i0 = (long long)blockIdx.x * kBlock + threadIdx.x;
+    const bool act = i0 < n;
+    if (EVAL == kDense && !act) return;
+    const long long i = act ? i0 : n - 1;
     const int t = (int)(i / a.W);
     const float x = wp[3 * i], y = wp[3 * i + 1], z = wp[3 * i + 2];
     const int k = slice[i];
-    const Bil b = bilinear(ground, a, x, y, z, k);
-    float gx = 0.0f, gy = 0.0f, gzw = 0.0f;
+    Bil b = bilinear(ground, a, x, y, z, k);
+    b.ok = b.ok && act;
+    float gx = 0.0f, gy = 0.0f, gzw = 0.0f, g = 0.0f;
+    float ws[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (b.ok) {
-        const float g = gf[t];
+        g = gf[t];
         const float w00 = (1.0f - b.fu) * (1.0f - b.fv), w10 = b.fu * (1.0f - b.fv);
         const float w01 = (1.0f - b.fu) * b.fv, w11 = b.fu * b.fv;
         const float c00 = cost[b.c00], c10 = cost[b.c10], c01 = cost[b.c01], c11 = cost[b.c11];
@@ -483,7 +817,7 @@ __global__ __launch_bounds__(kBlock) void k_sample_bwd(const float* __restrict__
         gx = g * dCdu * b.du;
         gy = g * dCdv * b.dv;
         const long long cs[4] = {b.c00, b.c10, b.c01, b.c11};
-        const float ws[4] = {w00, w10, w01, w11};
+        ws[0] = w00, ws[1] = w10, ws[2] = w01, ws[3] = w11;
         if (b.hterm) {
             const float G00 = ground[b.c00], G10 = ground[b.c10], G01 = ground[b.c01], G11 = ground[b.c11];
             const float G = w00 * G00 + w10 * G10 + w01 * G01 + w11 * G11;
@@ -498,15 +832,39 @@ __global__ __launch_bounds__(kBlock) void k_sample_bwd(const float* __restrict__
         for (int c = 0; c < 4; ++c) {
             const float gc = g * ws[c];
             if (gcost && gc != 0.0f) grad_add(gcost, cs[c], gc, s.fixed);
-            if (eval && gc != 0.0f) {
+            if (EVAL == kWindows && gc != 0.0f) {
                 const long long local = cs[c] - (long long)k * a.plane;
                 eval_adjoint_cell(ground, ceil, k, (int)(local % a.nx), (int)(local / a.nx), gc, ep, s);
             }
         }
     }
-    gwp[3 * i] = gx;
-    gwp[3 * i + 1] = gy;
-    gwp[3 * i + 2] = gzw;
+    if (act) {
+        gwp[3 * i] = gx;
+        gwp[3 * i + 1] = gy;
+        gwp[3 * i + 2] = gzw;
+    }
+    if constexpr (EVAL == kBoxes) {
+        __shared__ BoxLds s_box[kBlock / 64];
+        BoxLds& lds = s_box[threadIdx.x / 64];
+        fill_weights(lds, ep);
+        Box box{};
+        box.k = -1;
+        auto body = [&](const WinMax (&wm)[4], auto detail, const BoxSink& to) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float gc = g * ws[c];
+                if (gc == 0.0f) continue;
+                cinit_adjoint(detail(wm[c]), wm[c].qx, wm[c].qy, wm[c].k * gc, ep, to);
+            }
+        };
+        const bool ok = b.ok && g != 0.0f;
+        if (s.fixed) {
+            for_box_groups<true>(box, lds, ground, ceil, ep, ok, k, b.i0, b.j0, true, s, body);
+            flush_box(box, s, a.plane, a.nx);
+        } else {
+            for_box_groups<false>(box, lds, ground, ceil, ep, ok, k, b.i0, b.j0, true, s, body);
+        }
+    }
 }
 
 // Dense traversability adjoint: one thread per cell-slice with a gradient.
@@ -567,96 +925,72 @@ int grid_for(long long n) { return (int)std::max<long long>(1, std::min<long lon
 
 // Value and gradient for many robot profiles in one launch, each profile
 // with its own trajectories, with c^T evaluated on demand at the bilinear
-// corners (no cost maps).  One wavefront per (profile, trajectory), lanes
-// over its waypoints; per waypoint the value and the waypoint gradient are
-// the same FP32 sequences as k_sample_fwd / k_sample_bwd on a materialised
-// map, and the maximising taps found for the value feed the traversability
-// adjoint directly.
-__global__ __launch_bounds__(kBlock) void k_traj_value_grad(const float* __restrict__ ground,
-                                                            const float* __restrict__ ceil,
-                                                            const EvalParams* __restrict__ robots, SampleArgs a,
-                                                            int n_profiles, const float* __restrict__ wp,
-                                                            const int* __restrict__ slice,
-                                                            const float* __restrict__ gf, float* __restrict__ f,
-                                                            float* __restrict__ gwp, Sink s) {
+// corners (no cost maps).  One wavefront per trajectory and run of up to
+// kTrajProfiles profiles, lanes over its waypoints: per round of 64
+// waypoints the profiles follow one another, so that profiles on the same
+// walk share the round's box.  Per waypoint the value and the waypoint
+// gradient are the same FP32 sequences as k_sample_fwd / k_sample_bwd on a
+// materialised map, and the maximising taps found for the value feed the
+// traversability adjoint directly.
+// SUMS: fixed-point gradient sums with a ground or point output.
+// BOX false: windows walked over the map, one profile per wavefront (radii
+// and maps that boxes do not take).
+constexpr int kTrajProfiles = 8;
+
+template <bool BOX, bool SUMS>
+__global__ __launch_bounds__(kBlock, 4) void k_traj_value_grad(const float* __restrict__ ground,
+                                                               const float* __restrict__ ceil,
+                                                               const EvalParams* __restrict__ robots, SampleArgs a,
+                                                               int n_profiles, int run, const float* __restrict__ wp,
+                                                               const int* __restrict__ slice,
+                                                               const float* __restrict__ gf, float* __restrict__ f,
+                                                               float* __restrict__ gwp, Sink s) {
     const long long wave = (long long)blockIdx.x * (kBlock / 64) + threadIdx.x / 64;
-    if (wave >= (long long)n_profiles * a.T) return;
-    const int prof = __builtin_amdgcn_readfirstlane((int)(wave / a.T));
-    const EvalParams& p = robots[prof];
+    const int p0 = __builtin_amdgcn_readfirstlane((int)(wave / a.T)) * run;
+    const int t = __builtin_amdgcn_readfirstlane((int)(wave % a.T));
+    if (p0 >= n_profiles) return;
+    const int np = min(run, n_profiles - p0);
     const int lane = threadIdx.x & 63;
-    const float g = gf ? gf[wave] : 0.0f;
-    __shared__ float s_box[kBlock / 64][kTrajBox];
-    float* box = s_box[threadIdx.x / 64];
-    float acc = 0.0f;
-    // rounds of 64 waypoints; a round whose waypoints share a slice and whose
-    // windows fit one box has the wavefront compute each c^init of the box
-    // once (consecutive waypoints of a trajectory are close, so their
-    // windows overlap) and every lane take its window maxima from it
-    for (int w0 = 0; w0 < a.W; w0 += 64) {
-        const int w = w0 + lane;
-        const bool act = w < a.W;
-        const long long i = wave * a.W + min(w, a.W - 1);
-        const float x = wp[3 * i], y = wp[3 * i + 1], z = wp[3 * i + 2];
-        const int k = slice[i];
-        Bil b = bilinear(ground, a, x, y, z, k);
-        b.ok = b.ok && act;
-        int cx[4] = {0, 0, 0, 0}, cy[4] = {0, 0, 0, 0};
-        if (b.ok) {
-            const long long base = (long long)k * a.plane;
-            const long long cs[4] = {b.c00, b.c10, b.c01, b.c11};
+    __shared__ BoxLds s_box[BOX ? kBlock / 64 : 1];
+    BoxLds& lds = s_box[BOX ? threadIdx.x / 64 : 0];
+    Box box{};
+    box.k = -1;
+    int weights_of = -1;
+    float accs[kTrajProfiles];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const long long local = cs[c] - base;
-                cx[c] = (int)(local % a.nx);
-                cy[c] = (int)(local / a.nx);
-            }
-        }
-        const unsigned long long okm = __ballot(b.ok);
-        bool use_box = false;
-        int bx0 = 0, by0 = 0, bw = 0;
-        if (okm != 0ull) {   // uniform
-            const int kb = __shfl(k, (int)__builtin_ctzll(okm), 64);
-            const bool same_k = __ballot(b.ok && k != kb) == 0ull;
-            const int xlo = wave_min_int(b.ok ? min(min(cx[0], cx[1]), min(cx[2], cx[3])) : INT_MAX);
-            const int xhi = wave_max_int(b.ok ? max(max(cx[0], cx[1]), max(cx[2], cx[3])) : INT_MIN);
-            const int ylo = wave_min_int(b.ok ? min(min(cy[0], cy[1]), min(cy[2], cy[3])) : INT_MAX);
-            const int yhi = wave_max_int(b.ok ? max(max(cy[0], cy[1]), max(cy[2], cy[3])) : INT_MIN);
-            bx0 = max(0, xlo - p.R);
-            by0 = max(0, ylo - p.R);
-            bw = min(a.nx - 1, xhi + p.R) - bx0 + 1;
-            const int bh = min(a.ny - 1, yhi + p.R) - by0 + 1;
-            use_box = same_k && (long long)bw * bh <= kTrajBox;
-            if (use_box) {
-                const long long base = (long long)kb * a.plane;
-                for (int idx = lane; idx < bw * bh; idx += 64)
-                    box[idx] = cinit_at(ground + base, ceil + base, bx0 + idx % bw, by0 + idx / bw, p).ci;
-                wave_lds_sync();
-            }
-        }
-        float gx = 0.0f, gy = 0.0f, gzw = 0.0f;
-        if (b.ok) {
-            const long long base = (long long)k * a.plane;
-            const float* gk = ground + base;
-            const float* ck = ceil + base;
-            const long long cs[4] = {b.c00, b.c10, b.c01, b.c11};
-            WinMax wm[4];
-            if (use_box) window_max4_box(box, bx0, by0, bw, gk, ck, cx, cy, p, gf != nullptr, wm);
-            else window_max4(gk, ck, cx, cy, p, wm);
-            const float w00 = (1.0f - b.fu) * (1.0f - b.fv), w10 = b.fu * (1.0f - b.fv);
-            const float w01 = (1.0f - b.fu) * b.fv, w11 = b.fu * b.fv;
-            const float ws[4] = {w00, w10, w01, w11};
-            acc += w00 * wm[0].v + w10 * wm[1].v + w01 * wm[2].v + w11 * wm[3].v;
-            float G00 = 0.0f, G10 = 0.0f, G01 = 0.0f, G11 = 0.0f, G = 0.0f;
-            if (b.hterm) {
-                G00 = ground[b.c00];
-                G10 = ground[b.c10];
-                G01 = ground[b.c01];
-                G11 = ground[b.c11];
-                G = w00 * G00 + w10 * G10 + w01 * G01 + w11 * G11;
-                const float e = z - G - p.d_ref;
-                acc += a.w_z * e * e;
-            }
-            if (gf) {
+    for (int q = 0; q < kTrajProfiles; ++q) accs[q] = 0.0f;
+    for (int w0 = 0; w0 < a.W; w0 += 64) {
+        for (int pi = 0; pi < np; ++pi) {
+            const EvalParams& p = robots[p0 + pi];
+            const long long row = (long long)(p0 + pi) * a.T + t;
+            const int w = w0 + lane;
+            const bool act = w < a.W;
+            const long long i = row * a.W + min(w, a.W - 1);
+            const float x = wp[3 * i], y = wp[3 * i + 1], z = wp[3 * i + 2];
+            const int k = slice[i];
+            const float g = gf ? gf[row] : 0.0f;
+            Bil b = bilinear(ground, a, x, y, z, k);
+            b.ok = b.ok && act;
+            float gx = 0.0f, gy = 0.0f, gzw = 0.0f;
+            float acc = 0.0f;
+#pragma unroll
+            for (int q = 0; q < kTrajProfiles; ++q) acc = q == pi ? accs[q] : acc;
+            auto body = [&](const WinMax (&wm)[4], auto detail, const BoxSink& to) {
+                const float w00 = (1.0f - b.fu) * (1.0f - b.fv), w10 = b.fu * (1.0f - b.fv);
+                const float w01 = (1.0f - b.fu) * b.fv, w11 = b.fu * b.fv;
+                const float ws[4] = {w00, w10, w01, w11};
+                acc += w00 * wm[0].v + w10 * wm[1].v + w01 * wm[2].v + w11 * wm[3].v;
+                float G00 = 0.0f, G10 = 0.0f, G01 = 0.0f, G11 = 0.0f, G = 0.0f;
+                if (b.hterm) {
+                    G00 = ground[b.c00];
+                    G10 = ground[b.c10];
+                    G01 = ground[b.c01];
+                    G11 = ground[b.c11];
+                    G = w00 * G00 + w10 * G10 + w01 * G01 + w11 * G11;
+                    const float e = z - G - p.d_ref;
+                    acc += a.w_z * e * e;
+                }
+                if (!gf) return;
                 const float dCdu = (1.0f - b.fv) * (wm[1].v - wm[0].v) + b.fv * (wm[3].v - wm[2].v);
                 const float dCdv = (1.0f - b.fu) * (wm[2].v - wm[0].v) + b.fu * (wm[3].v - wm[1].v);
                 gx = g * dCdu * b.du;
@@ -668,27 +1002,66 @@ __global__ __launch_bounds__(kBlock) void k_traj_value_grad(const float* __restr
                     gx -= de * dGdu * b.du;
                     gy -= de * dGdv * b.dv;
                     gzw = de;
-                    for (int c = 0; c < 4; ++c) add_ground(s, cs[c], -de * ws[c]);
+                    const int x1 = min(b.i0 + 1, a.nx - 1), y1 = min(b.j0 + 1, a.ny - 1);
+                    to.ground(b.i0, b.j0, -de * ws[0]);
+                    to.ground(x1, b.j0, -de * ws[1]);
+                    to.ground(b.i0, y1, -de * ws[2]);
+                    to.ground(x1, y1, -de * ws[3]);
                 }
+#pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     const float gc = g * ws[c];
                     if (gc == 0.0f) continue;
-                    cinit_adjoint(wm[c].q, base + (long long)wm[c].qy * a.nx + wm[c].qx, a.nx, wm[c].k * gc, p, s);
+                    cinit_adjoint(detail(wm[c]), wm[c].qx, wm[c].qy, wm[c].k * gc, p, to);
                 }
+            };
+            if constexpr (BOX) {
+                if (weights_of != pi) {
+                    fill_weights(lds, p);
+                    weights_of = pi;
+                }
+                for_box_groups<SUMS>(box, lds, ground, ceil, p, b.ok, k, b.i0, b.j0, gf != nullptr, s, body);
+            } else if (b.ok) {
+                const float* gk = ground + (long long)k * a.plane;
+                const float* ck = ceil + (long long)k * a.plane;
+                const int x1 = min(b.i0 + 1, a.nx - 1), y1 = min(b.j0 + 1, a.ny - 1);
+                const int cx[4] = {b.i0, x1, b.i0, x1}, cy[4] = {b.j0, b.j0, y1, y1};
+                WinMax wm[4];
+                window_max4(gk, ck, cx, cy, p, wm);
+                body(wm, [&](const WinMax& m) { return cinit_at(gk, ck, m.qx, m.qy, p); },
+                     BoxSink{&s, nullptr, (long long)k * a.plane, a.nx});
             }
+            if (gwp && act) {
+                gwp[3 * i] = gx;
+                gwp[3 * i + 1] = gy;
+                gwp[3 * i + 2] = gzw;
+            }
+#pragma unroll
+            for (int q = 0; q < kTrajProfiles; ++q) accs[q] = q == pi ? acc : accs[q];
         }
-        if (gwp && act) {
-            gwp[3 * i] = gx;
-            gwp[3 * i + 1] = gy;
-            gwp[3 * i + 2] = gzw;
-        }
-        if (use_box) wave_lds_sync();   // the next round refills the box
     }
-    for (int m = 32; m >= 1; m >>= 1) acc += __shfl_xor(acc, m, 64);
-    if (lane == 0) f[wave] = acc;
+    if constexpr (BOX && SUMS) flush_box(box, s, a.plane, a.nx);
+#pragma unroll
+    for (int q = 0; q < kTrajProfiles; ++q) {
+        if (q >= np) break;
+        float v = accs[q];
+        for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+        if (lane == 0) f[(long long)(p0 + q) * a.T + t] = v;
+    }
 }
 
 }  // namespace
+
+// Boxes hold windows of at most this radius, and waypoints with four distinct
+// corners; k_traj_value_grad and k_sample_bwd take other radii and maps one
+// cell wide through walks over the map.
+bool boxes_apply(const EvalParams& p) { return p.R <= kBoxR && p.nx > 1 && p.ny > 1; }
+
+void mark_zero_taps(EvalParams& p) {
+    for (auto& row : p.K)
+        for (float& k : row)
+            if (!(k > 0.0f)) k = __builtin_nanf("");
+}
 
 pct_status launch_zero(float* p, long long n, hipStream_t s) {
     if (!p || n <= 0) return PCT_OK;
@@ -739,8 +1112,18 @@ pct_status launch_sample_bwd(const float* cost, const float* ground, const float
     EvalParams p = ep ? *ep : EvalParams{};
     const long long n = (long long)T * W;
     if (n == 0) return PCT_OK;
-    hipLaunchKernelGGL(k_sample_bwd, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, cost, ground, ceil,
-                       wp, slice, a, gf, gwp, gcost, p, ep ? 1 : 0, sk);
+    const dim3 blocks((unsigned)((n + kBlock - 1) / kBlock));
+    if (ep && boxes_apply(p)) {
+        mark_zero_taps(p);
+        hipLaunchKernelGGL(k_sample_bwd<kBoxes>, blocks, dim3(kBlock), 0, s, cost, ground, ceil, wp, slice, a, gf, gwp,
+                           gcost, p, sk);
+    } else if (ep) {
+        hipLaunchKernelGGL(k_sample_bwd<kWindows>, blocks, dim3(kBlock), 0, s, cost, ground, ceil, wp, slice, a, gf,
+                           gwp, gcost, p, sk);
+    } else {
+        hipLaunchKernelGGL(k_sample_bwd<kDense>, blocks, dim3(kBlock), 0, s, cost, ground, ceil, wp, slice, a, gf, gwp,
+                           gcost, p, sk);
+    }
     PCT_LAUNCH_CHECK();
     return PCT_OK;
 }
@@ -775,7 +1158,7 @@ pct_status launch_traj_value_grad(const float* ground, const float* ceil, const 
                                   const pct_grid& g, int N, const EvalParams* d_robots, int n_profiles, float w_z,
                                   const float* wp, const int* slice, int T, int W, const float* gf, float* f,
                                   float* gwp, float* gground, float* gceil, float* gz, long long n_points,
-                                  bool fixed, hipStream_t s) {
+                                  bool fixed, bool boxes, hipStream_t s) {
     const SampleArgs a = make_sample_args(g, N, 0.0f, w_z, T, W);
     Sink sk{};
     sk.fixed = fixed;
@@ -787,11 +1170,25 @@ pct_status launch_traj_value_grad(const float* ground, const float* ceil, const 
         sk.gz = n_points > 0 ? gz : nullptr;
         sk.n_points = n_points;
     }
-    const long long waves = (long long)n_profiles * T;
-    if (waves == 0) return PCT_OK;
+    if ((long long)n_profiles * T == 0) return PCT_OK;
+    // profiles per wavefront: as many as leave 16384 wavefronts, four rounds
+    // of the chip (64 profiles x 1024 walks on the building: 2.80 ms, at
+    // 8192 3.08 ms); one where the windows are walked over the map
+    const int run = boxes ? (int)std::min<long long>(kTrajProfiles, std::max<long long>(1, (long long)n_profiles * T / 16384))
+                          : 1;
+    const long long waves = (long long)((n_profiles + run - 1) / run) * T;
     const unsigned blocks = (unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64));
-    hipLaunchKernelGGL(k_traj_value_grad, dim3(blocks), dim3(kBlock), 0, s, ground, ceil, d_robots, a, n_profiles, wp,
-                       slice, gf, f, gf ? gwp : nullptr, sk);
+    const bool sums = fixed && (sk.gG || sk.gz);
+    float* gw = gf ? gwp : nullptr;
+    if (boxes && sums)
+        hipLaunchKernelGGL((k_traj_value_grad<true, true>), dim3(blocks), dim3(kBlock), 0, s, ground, ceil, d_robots, a,
+                           n_profiles, run, wp, slice, gf, f, gw, sk);
+    else if (boxes)
+        hipLaunchKernelGGL((k_traj_value_grad<true, false>), dim3(blocks), dim3(kBlock), 0, s, ground, ceil, d_robots,
+                           a, n_profiles, run, wp, slice, gf, f, gw, sk);
+    else
+        hipLaunchKernelGGL((k_traj_value_grad<false, false>), dim3(blocks), dim3(kBlock), 0, s, ground, ceil, d_robots,
+                           a, n_profiles, run, wp, slice, gf, f, gw, sk);
     PCT_LAUNCH_CHECK();
     return PCT_OK;
 }

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <stdint.h>
 #include <stddef.h>
 
@@ -70,6 +71,29 @@ __host__ __device__ __forceinline__ float plane_height(float zmin, float ds, int
     return zmin + step;
 }
 
+// ---------------------------------------------------------------- wavefronts
+// Reductions over a whole wavefront (every lane active) by DPP moves:
+// row_shr 1, 2, 4, 8 leave each row's result in its lane 15, row_bcast:15
+// into rows 1 and 3 and row_bcast:31 into rows 2 and 3 leave the
+// wavefront's in lane 63.  Lanes whose source is outside their row, and
+// rows outside the row mask, take the identity `id` instead.
+template <class Op>
+__device__ __forceinline__ int wave_reduce_dpp(int v, int id, Op op) {
+    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x111, 0xf, 0xf, false));   // row_shr:1
+    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x112, 0xf, 0xf, false));   // row_shr:2
+    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x114, 0xf, 0xf, false));   // row_shr:4
+    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x118, 0xf, 0xf, false));   // row_shr:8
+    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x142, 0xa, 0xf, false));   // row_bcast:15
+    v = op(v, __builtin_amdgcn_update_dpp(id, v, 0x143, 0xc, 0xf, false));   // row_bcast:31
+    return __builtin_amdgcn_readlane(v, 63);
+}
+__device__ __forceinline__ int wave_max_i(int v) {
+    return wave_reduce_dpp(v, INT_MIN, [](int a, int b) { return max(a, b); });
+}
+__device__ __forceinline__ int wave_min_i(int v) {
+    return wave_reduce_dpp(v, INT_MAX, [](int a, int b) { return min(a, b); });
+}
+
 // ---------------------------------------------------------------- extent
 struct ExtentDev {
     float zmin, zmax;
@@ -112,6 +136,10 @@ struct EvalParams {
 };
 
 pct_status make_eval_params(const pct_robot& r, const pct_grid& g, int N, EvalParams* out);
+// The weights that are zero become NaN: the adjoints' window maxima pass
+// over the products of such taps without a test per tap.
+void mark_zero_taps(EvalParams& p);
+bool boxes_apply(const EvalParams& p);   // whether the adjoints may share c^init in boxes
 
 // ---------------------------------------------------------------- launchers
 pct_status launch_extent(const float* xyz, int64_t n, const GridDev& g, void* ws, ExtentDev* d_out,
@@ -202,7 +230,7 @@ pct_status launch_traj_value_grad(const float* ground, const float* ceil, const 
                                   const pct_grid& g, int N, const EvalParams* d_robots, int n_profiles, float w_z,
                                   const float* wp, const int* slice, int T, int W, const float* gf, float* f,
                                   float* gwp, float* gground, float* gceil, float* gz, long long n_points,
-                                  bool fixed, hipStream_t s);
+                                  bool fixed, bool boxes, hipStream_t s);
 pct_status launch_route(const float* gG, const float* gC, const int* aG, const int* aC, long long plane, int N,
                         long long n_points, float* gz, bool fixed, hipStream_t s);
 pct_status launch_fixed_to_float(const int64_t* q, long long n, float* out, hipStream_t s);

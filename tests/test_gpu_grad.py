@@ -225,3 +225,69 @@ def test_full_size_config2(P, oracle_lib):
         uz[a[m]] = True
     assert np.count_nonzero(rz) > 0
     close(gz, rz, ~uz, rel=2e-3)
+
+
+@pytest.mark.parametrize("d_inf,d_sm,layout", [(0.1, 0.3, "walks"), (0.2, 0.3, "scattered"), (0.2, 0.4, "spread"),
+                                               (0.3, 0.4, "scattered"), (0.4, 0.6, "spread"), (0.4, 0.6, "walks"),
+                                               (0.5, 0.6, "walks"), (0.3, 0.4, "column")])
+def test_window_boxes(P, oracle_lib, world, d_inf, d_sm, layout):
+    """The adjoints' shared boxes at inflation radii 2, 3, 4, 5, 8 and (walked
+    over the map) 9, for waypoints that share one box, need several
+    ("spread": 0.7 m apart, slices changing along the way) or one each
+    ("scattered"), out to the grid's edges and beyond, and on a map one cell
+    wide.  Values and gradients against the oracle; several profiles in one
+    call against the per-profile calls, exactly."""
+    import torch
+    w, rng = world, np.random.default_rng(5)
+    g, pts = w["g"], w["sc"].points
+    if layout == "column":
+        g = dict(g, nx=1, x0=6.0)
+    xyz = torch.from_numpy(pts).cuda()
+    n = len(pts)
+    ext = P.pct_tomogram_extent(xyz, g)
+    G, Cc, aG, aC = P.pct_build_tomogram(xyz, g, ext, with_ids=True)
+    tm = oracle_lib.tomogram(pts, g)
+    rs = [dict(w["r"], d_inf=d_inf, d_sm=d_sm), dict(w["r"], d_inf=d_inf, d_sm=d_sm, d_min=0.6, theta_s=0.5),
+          dict(w["r"], d_inf=0.1, d_sm=0.2, patch_radius=2)]
+    T, W, N = 3, 70, ext.n_slices
+    if layout == "walks":
+        mask = np.isfinite(tm["ground"])
+        wp, sl = scenes.random_walks(9, mask, tm["ground"], g, T, W, w["r"]["d_ref"])
+    else:
+        lo, hi = np.array([g["x0"], g["y0"]]), np.array([g["x0"] + g["nx"] * g["res"], g["y0"] + g["ny"] * g["res"]])
+        if layout == "spread":
+            xy = np.stack([np.linspace(lo + 0.3 * t, hi - 0.2 * t, W) for t in range(T)])
+            sl = np.broadcast_to(np.arange(W) // 9 % N, (T, W)).astype(np.int32)
+        else:
+            xy = rng.uniform(lo - 0.1, hi + 0.1, (T, W, 2))
+            sl = rng.integers(-1, N + 1, (T, W)).astype(np.int32)
+        wp = np.concatenate([xy, rng.uniform(0.5, 4.0, (T, W, 1))], 2).astype(np.float32)
+    wp, sl = np.ascontiguousarray(wp), np.ascontiguousarray(sl)
+    wp_t, sl_t = torch.from_numpy(wp).cuda(), torch.from_numpy(sl).cuda()
+    gf = torch.linspace(-1.0, 1.5, len(rs) * T, device="cuda").view(len(rs), T)
+    acc1 = torch.zeros(n, dtype=torch.int64, device="cuda")
+    f1, gwp1 = [], []
+    for i, r in enumerate(rs):
+        cost = P.pct_eval_traversability(G, Cc, g, ext, [r], keep=False)[0][0].contiguous()
+        f1.append(P.pct_sample_cost_fwd(cost, G, g, ext, r, W_Z, wp_t, sl_t))
+        gwp, gz = P.pct_trajectory_cost_bwd(G, Cc, cost, aG, aC, g, ext, r, W_Z, wp_t, sl_t, gf[i], n)
+        gwp1.append(gwp)
+        P.pct_trajectory_cost_bwd(G, Cc, cost, aG, aC, g, ext, r, W_Z, wp_t, sl_t, gf[i], n, gz=acc1,
+                                  flags=P.PCT_ACCUMULATE)
+        cT = oracle_lib.evaluate(tm["ground"], tm["ceil"], g["res"], r)
+        rgwp, rgc, rgg = oracle_lib.sample_bwd(cT, tm["ground"], g, W_Z, r["d_ref"], wp, sl,
+                                               gf[i].cpu().numpy().astype(np.float64))
+        rG, rC, unc = oracle_lib.eval_bwd(tm["ground"], tm["ceil"], g["res"], r, rgc)
+        rz = oracle_lib.route(rG + rgg, rC, tm["arg_ground"], tm["arg_ceil"], n)
+        uz = np.zeros(n, bool)
+        for a in (tm["arg_ground"], tm["arg_ceil"]):
+            uz[a[(a >= 0) & unc]] = True
+        close(gwp.cpu().numpy(), rgwp)
+        close(gz.cpu().numpy(), rz, ~uz)
+    acc2 = torch.empty(n, dtype=torch.int64, device="cuda")
+    f2 = torch.empty((len(rs), T), device="cuda")
+    gwp2 = torch.empty((len(rs), T, W, 3), device="cuda")
+    P.pct_trajectory_cost_multi(G, Cc, aG, aC, g, ext, rs, W_Z, wp_t.expand(len(rs), -1, -1, -1).contiguous(),
+                                sl_t.expand(len(rs), -1, -1).contiguous(), gf, n_points=n,
+                                out=(f2, gwp2, None, None, acc2))
+    assert torch.equal(f2, torch.stack(f1)) and torch.equal(gwp2, torch.stack(gwp1)) and torch.equal(acc1, acc2)
