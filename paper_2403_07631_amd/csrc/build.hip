@@ -2,8 +2,9 @@
 //
 // Algorithm 1 compares every point with every plane.  Here the points are
 // first binned by a counting sort into construction tiles (256 x th cells),
-// with LDS-privatised integer counters; then one workgroup per tile sorts
-// each cell's heights in LDS and sweeps the planes once:
+// with LDS-privatised integer counters; then one workgroup per tile takes
+// the extremes of each cell's heights between planes in LDS and sweeps the
+// planes once:
 //   ground e^G_k = the largest height <= h_k, ceiling e^C_k = the next one.
 // This equals Algorithm 1's per-plane max/min exactly (only comparisons are
 // involved) and writes each output element once, coalesced along x.
@@ -14,12 +15,11 @@ namespace pct {
 namespace {
 
 constexpr int kBlock = 256;
-// LDS record capacity of the tile reduce: at least these (with point ids,
-// without), raised per launch towards the mean records per tile, up to
-// kReduceCapMax, so that a dense map reduces each tile in one pass.
-constexpr int kReduceCapIds = 4096;
-constexpr int kReduceCap = 6144;
-constexpr int kReduceCapMax = 16384;
+// LDS slots of the tile reduce: at least kReduceCap (a cell has at most
+// PCT_MAX_SLICES + 1), at most kReduceBins per cell of a tile.
+constexpr int kReduceCap = 2048;
+constexpr int kReduceBins = 8;
+static_assert(kReduceCap > PCT_MAX_SLICES, "one cell's bins fit");
 
 __device__ __forceinline__ float wave_min(float v) {
     for (int m = 32; m >= 1; m >>= 1) v = fminf(v, __shfl_xor(v, m, 64));
@@ -650,10 +650,70 @@ __global__ __launch_bounds__(kBinBlock) void k_bin2_scatter_staged(const float* 
 }
 
 // ------------------------------------------------------------------ reduce
+//
+// A record's bin is the first plane at or above its height (N: above every
+// plane).  At plane k the ground is the greatest height of the highest
+// occupied bin <= k and the ceiling the least height of the lowest occupied
+// bin > k, so a cell needs only the extremes of its occupied bins and no
+// order within them.  A workgroup marks the occupied (cell, bin) pairs of its
+// tile in a bit matrix, gives each a slot by a scan of the bit counts, and
+// takes the slots' extremes with LDS atomics, all parallel over records;
+// then one lane per cell walks the planes.  Sorting each cell by the lane
+// that walks it was a chain of LDS round trips per cell: construction of the
+// 26.4 M-point building (26 records per cell) 0.94 -> 0.60 ms, 200 k points
+// inserted into it with the window's evaluation 0.68 -> 0.34 ms, the 20M-point
+// map (5 per cell, bound by the stores) 0.80 -> 0.77 ms.  Eight bins per cell
+// keep four workgroups on a CU (two with ids); six to ten measure alike, four
+// or five cut the building's tiles into groups (+10 %).
 constexpr int kReduceBlock = 512;   // one cell per thread for the 512-cell tiles
-__device__ __forceinline__ bool rec_less(float za, int ia, float zb, int ib, bool ids) {
-    return za < zb || (ids && za == zb && ia < ib);
+constexpr int kReduceKeep = 4;      // records per thread kept in registers between the passes
+
+// Heights as integers of the same order (finite; -0 has become +0).
+__device__ __forceinline__ int height_key(float z) {
+    const int i = __builtin_bit_cast(int, z);
+    return i ^ ((i >> 31) & 0x7fffffff);
 }
+__device__ __forceinline__ float key_height(int k) { return __builtin_bit_cast(float, k ^ ((k >> 31) & 0x7fffffff)); }
+
+// The first plane at or above z, N if none: a guess from the slice height,
+// put right by the planes' own FP32 heights (which do not decrease).
+__device__ __forceinline__ int plane_bin(float z, float zmin, float ds, float inv_ds, int N) {
+    const float q = (z - zmin) * inv_ds;
+    int k = q > 0.0f ? (q < (float)N ? (int)q : N) : 0;
+    while (k > 0 && z <= plane_height(zmin, ds, k - 1)) --k;
+    while (k < N && z > plane_height(zmin, ds, k)) ++k;
+    return k;
+}
+
+// A slot's extremes: heights, or with ids (height, id) with the lowest id
+// first among equal heights.
+template <bool IDS>
+struct SlotKeys;
+template <>
+struct SlotKeys<false> {
+    typedef int T;
+    static __device__ __forceinline__ T none_max() { return INT_MIN; }
+    static __device__ __forceinline__ T none_min() { return INT_MAX; }
+    static __device__ __forceinline__ T max_key(float z, int) { return height_key(z); }
+    static __device__ __forceinline__ T min_key(float z, int) { return height_key(z); }
+    static __device__ __forceinline__ float height(T k) { return key_height(k); }
+    static __device__ __forceinline__ int max_id(T) { return -1; }
+    static __device__ __forceinline__ int min_id(T) { return -1; }
+};
+template <>
+struct SlotKeys<true> {
+    typedef unsigned long long T;
+    static __device__ __forceinline__ T high(float z) {
+        return (unsigned long long)((unsigned)height_key(z) ^ 0x80000000u) << 32;
+    }
+    static __device__ __forceinline__ T none_max() { return 0ull; }
+    static __device__ __forceinline__ T none_min() { return ~0ull; }
+    static __device__ __forceinline__ T max_key(float z, int id) { return high(z) | (0xffffffffu - (unsigned)id); }
+    static __device__ __forceinline__ T min_key(float z, int id) { return high(z) | (unsigned)id; }
+    static __device__ __forceinline__ float height(T k) { return key_height((int)((unsigned)(k >> 32) ^ 0x80000000u)); }
+    static __device__ __forceinline__ int max_id(T k) { return (int)(0xffffffffu - (unsigned)k); }
+    static __device__ __forceinline__ int min_id(T k) { return (int)(unsigned)k; }
+};
 
 // Merge of a cell-slice's value with the one already stored (insertion
 // into an existing tomogram): the higher ground / lower ceiling wins, equal
@@ -673,52 +733,48 @@ __device__ __forceinline__ void merge_vals(float og, float oc, int oi, int oj, f
     }
 }
 
-template <bool IDS>
-__device__ __forceinline__ void merge_old(int64_t o, const float* __restrict__ ground, const float* __restrict__ ceil,
-                                          const int* __restrict__ ag, const int* __restrict__ ac, float& gz, int& gi,
-                                          float& cz, int& ci) {
-    merge_vals(ground[o], ceil[o], IDS ? ag[o] : 0, IDS ? ac[o] : 0, gz, gi, cz, ci);
-}
-
-// One cell: sort its heights (ties by point id) and sweep the planes.
-// MERGE: combine with the stored values instead of overwriting them (ids
-// are offset by id_base); a cell without records is left as it is.
+// One cell: walk the planes over its occupied bins (bits of `mask`, `words`
+// words `stride` apart) and their extremes smax, smin.  The next occupied
+// bin's extremes are read ahead.  MERGE: combine with the stored values
+// instead of overwriting them (ids are offset by id_base); a cell without
+// records is left as it is.
 template <bool IDS, bool MERGE>
-__device__ void sweep_cell(float* zs, int* is, int n, int ix, int iy, const GridDev& g, float zmin, float ds,
-                           int N, float* __restrict__ ground, float* __restrict__ ceil, int* __restrict__ ag,
-                           int* __restrict__ ac, int id_base) {
+__device__ __forceinline__ void sweep_cell(const unsigned* mask, int stride,
+                                           const typename SlotKeys<IDS>::T* smax,
+                                           const typename SlotKeys<IDS>::T* smin, int n, int ix, int iy,
+                                           const GridDev& g, int N, float* __restrict__ ground,
+                                           float* __restrict__ ceil, int* __restrict__ ag, int* __restrict__ ac,
+                                           int id_base) {
+    typedef SlotKeys<IDS> S;
     if (MERGE && n == 0) return;
-    // Shell sort by (height, id) with Ciura's gaps when merging (a scan can
-    // pile many new points into few cells); a plain insertion sort (gap 1)
-    // otherwise.  The order is total (ids are unique), so the result does
-    // not depend on the gaps.
-    constexpr int kGaps[] = {701, 301, 132, 57, 23, 10, 4, 1};
-    for (int gi = MERGE ? 0 : 7; gi < 8; ++gi) {
-        const int gap = kGaps[gi];
-        if (gap >= n) continue;
-        for (int a = gap; a < n; ++a) {
-            float z = zs[a];
-            int id = IDS ? is[a] : 0;
-            int b = a - gap;
-            while (b >= 0 && rec_less(z, id, zs[b], IDS ? is[b] : 0, IDS)) {
-                zs[b + gap] = zs[b];
-                if (IDS) is[b + gap] = is[b];
-                b -= gap;
-            }
-            zs[b + gap] = z;
-            if (IDS) is[b + gap] = id;
-        }
-    }
     const int64_t plane = (int64_t)g.nx * g.ny;
     int64_t o = (int64_t)iy * g.nx + ix;
-    int j = 0, rs = 0;
-    float znext = n > 0 ? zs[0] : INFINITY;
+    float gz = -INFINITY, cz = INFINITY, nextz = -INFINITY;
+    int gi = -1, ci = -1, nexti = -1;
+    int j = 0;
+    auto read_next = [&]() {
+        if (j < n) {
+            const typename S::T hi = smax[j], lo = smin[j];
+            nextz = S::height(hi);
+            cz = S::height(lo);
+            if (IDS) {
+                nexti = S::max_id(hi) + id_base;
+                ci = S::min_id(lo) + id_base;
+            }
+        } else {
+            cz = INFINITY;
+            ci = -1;
+        }
+    };
+    read_next();
     // MERGE reads the stored values of kAhead planes before it writes
     // any of them, so that their loads overlap
     constexpr int kAhead = MERGE ? 8 : 1;
+    unsigned bits = 0u;
     for (int k0 = 0; k0 < N; k0 += kAhead) {
         float og[kAhead], oc[kAhead];
         int oi[kAhead], oj[kAhead];
+        if ((k0 & 31) == 0) bits = mask[(k0 >> 5) * stride];
         if (MERGE) {
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
@@ -734,170 +790,135 @@ __device__ void sweep_cell(float* zs, int* is, int n, int ix, int iy, const Grid
         for (int u = 0; u < kAhead; ++u, o += plane) {
             const int k = k0 + u;
             if (k >= N) break;
-            const float hk = plane_height(zmin, ds, k);
-            while (j < n && znext <= hk) {
-                if (j == 0 || znext != zs[j - 1]) rs = j;
+            if ((bits >> (k & 31)) & 1u) {
+                gz = nextz;
+                gi = nexti;
                 ++j;
-                znext = j < n ? zs[j] : INFINITY;
+                read_next();
             }
-            float gz = j > 0 ? zs[j - 1] : -INFINITY, cz = znext;
-            int gi = IDS && j > 0 ? is[rs] + id_base : -1, ci = IDS && j < n ? is[j] + id_base : -1;
-            if (MERGE) merge_vals(og[u], oc[u], oi[u], oj[u], gz, gi, cz, ci);
+            float vg = gz, vc = cz;
+            int wg = gi, wc = ci;
+            if (MERGE) merge_vals(og[u], oc[u], oi[u], oj[u], vg, wg, vc, wc);
             // streaming stores: the grids are far larger than the caches
-            __builtin_nontemporal_store(gz, &ground[o]);
-            __builtin_nontemporal_store(cz, &ceil[o]);
+            __builtin_nontemporal_store(vg, &ground[o]);
+            __builtin_nontemporal_store(vc, &ceil[o]);
             if (IDS) {
-                __builtin_nontemporal_store(gi, &ag[o]);
-                __builtin_nontemporal_store(ci, &ac[o]);
+                __builtin_nontemporal_store(wg, &ag[o]);
+                __builtin_nontemporal_store(wc, &ac[o]);
             }
         }
-    }
-}
-
-// A cell with more points than the LDS holds: per plane, a block-wide
-// max/min reduction over the tile's records (ties to the lowest id).
-template <bool IDS, bool MERGE>
-__device__ void huge_cell(unsigned c, unsigned r0, unsigned r1, const float* __restrict__ rz,
-                          const unsigned* __restrict__ rmeta, const int* __restrict__ rid, int ix, int iy,
-                          const GridDev& g, float zmin, float ds, int N, float* __restrict__ ground,
-                          float* __restrict__ ceil, int* __restrict__ ag, int* __restrict__ ac, int id_base) {
-    __shared__ float s_gz[kReduceBlock], s_cz[kReduceBlock];
-    __shared__ int s_gi[kReduceBlock], s_ci[kReduceBlock];
-    const int64_t plane = (int64_t)g.nx * g.ny;
-    for (int k = 0; k < N; ++k) {
-        const float hk = plane_height(zmin, ds, k);
-        float gz = -INFINITY, cz = INFINITY;
-        int gi = 0x7fffffff, ci = 0x7fffffff;
-        for (unsigned r = r0 + threadIdx.x; r < r1; r += kReduceBlock) {
-            if (rmeta[r] != c) continue;
-            float z = rz[r];
-            int id = IDS ? rid[r] : 0;
-            if (z <= hk) {
-                if (z > gz || (z == gz && id < gi)) { gz = z; gi = id; }
-            } else {
-                if (z < cz || (z == cz && id < ci)) { cz = z; ci = id; }
-            }
-        }
-        s_gz[threadIdx.x] = gz; s_gi[threadIdx.x] = gi;
-        s_cz[threadIdx.x] = cz; s_ci[threadIdx.x] = ci;
-        __syncthreads();
-        for (int s = kReduceBlock / 2; s > 0; s >>= 1) {
-            if ((int)threadIdx.x < s) {
-                float z2 = s_gz[threadIdx.x + s];
-                int i2 = s_gi[threadIdx.x + s];
-                if (z2 > s_gz[threadIdx.x] || (z2 == s_gz[threadIdx.x] && i2 < s_gi[threadIdx.x])) {
-                    s_gz[threadIdx.x] = z2; s_gi[threadIdx.x] = i2;
-                }
-                z2 = s_cz[threadIdx.x + s];
-                i2 = s_ci[threadIdx.x + s];
-                if (z2 < s_cz[threadIdx.x] || (z2 == s_cz[threadIdx.x] && i2 < s_ci[threadIdx.x])) {
-                    s_cz[threadIdx.x] = z2; s_ci[threadIdx.x] = i2;
-                }
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            int64_t o = (int64_t)k * plane + (int64_t)iy * g.nx + ix;
-            float gz = s_gz[0], cz = s_cz[0];
-            int gi = IDS && isfinite(gz) ? s_gi[0] + id_base : -1, ci = IDS && isfinite(cz) ? s_ci[0] + id_base : -1;
-            if (MERGE) merge_old<IDS>(o, ground, ceil, ag, ac, gz, gi, cz, ci);
-            ground[o] = gz;
-            ceil[o] = cz;
-            if (IDS) {
-                ag[o] = gi;
-                ac[o] = ci;
-            }
-        }
-        __syncthreads();
     }
 }
 
 // One construction tile: records off[tg] .. off[tg+1] of the tile whose
 // position in its grid is tl.  Shared by the single-map and batched kernels.
+// CAP: slots that fit in LDS; a tile with more takes groups of cells in
+// turn, reading its records again for each.
 template <bool IDS, bool MERGE = false>
 __device__ void reduce_tile(int tg, int tl, const unsigned* __restrict__ off, const float* __restrict__ rz,
                             const unsigned* __restrict__ rmeta, const int* __restrict__ rid, const GridDev& g,
                             float zmin, float ds, int N, float* __restrict__ ground, float* __restrict__ ceil,
                             int* __restrict__ ag, int* __restrict__ ac, int CAP, int id_base = 0) {
+    typedef SlotKeys<IDS> S;
     extern __shared__ unsigned s_mem[];
     const int cells = g.tw * g.th;
-    unsigned* s_cnt = s_mem;                 // cells
-    unsigned* s_start = s_cnt + cells;       // cells + 1
-    float* s_z = (float*)(s_start + cells + 1);
-    int* s_id = (int*)(s_z + CAP);
+    const int W = N / 32 + 1;                // bins 0 .. N
+    typename S::T* s_max = (typename S::T*)s_mem;
+    typename S::T* s_min = s_max + CAP;
+    unsigned* s_bits = (unsigned*)(s_min + CAP);   // [W][cells]
+    unsigned* s_base = s_bits + W * cells;         // cells + 1
+    __shared__ unsigned s_w[kReduceBlock / 64];
 
     const int tx = tl % g.ntx, ty = tl / g.ntx;
     const unsigned r0 = off[tg], r1 = off[tg + 1];
     if (MERGE && r0 == r1) return;   // an insertion leaves tiles without new points alone
 
-    for (int c = threadIdx.x; c < cells; c += kReduceBlock) s_cnt[c] = 0;
+    const float inv_ds = 1.0f / ds;
+    for (int i = threadIdx.x; i < W * cells; i += kReduceBlock) s_bits[i] = 0u;
     __syncthreads();
-    for (unsigned r = r0 + threadIdx.x; r < r1; r += kReduceBlock) atomicAdd(&s_cnt[rmeta[r]], 1u);
+    // occupied bins; a thread's first kReduceKeep records stay in registers
+    unsigned kc[kReduceKeep];   // cell | bin << 16; ~0: no record
+    float kz[kReduceKeep];
+    int ki[kReduceKeep];
+    auto mark = [&](unsigned c, float z) -> unsigned {
+        const unsigned b = (unsigned)plane_bin(z, zmin, ds, inv_ds, N);
+        atomicOr(&s_bits[(b >> 5) * cells + c], 1u << (b & 31));
+        return b;
+    };
+#pragma unroll
+    for (int q = 0; q < kReduceKeep; ++q) {
+        const unsigned r = r0 + q * kReduceBlock + threadIdx.x;
+        const bool ok = r < r1;
+        kc[q] = ok ? rmeta[r] : ~0u;
+        kz[q] = ok ? rz[r] : 0.0f;
+        ki[q] = IDS && ok ? rid[r] : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < kReduceKeep; ++q)
+        if (kc[q] != ~0u) kc[q] |= mark(kc[q], kz[q]) << 16;
+    const unsigned r2 = r0 + kReduceKeep * kReduceBlock;
+    for (unsigned r = r2 + threadIdx.x; r < r1; r += kReduceBlock) mark(rmeta[r], rz[r]);
     __syncthreads();
-    // exclusive scan of the per-cell counts; thread i owns a contiguous run
+    // slots: thread i owns a contiguous run of cells
     {
-        __shared__ unsigned s_part[kReduceBlock];
         const int per = (cells + kReduceBlock - 1) / kReduceBlock;
-        const int b = threadIdx.x * per, e = min(b + per, cells);
-        unsigned sum = 0;
-        for (int i = b; i < e; ++i) sum += s_cnt[i];
-        s_part[threadIdx.x] = sum;
-        __syncthreads();
-        for (int d = 1; d < kReduceBlock; d <<= 1) {
-            unsigned v = threadIdx.x >= (unsigned)d ? s_part[threadIdx.x - d] : 0u;
-            __syncthreads();
-            s_part[threadIdx.x] += v;
-            __syncthreads();
+        const int b = min((int)threadIdx.x * per, cells), e = min(b + per, cells);
+        unsigned sum = 0, total;
+        for (int c = b; c < e; ++c)
+            for (int w = 0; w < W; ++w) sum += (unsigned)__popc(s_bits[w * cells + c]);
+        unsigned run = block_scan_excl(sum, s_w, total);
+        for (int c = b; c < e; ++c) {
+            s_base[c] = run;
+            for (int w = 0; w < W; ++w) run += (unsigned)__popc(s_bits[w * cells + c]);
         }
-        unsigned run = s_part[threadIdx.x] - sum;
-        for (int i = b; i < e; ++i) {
-            s_start[i] = run;
-            run += s_cnt[i];
-        }
-        if (threadIdx.x == kReduceBlock - 1) s_start[cells] = s_part[kReduceBlock - 1];
+        if (threadIdx.x == 0) s_base[cells] = total;
     }
     __syncthreads();
 
     int c_lo = 0;
     while (c_lo < cells) {
-        // largest group [c_lo, c_hi) whose records fit in LDS
-        int lo = c_lo + 1, hi = cells;
-        if (s_start[c_lo + 1] - s_start[c_lo] > (unsigned)CAP) {
-            hi = c_lo + 1;
-        } else {
-            while (lo < hi) {
-                int mid = (lo + hi + 1) / 2;
-                if (s_start[mid] - s_start[c_lo] <= (unsigned)CAP) lo = mid;
-                else hi = mid - 1;
+        // largest group [c_lo, c_hi) whose slots fit in LDS; one cell has at
+        // most N + 1 <= CAP
+        int c_hi = cells;
+        const unsigned g0 = s_base[c_lo];
+        if (s_base[cells] - g0 > (unsigned)CAP) {
+            int lo = c_lo + 1;
+            while (lo < c_hi) {
+                const int mid = (lo + c_hi + 1) / 2;
+                if (s_base[mid] - g0 <= (unsigned)CAP) lo = mid;
+                else c_hi = mid - 1;
             }
-            hi = lo;
         }
-        const int c_hi = hi;
-        const unsigned g0 = s_start[c_lo];
-        if (c_hi == c_lo + 1 && s_start[c_hi] - g0 > (unsigned)CAP) {
-            const int ix = tx * g.tw + (c_lo % g.tw);
-            const int iy = ty * g.th + c_lo / g.tw;
-            huge_cell<IDS, MERGE>((unsigned)c_lo, r0, r1, rz, rmeta, rid, ix, iy, g, zmin, ds, N, ground, ceil, ag, ac,
-                                  id_base);
-        } else {
-            for (int c = c_lo + threadIdx.x; c < c_hi; c += kReduceBlock) s_cnt[c] = 0;
-            __syncthreads();
-            for (unsigned r = r0 + threadIdx.x; r < r1; r += kReduceBlock) {
-                unsigned c = rmeta[r];
-                if ((int)c < c_lo || (int)c >= c_hi) continue;
-                unsigned pos = s_start[c] - g0 + atomicAdd(&s_cnt[c], 1u);
-                s_z[pos] = rz[r];
-                if (IDS) s_id[pos] = rid[r];
-            }
-            __syncthreads();
-            for (int c = c_lo + threadIdx.x; c < c_hi; c += kReduceBlock) {
-                const int ix = tx * g.tw + (c % g.tw);
-                const int iy = ty * g.th + c / g.tw;
-                if (ix >= g.nx || iy >= g.ny) continue;
-                const unsigned s = s_start[c] - g0;
-                sweep_cell<IDS, MERGE>(s_z + s, s_id + s, (int)(s_start[c + 1] - s_start[c]), ix, iy, g, zmin, ds,
-                                       N, ground, ceil, ag, ac, id_base);
-            }
+        const int ns = (int)(s_base[c_hi] - g0);
+        for (int i = threadIdx.x; i < ns; i += kReduceBlock) {
+            s_max[i] = S::none_max();
+            s_min[i] = S::none_min();
+        }
+        __syncthreads();
+        auto put = [&](unsigned c, unsigned b, float z, int id) {
+            if ((int)c < c_lo || (int)c >= c_hi) return;
+            unsigned slot = s_base[c] - g0;
+            const unsigned w = b >> 5;
+            for (unsigned v = 0; v < w; ++v) slot += (unsigned)__popc(s_bits[v * cells + c]);
+            slot += (unsigned)__popc(s_bits[w * cells + c] & ((1u << (b & 31)) - 1u));
+            atomicMax(&s_max[slot], S::max_key(z, id));
+            atomicMin(&s_min[slot], S::min_key(z, id));
+        };
+#pragma unroll
+        for (int q = 0; q < kReduceKeep; ++q)
+            if (kc[q] != ~0u) put(kc[q] & 0xffffu, kc[q] >> 16, kz[q], ki[q]);
+        for (unsigned r = r2 + threadIdx.x; r < r1; r += kReduceBlock) {
+            const float z = rz[r];
+            put(rmeta[r], (unsigned)plane_bin(z, zmin, ds, inv_ds, N), z, IDS ? rid[r] : 0);
+        }
+        __syncthreads();
+        for (int c = c_lo + threadIdx.x; c < c_hi; c += kReduceBlock) {
+            const int ix = tx * g.tw + (c % g.tw);
+            const int iy = ty * g.th + c / g.tw;
+            if (ix >= g.nx || iy >= g.ny) continue;
+            const unsigned s = s_base[c] - g0;
+            sweep_cell<IDS, MERGE>(s_bits + c, cells, s_max + s, s_min + s, (int)(s_base[c + 1] - s_base[c]), ix, iy, g,
+                                   N, ground, ceil, ag, ac, id_base);
         }
         __syncthreads();
         c_lo = c_hi;
@@ -905,7 +926,7 @@ __device__ void reduce_tile(int tg, int tl, const unsigned* __restrict__ off, co
 }
 
 template <bool IDS, bool MERGE>
-__global__ __launch_bounds__(kReduceBlock) void k_tile_reduce(const unsigned* __restrict__ off,
+__global__ __launch_bounds__(kReduceBlock, MERGE || IDS ? 4 : 8) void k_tile_reduce(const unsigned* __restrict__ off,
                                                         const float* __restrict__ rz,
                                                         const unsigned* __restrict__ rmeta,
                                                         const int* __restrict__ rid, GridDev g, float zmin,
@@ -916,17 +937,19 @@ __global__ __launch_bounds__(kReduceBlock) void k_tile_reduce(const unsigned* __
                             ac, cap, id_base);
 }
 
-// Record capacity for n points over the grid's tiles: the floor, or 1.25x
-// the mean per tile (rounded up to 1024) when that is larger, up to the cap.
-inline int reduce_cap(int64_t n, const GridDev& g, bool ids) {
+// Slots per tile in LDS: 1.25x the mean records per tile (rounded up to
+// 1024), which a tile's occupied bins seldom exceed, at most kReduceBins bins
+// per cell (storeyed scenes occupy two or three bins per surface), and at
+// least one cell's N + 1.
+inline int reduce_cap(int64_t n, const GridDev& g) {
     const int64_t mean = g.ntiles > 0 ? n / g.ntiles : 0;
     const int64_t want = (mean + mean / 4 + 1023) / 1024 * 1024;
-    return (int)std::min<int64_t>(kReduceCapMax, std::max<int64_t>(ids ? kReduceCapIds : kReduceCap, want));
+    return (int)std::min<int64_t>((int64_t)kReduceBins * g.tw * g.th, std::max<int64_t>(kReduceCap, want));
 }
 
-inline size_t reduce_lds_bytes(const GridDev& g, bool ids, int cap) {
+inline size_t reduce_lds_bytes(const GridDev& g, int N, bool ids, int cap) {
     const int cells = g.tw * g.th;
-    return sizeof(unsigned) * (2 * cells + 1) + (size_t)cap * (ids ? 8 : 4);
+    return sizeof(unsigned) * ((size_t)(N / 32 + 1) * cells + cells + 1) + (size_t)cap * (ids ? 16 : 8);
 }
 
 // Kernels may take more than 64 KB of LDS only once asked for.
@@ -1154,7 +1177,7 @@ __global__ __launch_bounds__(kBlock) void k_bscatter(const float* __restrict__ x
 }
 
 template <bool IDS>
-__global__ __launch_bounds__(kReduceBlock) void k_breduce(const unsigned* __restrict__ off, const float* __restrict__ rz,
+__global__ __launch_bounds__(kReduceBlock, IDS ? 4 : 8) void k_breduce(const unsigned* __restrict__ off, const float* __restrict__ rz,
                                                     const unsigned* __restrict__ rmeta, const int* __restrict__ rid,
                                                     const BuildItemDev* __restrict__ items, int n_items,
                                                     float* __restrict__ ground, float* __restrict__ ceil,
@@ -1349,8 +1372,8 @@ pct_status launch_build(const float* xyz, int64_t n, const GridDev& g, float zmi
             PCT_LAUNCH_CHECK();
         }
     }
-    const int cap = reduce_cap(n, g, ids);
-    const size_t rl = reduce_lds_bytes(g, ids, cap);
+    const int cap = reduce_cap(n, g);
+    const size_t rl = reduce_lds_bytes(g, N, ids, cap);
     if (ids && merge) {
         if (pct_status st = allow_lds((const void*)k_tile_reduce<true, true>, rl)) return st;
         hipLaunchKernelGGL((k_tile_reduce<true, true>), dim3(g.ntiles), dim3(kReduceBlock), rl, s, w.off, w.rz, w.rmeta,
@@ -1527,12 +1550,11 @@ pct_status launch_build_batched(const float* xyz, const BuildItemDev* h_items, i
     int max_tiles_lds = 0, cap = 0;
     for (int i = 0; i < n_items; ++i) {
         if (h_items[i].g.ntiles <= kMaxLdsTiles) max_tiles_lds = std::max(max_tiles_lds, h_items[i].g.ntiles);
-        cap = std::max(cap, reduce_cap(h_items[i].n, h_items[i].g, ids));
+        cap = std::max(cap, reduce_cap(h_items[i].n, h_items[i].g));
     }
-    cap = std::max(cap, ids ? kReduceCapIds : kReduceCap);
-    // the largest tile (tw x th cells) of any item sizes the counters
+    // the largest tile (tw x th cells) and plane count of any item size the bit matrix
     size_t max_reduce_lds = 0;
-    for (int i = 0; i < n_items; ++i) max_reduce_lds = std::max(max_reduce_lds, reduce_lds_bytes(h_items[i].g, ids, cap));
+    for (int i = 0; i < n_items; ++i) max_reduce_lds = std::max(max_reduce_lds, reduce_lds_bytes(h_items[i].g, h_items[i].N, ids, cap));
     if (pct_status st = allow_lds(ids ? (const void*)k_breduce<true> : (const void*)k_breduce<false>, max_reduce_lds))
         return st;
     hipLaunchKernelGGL(k_fill_u32, dim3(std::min(1024, w.total_tiles / kBlock + 1)), dim3(kBlock), 0, s, w.count,

@@ -124,6 +124,33 @@ def test_build_edge_cases(P, oracle_lib):
     check_tomogram(P, oracle_lib, e, grid)
 
 
+@pytest.mark.parametrize("planes,z0,ds,per_cell", [(31, 0.0, 0.25, 30), (32, -3.7, 0.3, 30), (33, 1e4, 0.3, 60),
+                                                   (64, -2e3, 0.11, 90), (300, 5.0, 0.05, 120), (1024, -40.0, 0.07, 900)])
+@pytest.mark.parametrize("ids", [True, False])
+def test_build_many_occupied_bins(P, oracle_lib, planes, z0, ds, per_cell, ids):
+    """Heights over the whole stack, on planes and beside them (the next
+    float below and above), with many equal ones: every occupied bin of a
+    cell, tiles whose bins exceed the LDS slots, words of the bit matrix
+    filled to their ends, and planes coarse in FP32 far from zero."""
+    rng = np.random.default_rng(planes)
+    nx, ny = (300, 5) if per_cell < 100 else (45, 3)
+    grid = dict(x0=-2.0, y0=1.0, res=0.2, nx=nx, ny=ny, slice_dz=ds)
+    n = nx * ny * per_cell
+    h = (np.float32(z0) + (np.arange(planes, dtype=np.float32) + np.float32(1)) * np.float32(ds)).astype(np.float32)
+    z = np.empty(n, np.float32)
+    kind = rng.integers(0, 4, n)
+    on = h[rng.integers(0, planes - 1, n)]
+    z = np.where(kind == 0, on, np.where(kind == 1, np.nextafter(on, np.float32(-np.inf)),
+                 np.where(kind == 2, np.nextafter(on, np.float32(np.inf)),
+                          rng.uniform(z0, float(h[-2]), n).astype(np.float32)))).astype(np.float32)
+    z = np.maximum(z, np.float32(z0))
+    z[:2] = np.float32(z0), np.nextafter(h[-2], np.float32(np.inf))     # the lowest point and one in the last bin
+    xy = np.stack([rng.uniform(-2.0, -2.0 + 0.2 * nx, n), rng.uniform(1.0, 1.0 + 0.2 * ny, n)], 1)
+    xy[:2] = [[-1.9, 1.1], [-1.9, 1.1]]
+    ext, _, _ = check_tomogram(P, oracle_lib, np.concatenate([xy, z[:, None]], 1).astype(np.float32), grid, ids)
+    assert ext.n_slices == planes
+
+
 def test_build_deterministic(P):
     sc = crop_scene(seed=23, n=300_000)
     say("determinism")
