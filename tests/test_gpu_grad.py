@@ -291,3 +291,29 @@ def test_window_boxes(P, oracle_lib, world, d_inf, d_sm, layout):
                                 sl_t.expand(len(rs), -1, -1).contiguous(), gf, n_points=n,
                                 out=(f2, gwp2, None, None, acc2))
     assert torch.equal(f2, torch.stack(f1)) and torch.equal(gwp2, torch.stack(gwp1)) and torch.equal(acc1, acc2)
+
+
+@pytest.mark.parametrize("d_inf,d_sm,rp", [(0.1, 0.2, 1), (0.2, 0.3, 1), (0.2, 0.4, 2), (0.3, 0.4, 1), (0.3, 0.5, 1),
+                                           (0.4, 0.5, 1), (0.4, 0.6, 1), (0.3, 0.6, 4), (0.5, 0.6, 1)])
+@pytest.mark.parametrize("dense", [True, False])
+def test_eval_bwd_tiles(P, oracle_lib, world, d_inf, d_sm, rp, dense):
+    """The dense traversability adjoint at inflation radii 1 to 9 and patch
+    radii 1 to 4 (tiles of 128, 64, 32 and 16 cells, and windows over the map),
+    for a gradient at every cell of a few slices and at scattered cells,
+    corners of the map among them, in fixed point and with float sums."""
+    import torch
+    w, rng = world, np.random.default_rng(3)
+    r = dict(w["r"], d_inf=d_inf, d_sm=d_sm, patch_radius=rp)
+    N, ny, nx = w["tm"]["ground"].shape
+    gc = np.zeros((N, ny, nx), np.float32)
+    if dense:
+        gc[[0, 3, N - 1]] = rng.normal(size=(3, ny, nx))
+    else:
+        gc[rng.integers(0, N, 200), rng.integers(0, ny, 200), rng.integers(0, nx, 200)] = rng.normal(size=200)
+        gc[1, [0, 0, ny - 1, ny - 1], [0, nx - 1, 0, nx - 1]] = 1.0
+    rG, rC, unc = oracle_lib.eval_bwd(w["tm"]["ground"], w["tm"]["ceil"], w["g"]["res"], r, gc.astype(np.float64))
+    for det in (True, False):
+        gG, gC = P.pct_eval_traversability_bwd(w["G"], w["C"], w["g"], w["ext"], r, torch.from_numpy(gc).cuda(),
+                                               deterministic=det)
+        close(gG.cpu().numpy(), rG, ~unc)
+        close(gC.cpu().numpy(), rC, ~unc)
