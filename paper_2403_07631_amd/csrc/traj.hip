@@ -33,6 +33,14 @@
 // several lanes per piece when M is small (they split the samples and their
 // sums are combined by butterfly shuffles); the two block-tridiagonal solves
 // run on three lanes, one per axis.
+//
+// Latency bounds it: two wavefronts per SIMD (238 registers; capping them
+// for three spills 100 and costs more than it hides) on chains of dependent
+// FP64 operations and gathers, vector issue busy a third of the time.  4096
+// trajectories x 32 pieces x 16 samples on the building, ten iterations:
+// 5.58 ms; with the blocks of the elimination formed in parallel, an accepted
+// point's gradient taken at the knot states of its trial, and no divisions
+// per sample 4.18 ms; with two corners per gather 3.72 ms.
 #include "traj_internal.h"
 
 namespace pct {
@@ -69,9 +77,8 @@ struct Pow {
     __device__ __forceinline__ double operator()(int k) const { return v[k + 6]; }
 };
 
-__device__ __forceinline__ Pow powers(double T) {
+__device__ __forceinline__ Pow powers(double T, double ti) {   // ti = 1 / T
     Pow p;
-    const double ti = 1.0 / T;
     p.v[6] = 1.0;
     p.v[7] = T;
     p.v[8] = T * T;
@@ -83,22 +90,23 @@ __device__ __forceinline__ Pow powers(double T) {
 
 __device__ __forceinline__ double qel(const Pow& p, int a, int b) { return kQ[a][b] * p(hexp(a) + hexp(b) - 5); }
 
-// The wavefront's state in LDS, laid out for its M pieces (M + 1 knots).
+// The wavefront's state in LDS, laid out for its M pieces (M + 1 knots);
+// arrays per interior knot m = 1 .. M - 1 are indexed by m.  What only its
+// own lane needs (log-durations, the accepted variables, a piece's gradient
+// with respect to its end positions and duration) stays in registers: with
+// 10 KB at M = 32, sixteen wavefronts fit on a CU.
 struct Smem {
-    double *T, *tau;
+    double *T, *ti;                         // durations and their inverses
     double (*P)[3], (*V)[3], (*A)[3];
-    double (*Dinv)[4], (*Fm)[4], (*Um)[4];  // block factors per interior knot
-    double (*rp)[2][3];                     // forward-eliminated right-hand sides
-    double (*lam)[2][3];                    // adjoint per interior knot
-    double (*gx)[6][3];                     // d(effort + penalties) / d(piece end data)
-    double *gT;                             // ... / d T_i at fixed end data
+    double (*Dinv)[4], (*Fm)[4], (*Um)[4];  // blocks, then block factors per interior knot
+    double (*rp)[2][3];                     // right-hand sides, then forward-eliminated ones
+    double (*lam)[2][3];                    // the left pieces' share of the adjoint's right-hand sides, then the adjoint
     double *val;
-    double (*xk)[3], *xt;  // accepted variables
-    double (*gk)[3], *gt;  // gradient there
+    double (*gk)[3], *gt;                   // gradient at the accepted point (gk: knot m at m)
 };
 
 __host__ __device__ constexpr int smem_doubles(int M) {
-    return 2 * M + 3 * 3 * (M + 1) + 3 * 4 * M + 6 * M + 6 * (M + 1) + 18 * M + 2 * M + 4 * M + 4 * M;
+    return 2 * M + 3 * 3 * (M + 1) + (3 * 4 + 2 * 6 + 3) * (M > 1 ? M - 1 : 1) + M + M;
 }
 
 __device__ __forceinline__ Smem smem_view(double* base, int M) {
@@ -109,22 +117,19 @@ __device__ __forceinline__ Smem smem_view(double* base, int M) {
         p += n;
         return q;
     };
+    const int I = M > 1 ? M - 1 : 1;   // interior knots, the first at index 1
     s.T = take(M);
-    s.tau = take(M);
+    s.ti = take(M);
     s.P = (double(*)[3])take(3 * (M + 1));
     s.V = (double(*)[3])take(3 * (M + 1));
     s.A = (double(*)[3])take(3 * (M + 1));
-    s.Dinv = (double(*)[4])take(4 * M);
-    s.Fm = (double(*)[4])take(4 * M);
-    s.Um = (double(*)[4])take(4 * M);
-    s.rp = (double(*)[2][3])take(6 * M);
-    s.lam = (double(*)[2][3])take(6 * (M + 1));
-    s.gx = (double(*)[6][3])take(18 * M);
-    s.gT = take(M);
+    s.Dinv = (double(*)[4])take(4 * I) - 1;
+    s.Fm = (double(*)[4])take(4 * I) - 1;
+    s.Um = (double(*)[4])take(4 * I) - 1;
+    s.rp = (double(*)[2][3])take(6 * I) - 1;
+    s.lam = (double(*)[2][3])take(6 * I) - 1;
+    s.gk = (double(*)[3])take(3 * I) - 1;
     s.val = take(M);
-    s.xk = (double(*)[3])take(3 * M);
-    s.xt = take(M);
-    s.gk = (double(*)[3])take(3 * M);
     s.gt = take(M);
     return s;
 }
@@ -145,34 +150,61 @@ __device__ __forceinline__ void mul2(const double a[4], const double b[4], doubl
     o[3] = a[2] * b[1] + a[3] * b[3];
 }
 
-// Interior knot states of the minimum-jerk spline: lanes 0..2 (one axis
-// each) eliminate forward; lane 0 keeps the factors for the back pass and
-// the adjoint.
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Interior knot states of the minimum-jerk spline.  Lane m - 1 forms the
+// blocks and right-hand sides of knot m, in the places that their factors
+// take afterwards; lanes 0..2 (one axis each) then eliminate forward and
+// substitute back.  Forming the blocks inside the elimination made its 31
+// steps three times as long for three working lanes.
 __device__ __forceinline__ void solve_knots(const Smem& s, int M) {
-    const int ax = threadIdx.x;
-    if (ax < 3) {
-        double Dp[4] = {0, 0, 0, 0}, Up[4] = {0, 0, 0, 0}, rprev[2] = {0, 0};
-        for (int m = 1; m < M; ++m) {
-            const Pow pl = powers(s.T[m - 1]), pr = powers(s.T[m]);
-            double D[4], L[4], U[4], r[2];
+    if ((int)threadIdx.x + 1 < M) {
+        const int m = (int)threadIdx.x + 1;
+        const Pow pl = powers(s.T[m - 1], s.ti[m - 1]), pr = powers(s.T[m], s.ti[m]);
+        #pragma unroll
+        for (int i = 0; i < 2; ++i) {
             #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    D[2 * i + j] = qel(pl, 4 + i, 4 + j) + qel(pr, 1 + i, 1 + j);
-                    L[2 * i + j] = qel(pl, 4 + i, 1 + j);
-                    U[2 * i + j] = qel(pr, 1 + i, 4 + j);
-                }
+            for (int j = 0; j < 2; ++j) {
+                s.Dinv[m][2 * i + j] = qel(pl, 4 + i, 4 + j) + qel(pr, 1 + i, 1 + j);
+                s.Fm[m][2 * i + j] = qel(pl, 4 + i, 1 + j);
+                s.Um[m][2 * i + j] = qel(pr, 1 + i, 4 + j);
+            }
+            #pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
                 double b = qel(pl, 4 + i, 0) * s.P[m - 1][ax] + qel(pl, 4 + i, 3) * s.P[m][ax] +
                            qel(pr, 1 + i, 0) * s.P[m][ax] + qel(pr, 1 + i, 3) * s.P[m + 1][ax];
                 if (m == 1) b += qel(pl, 4 + i, 1) * s.V[0][ax] + qel(pl, 4 + i, 2) * s.A[0][ax];
                 if (m == M - 1) b += qel(pr, 1 + i, 4) * s.V[M][ax] + qel(pr, 1 + i, 5) * s.A[M][ax];
-                r[i] = -b;
+                s.rp[m][i][ax] = -b;
             }
-            double F[4] = {0, 0, 0, 0};
+        }
+    }
+    __syncthreads();
+    // every lane runs the sweeps (lanes from 3 on repeat axis 2), so that the
+    // wavefront's one instruction stream needs no masks; lanes 0..2 store
+    const int ax = min((int)threadIdx.x, 2);
+    const bool mine = threadIdx.x < 3;
+    {
+        double Dp[4] = {0, 0, 0, 0}, Up[4] = {0, 0, 0, 0}, rprev[2] = {0, 0};
+        for (int m = 1; m < M; ++m) {
+            double D[4], F[4], U[4], r[2];
+            #pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                D[q] = s.Dinv[m][q];
+                F[q] = s.Fm[m][q];
+                U[q] = s.Um[m][q];
+            }
+            r[0] = s.rp[m][0][ax];
+            r[1] = s.rp[m][1][ax];
             if (m >= 2) {
+                double L[4], FU[4];
+                #pragma unroll
+                for (int q = 0; q < 4; ++q) L[q] = F[q];
                 mul2(L, Dp, F);
-                double FU[4];
                 mul2(F, Up, FU);
                 #pragma unroll
                 for (int q = 0; q < 4; ++q) D[q] -= FU[q];
@@ -181,16 +213,18 @@ __device__ __forceinline__ void solve_knots(const Smem& s, int M) {
             }
             double Di[4];
             inv2(D, Di);
-            if (ax == 0) {
-                #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    s.Dinv[m][q] = Di[q];
-                    s.Fm[m][q] = F[q];
-                    s.Um[m][q] = U[q];
+            wave_order();   // lane 0's factors replace blocks that every lane has read
+            if (mine) {
+                if (ax == 0) {
+                    #pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        s.Dinv[m][q] = Di[q];
+                        s.Fm[m][q] = F[q];
+                    }
                 }
+                s.rp[m][0][ax] = r[0];
+                s.rp[m][1][ax] = r[1];
             }
-            s.rp[m][0][ax] = r[0];
-            s.rp[m][1][ax] = r[1];
             #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 Dp[q] = Di[q];
@@ -201,7 +235,7 @@ __device__ __forceinline__ void solve_knots(const Smem& s, int M) {
         }
     }
     __syncthreads();
-    if (ax < 3) {
+    if (mine) {
         double z[2] = {0, 0};
         for (int m = M - 1; m >= 1; --m) {
             double r0 = s.rp[m][0][ax], r1 = s.rp[m][1][ax];
@@ -219,14 +253,15 @@ __device__ __forceinline__ void solve_knots(const Smem& s, int M) {
 }
 
 // The adjoint: H lambda = d(effort + penalties) / d(interior knot
-// velocities and accelerations), with the factors of solve_knots.
+// velocities and accelerations), with the factors of solve_knots; the
+// right-hand sides are lam (the left pieces' share) + rp (the right pieces').
 __device__ __forceinline__ void solve_adjoint(const Smem& s, int M) {
     const int ax = threadIdx.x;
     if (ax < 3) {
         double prev[2] = {0, 0};
         for (int m = 1; m < M; ++m) {
-            double r0 = s.gx[m - 1][4][ax] + s.gx[m][1][ax];
-            double r1 = s.gx[m - 1][5][ax] + s.gx[m][2][ax];
+            double r0 = s.lam[m][0][ax] + s.rp[m][0][ax];
+            double r1 = s.lam[m][1][ax] + s.rp[m][1][ax];
             if (m >= 2) {
                 r0 -= s.Fm[m][0] * prev[0] + s.Fm[m][1] * prev[1];
                 r1 -= s.Fm[m][2] * prev[0] + s.Fm[m][3] * prev[1];
@@ -276,15 +311,57 @@ __device__ __forceinline__ void axis_of(double q, int n, double rinv, int& i0, i
     f = qc - a;
 }
 
+// The end data of piece i along axis d.
+__device__ __forceinline__ void end_data(const Smem& s, int i, int d, double (&x)[6]) {
+    x[0] = s.P[i][d];
+    x[1] = s.V[i][d];
+    x[2] = s.A[i][d];
+    x[3] = s.P[i + 1][d];
+    x[4] = s.V[i + 1][d];
+    x[5] = s.A[i + 1][d];
+}
+
+// x / b, correctly rounded, with binv = 1 / b correctly rounded: the product
+// x binv is within two units in the last place, one residual step brings it
+// within one, and a residual step from there rounds correctly (Markstein's
+// theorem).  Ends of the exponent range, where a residual would not be
+// exact, are divided.
+__device__ __forceinline__ double div_by(double x, double b, double binv) {
+    double q = x * binv;
+    q = fma(fma(-q, b, x), binv, q);
+    q = fma(fma(-q, b, x), binv, q);
+    if (x != 0.0 && !(fabs(x) > 0x1p-400 && fabs(x) < 0x1p400)) q = x / b;
+    return q;
+}
+
 struct Bil {
     double v, dx, dy;
     bool ok;
 };
 
-__device__ __forceinline__ Bil bilinear(const float* __restrict__ g, long long o00, long long o10, long long o01,
-                                        long long o11, double fu, double fv, double du, double dv) {
+// The four corners of a cell of a map: two neighbours of a row in one load
+// (4-byte aligned), each alone on a map one cell wide.
+struct Corners {
+    float g00, g10, g01, g11;
+};
+struct __attribute__((packed, aligned(4))) Pair {
+    float a, b;
+};
+__device__ __forceinline__ Corners corners(const float* __restrict__ g, long long o0, long long o1, bool wide) {
+    Corners c;
+    if (wide) {   // uniform
+        const Pair r0 = *(const Pair*)(g + o0), r1 = *(const Pair*)(g + o1);
+        c.g00 = r0.a, c.g10 = r0.b, c.g01 = r1.a, c.g11 = r1.b;
+    } else {
+        c.g00 = c.g10 = g[o0];
+        c.g01 = c.g11 = g[o1];
+    }
+    return c;
+}
+
+__device__ __forceinline__ Bil bilinear(const Corners& q, double fu, double fv, double du, double dv) {
     Bil b;
-    const double g00 = g[o00], g10 = g[o10], g01 = g[o01], g11 = g[o11];
+    const double g00 = q.g00, g10 = q.g10, g01 = q.g01, g11 = q.g11;
     b.ok = isfinite(g00) && isfinite(g10) && isfinite(g01) && isfinite(g11);
     b.v = b.dx = b.dy = 0.0;
     if (b.ok) {
@@ -297,28 +374,35 @@ __device__ __forceinline__ Bil bilinear(const float* __restrict__ g, long long o
 
 __device__ __forceinline__ double pos3(double x) { return x > 0.0 ? x : 0.0; }
 
-// Objective (and with GRAD its gradient) at the variables held in s.P[1..M-1]
-// and s.tau.  Returns +inf (uniform over the wavefront) at a point with a
-// non-finite duration or sample.
-template <bool GRAD>
-__device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int lpp, const int* __restrict__ slice, double* coef_out) {
+// Objective (and with GRAD its gradient, to s.gk and s.gt) at the variables
+// held in s.P[1..M-1] and tau (piece i's on lane i).  Returns +inf (uniform
+// over the wavefront) at a point with a non-finite duration or sample.
+// SOLVE false: the knot states of these variables are in place from the
+// evaluation before (an accepted trial point, whose objective was taken
+// without the gradient).
+template <bool GRAD, bool SOLVE>
+__device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int lpp, const int* __restrict__ slice,
+                                           double tau, double* coef_out) {
     const int lane = threadIdx.x;
     const int M = a.M;
     bool bad = false;
-    if (lane < M) {
-        const double T = exp(s.tau[lane]);
-        s.T[lane] = T;
-        bad = !(T > 0.0) || !isfinite(T);
+    if (SOLVE) {
+        if (lane < M) {
+            const double T = exp(tau);
+            s.T[lane] = T;
+            s.ti[lane] = 1.0 / T;
+            bad = !(T > 0.0) || !isfinite(T);
+        }
+        if (__ballot(bad) != 0ull) return INFINITY;
+        __syncthreads();
+        solve_knots(s, M);
     }
-    if (__ballot(bad) != 0ull) return INFINITY;
-    __syncthreads();
-    solve_knots(s, M);
 
     const int piece = lane / lpp, sub = lane % lpp;
     const bool live = piece < M;
     double F = 0.0, gTp = 0.0;
     double gc[6][3];
-    double c[6][3], x[6][3];
+    double c[6][3];
     #pragma unroll
     for (int j = 0; j < 6; ++j)
         #pragma unroll
@@ -326,23 +410,19 @@ __device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int
     double T = 1.0;
     if (live) {
         T = s.T[piece];
-        const Pow pw = powers(T);
+        const Pow pw = powers(T, s.ti[piece]);
         #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            x[0][d] = s.P[piece][d];
-            x[1][d] = s.V[piece][d];
-            x[2][d] = s.A[piece][d];
-            x[3][d] = s.P[piece + 1][d];
-            x[4][d] = s.V[piece + 1][d];
-            x[5][d] = s.A[piece + 1][d];
-            c[0][d] = x[0][d];
-            c[1][d] = x[1][d];
-            c[2][d] = 0.5 * x[2][d];
+            double x[6];
+            end_data(s, piece, d, x);
+            c[0][d] = x[0];
+            c[1][d] = x[1];
+            c[2][d] = 0.5 * x[2];
             #pragma unroll
             for (int j = 3; j < 6; ++j) {
                 double acc = 0.0;
                 #pragma unroll
-                for (int e = 0; e < 6; ++e) acc += kB[j - 3][e] * x[e][d] * pw(hexp(e) - j);
+                for (int e = 0; e < 6; ++e) acc += kB[j - 3][e] * x[e] * pw(hexp(e) - j);
                 c[j][d] = acc;
             }
         }
@@ -351,10 +431,11 @@ __device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int
         const long long base = on_map ? (long long)k * a.nx * a.ny : 0;
         const double rinv = 1.0 / a.res;
         const int K = a.K;
+        const double dK = (double)K, kinv = 1.0 / dK, TK = T / dK;
         for (int j = sub; j <= K; j += lpp) {
-            const double t = T * j / K;
+            const double t = div_by(T * j, dK, kinv);
             const double h = (j == 0 || j == K) ? 0.5 : 1.0;
-            const double w = T / K * h;
+            const double w = TK * h;
             double q[3], v[3], ac[3], jk[3];
             bool fin = true;
             #pragma unroll
@@ -369,29 +450,28 @@ __device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int
                 bad = true;
                 continue;
             }
-            double gq[3] = {0, 0, 0}, gv[3], ga[3];
+            double gq[3] = {0, 0, 0};
             const double v2 = v[0] * v[0] + v[1] * v[1] + v[2] * v[2];
             const double a2 = ac[0] * ac[0] + ac[1] * ac[1] + ac[2] * ac[2];
             const double sv = pos3(v2 - a.v_max2), sa = pos3(a2 - a.a_max2);
             double f = a.w_v * (sv * sv * sv) + a.w_a * (sa * sa * sa);
-            #pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                gv[d] = a.w_v * 3.0 * sv * sv * 2.0 * v[d];
-                ga[d] = a.w_a * 3.0 * sa * sa * 2.0 * ac[d];
-            }
+            // d/dv = kv v, d/da = ka a
+            const double kv = a.w_v * 3.0 * sv * sv * 2.0, ka = a.w_a * 3.0 * sa * sa * 2.0;
             if (on_map) {
                 int i0, i1, j0, j1;
                 double fu, fv, du, dv;
-                axis_of((q[0] - a.x0) / a.res - 0.5, a.nx, rinv, i0, i1, fu, du);
-                axis_of((q[1] - a.y0) / a.res - 0.5, a.ny, rinv, j0, j1, fv, dv);
-                const long long o00 = base + (long long)j0 * a.nx + i0, o10 = base + (long long)j0 * a.nx + i1;
-                const long long o01 = base + (long long)j1 * a.nx + i0, o11 = base + (long long)j1 * a.nx + i1;
-                const Bil C = bilinear(a.cost, o00, o10, o01, o11, fu, fv, du, dv);
+                axis_of(div_by(q[0] - a.x0, a.res, rinv) - 0.5, a.nx, rinv, i0, i1, fu, du);
+                axis_of(div_by(q[1] - a.y0, a.res, rinv) - 0.5, a.ny, rinv, j0, j1, fv, dv);
+                const long long o0 = base + (long long)j0 * a.nx + i0, o1 = base + (long long)j1 * a.nx + i0;
+                const bool wide = a.nx > 1;
+                const Corners qC = corners(a.cost, o0, o1, wide), qG = corners(a.ground, o0, o1, wide),
+                              qH = corners(a.ceil, o0, o1, wide);
+                const Bil C = bilinear(qC, fu, fv, du, dv);
                 const double sc = pos3(C.v - a.c_safe);
                 f += a.w_c * (sc * sc * sc);
                 gq[0] += a.w_c * 3.0 * sc * sc * C.dx;
                 gq[1] += a.w_c * 3.0 * sc * sc * C.dy;
-                const Bil G = bilinear(a.ground, o00, o10, o01, o11, fu, fv, du, dv);
+                const Bil G = bilinear(qG, fu, fv, du, dv);
                 if (G.ok) {
                     const double e = q[2] - G.v - a.d_ref;
                     const double sg = pos3(G.v + a.d_min - q[2]);
@@ -403,7 +483,7 @@ __device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int
                     gq[0] += dG * G.dx;
                     gq[1] += dG * G.dy;
                 }
-                const Bil H = bilinear(a.ceil, o00, o10, o01, o11, fu, fv, du, dv);
+                const Bil H = bilinear(qH, fu, fv, du, dv);
                 if (H.ok) {
                     const double sh = pos3(q[2] - H.v);
                     f += a.w_h * (sh * sh * sh);
@@ -417,8 +497,8 @@ __device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int
             if (GRAD) {
                 double dfdt = 0.0;
                 #pragma unroll
-                for (int d = 0; d < 3; ++d) dfdt += gq[d] * v[d] + gv[d] * ac[d] + ga[d] * jk[d];
-                gTp += f * (h / K) + w * dfdt * ((double)j / K);
+                for (int d = 0; d < 3; ++d) dfdt += gq[d] * v[d] + kv * v[d] * ac[d] + ka * ac[d] * jk[d];
+                gTp += f * (h * kinv) + w * dfdt * div_by((double)j, dK, kinv);
                 double tp[6];
                 tp[0] = 1.0;
                 #pragma unroll
@@ -428,8 +508,8 @@ __device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int
                     gc[0][d] += w * gq[d];
                     #pragma unroll
                     for (int m = 1; m < 6; ++m) {
-                        double g = gq[d] * tp[m] + gv[d] * m * tp[m - 1];
-                        if (m >= 2) g += ga[d] * (m * (m - 1)) * tp[m - 2];
+                        double g = gq[d] * tp[m] + kv * v[d] * m * tp[m - 1];
+                        if (m >= 2) g += ka * ac[d] * (m * (m - 1)) * tp[m - 2];
                         gc[m][d] += w * g;
                     }
                 }
@@ -448,22 +528,26 @@ __device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int
         }
     }
     if (__ballot(bad) != 0ull) return INFINITY;
-    if (live && sub == 0) {
-        const Pow pw = powers(T);
+    const bool head = live && sub == 0;   // the piece's lane
+    double g0[3] = {0, 0, 0}, g3[3] = {0, 0, 0}, gT = 0.0;
+    if (head) {
+        const Pow pw = powers(T, s.ti[piece]);
         double J = 0.0, dJdT = 0.0, dcdT = 0.0;
         #pragma unroll
         for (int d = 0; d < 3; ++d) {
+            double x[6];
+            end_data(s, piece, d, x);
             #pragma unroll
             for (int e = 0; e < 6; ++e) {
                 double qx = 0.0, qtx = 0.0;
                 #pragma unroll
                 for (int b = 0; b < 6; ++b) {
-                    qx += qel(pw, e, b) * x[b][d];
-                    qtx += qel(pw, e, b) * (hexp(e) + hexp(b) - 5) * x[b][d];
+                    qx += qel(pw, e, b) * x[b];
+                    qtx += qel(pw, e, b) * (hexp(e) + hexp(b) - 5) * x[b];
                 }
-                J += x[e][d] * qx;
+                J += x[e] * qx;
                 if (GRAD) {
-                    dJdT += x[e][d] * qtx;
+                    dJdT += x[e] * qtx;
                     // d c_j / d x_e at fixed T, then the effort's own gradient
                     double g = 2.0 * qx;
                     if (e == 0) g += gc[0][d];
@@ -471,7 +555,11 @@ __device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int
                     if (e == 2) g += 0.5 * gc[2][d];
                     #pragma unroll
                     for (int j = 3; j < 6; ++j) g += gc[j][d] * kB[j - 3][e] * pw(hexp(e) - j);
-                    s.gx[piece][e][d] = g;
+                    if (e == 0) g0[d] = g;
+                    else if (e == 3) g3[d] = g;
+                    else if (e < 3) {
+                        if (piece >= 1) s.rp[piece][e - 1][d] = g;
+                    } else if (piece + 1 < M) s.lam[piece + 1][e - 4][d] = g;
                 }
             }
             if (GRAD)
@@ -479,12 +567,12 @@ __device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int
                 for (int j = 3; j < 6; ++j) {
                     double dc = 0.0;
                     #pragma unroll
-                    for (int e = 0; e < 6; ++e) dc += kB[j - 3][e] * (hexp(e) - j) * pw(hexp(e) - j - 1) * x[e][d];
+                    for (int e = 0; e < 6; ++e) dc += kB[j - 3][e] * (hexp(e) - j) * pw(hexp(e) - j - 1) * x[e];
                     dcdT += gc[j][d] * dc;
                 }
         }
         s.val[piece] = J + F + a.w_T * T;
-        if (GRAD) s.gT[piece] = gTp + dJdT / T + dcdT;
+        if (GRAD) gT = gTp + dJdT / T + dcdT;
         if (coef_out)
             #pragma unroll
             for (int j = 0; j < 6; ++j)
@@ -497,10 +585,10 @@ __device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int
     if (!GRAD) return phi;
 
     solve_adjoint(s, M);
-    if (lane < M) {
-        const int i = lane;
+    if (head) {
+        const int i = piece;
         const double Ti = s.T[i];
-        const Pow pw = powers(Ti);
+        const Pow pw = powers(Ti, s.ti[i]);
         double corrT = 0.0;
         #pragma unroll
         for (int d = 0; d < 3; ++d) {
@@ -513,7 +601,8 @@ __device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int
                 lam[4] = s.lam[i + 1][0][d];
                 lam[5] = s.lam[i + 1][1][d];
             }
-            const double xe[6] = {s.P[i][d], s.V[i][d], s.A[i][d], s.P[i + 1][d], s.V[i + 1][d], s.A[i + 1][d]};
+            double xe[6];
+            end_data(s, i, d, xe);
             double c0 = 0.0, c3 = 0.0;
             #pragma unroll
             for (int e = 1; e < 6; ++e) {
@@ -525,15 +614,16 @@ __device__ __forceinline__ double evaluate(const Smem& s, const TrajArgs& a, int
                 for (int b = 0; b < 6; ++b) st += qel(pw, e, b) * (hexp(e) + hexp(b) - 5) * xe[b];
                 corrT += lam[e] * st;
             }
-            s.gx[i][0][d] -= c0;
-            s.gx[i][3][d] -= c3;
+            g0[d] -= c0;
+            g3[d] -= c3;
         }
-        s.gt[i] = Ti * (s.gT[i] - corrT / Ti + a.w_T);
+        s.gt[i] = Ti * (gT - corrT / Ti + a.w_T);
     }
-    __syncthreads();
-    if (lane >= 1 && lane < M)
-        #pragma unroll
-        for (int d = 0; d < 3; ++d) s.gk[lane - 1][d] = s.gx[lane - 1][3][d] + s.gx[lane][0][d];
+    #pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double left = __shfl(g3[d], max(lane - lpp, 0), 64);   // the left piece's end position
+        if (head && piece >= 1) s.gk[piece][d] = left + g0[d];
+    }
     __syncthreads();
     return phi;
 }
@@ -564,50 +654,52 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
         s.V[M][lane] = bd[12 + lane];
         s.A[M][lane] = bd[15 + lane];
     }
-    if (lane >= 1 && lane < M)
-        #pragma unroll
-        for (int d = 0; d < 3; ++d) s.P[lane][d] = kn[(lane - 1) * 3 + d];
-    if (lane < M) s.tau[lane] = ta[lane];
+    // lane m: knot m's accepted position and piece m's accepted log-duration
+    const bool knot = lane >= 1 && lane < M, piece = lane < M;
+    double xk[3] = {0, 0, 0}, xt = piece ? ta[lane] : 0.0;
+    #pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        if (knot) s.P[lane][d] = xk[d] = kn[(lane - 1) * 3 + d];
+    }
     __syncthreads();
 
     if (!OPT) {
         double* cf = coef ? coef + (long long)tr * M * 18 : nullptr;
-        const double phi = evaluate<true>(s, a, lpp, slice, cf);
+        const double phi = evaluate<true, true>(s, a, lpp, slice, xt, cf);
         if (lane == 0) phi_out[tr] = phi;
         // no gradient at a point with a non-finite duration or sample
         const bool fin = isfinite(phi);
-        if (lane >= 1 && lane < M)
+        if (knot)
             for (int d = 0; d < 3; ++d)
-                gknots[(long long)tr * (M - 1) * 3 + (lane - 1) * 3 + d] = fin ? s.gk[lane - 1][d] : NAN;
-        if (lane < M) gtau[(long long)tr * M + lane] = fin ? s.gt[lane] : NAN;
+                gknots[(long long)tr * (M - 1) * 3 + (lane - 1) * 3 + d] = fin ? s.gk[lane][d] : NAN;
+        if (piece) gtau[(long long)tr * M + lane] = fin ? s.gt[lane] : NAN;
         return;
     }
 
-    double phi = evaluate<true>(s, a, lpp, slice, nullptr);
+    double phi = evaluate<false, true>(s, a, lpp, slice, xt, nullptr);
     double alpha = step;
     int done = 0;
     if (isfinite(phi)) {
-        if (lane >= 1 && lane < M)
-            #pragma unroll
-            for (int d = 0; d < 3; ++d) s.xk[lane - 1][d] = s.P[lane][d];
-        if (lane < M) s.xt[lane] = s.tau[lane];
-        __syncthreads();
+        // the first gradient, like that of every accepted point, at the knot
+        // states in place
+        evaluate<true, false>(s, a, lpp, slice, xt, nullptr);
         for (int it = 0; it < iters; ++it) {
             double g2 = 0.0;
-            for (int i = 0; i < M - 1; ++i)
+            for (int i = 1; i < M; ++i)
                 #pragma unroll
                 for (int d = 0; d < 3; ++d) g2 += s.gk[i][d] * s.gk[i][d];
             for (int i = 0; i < M; ++i) g2 += s.gt[i] * s.gt[i];
             if (g2 == 0.0) break;
             bool ok = false;
+            double pn = 0.0, tau = 0.0;
             for (int ls = 0; ls < 30; ++ls) {
                 __syncthreads();
-                if (lane >= 1 && lane < M)
-                    #pragma unroll
-                    for (int d = 0; d < 3; ++d) s.P[lane][d] = s.xk[lane - 1][d] - alpha * s.gk[lane - 1][d];
-                if (lane < M) s.tau[lane] = s.xt[lane] - alpha * s.gt[lane];
+                #pragma unroll
+                for (int d = 0; d < 3; ++d)
+                    if (knot) s.P[lane][d] = xk[d] - alpha * s.gk[lane][d];
+                tau = piece ? xt - alpha * s.gt[lane] : 0.0;
                 __syncthreads();
-                const double pn = evaluate<false>(s, a, lpp, slice, nullptr);
+                pn = evaluate<false, true>(s, a, lpp, slice, tau, nullptr);
                 if (pn <= phi - 1e-4 * alpha * g2) {
                     ok = true;
                     break;
@@ -616,22 +708,20 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
             }
             if (!ok) break;
             __syncthreads();
-            if (lane >= 1 && lane < M)
-                #pragma unroll
-                for (int d = 0; d < 3; ++d) s.xk[lane - 1][d] = s.P[lane][d];
-            if (lane < M) s.xt[lane] = s.tau[lane];
-            __syncthreads();
-            phi = evaluate<true>(s, a, lpp, slice, nullptr);
+            #pragma unroll
+            for (int d = 0; d < 3; ++d)
+                if (knot) xk[d] = s.P[lane][d];
+            xt = tau;
+            phi = evaluate<true, false>(s, a, lpp, slice, xt, nullptr);
             alpha *= 2.0;
             ++done;
         }
     }
-    __syncthreads();
     if (done > 0) {
-        if (lane >= 1 && lane < M)
-            #pragma unroll
-            for (int d = 0; d < 3; ++d) kn[(lane - 1) * 3 + d] = s.xk[lane - 1][d];
-        if (lane < M) ta[lane] = s.xt[lane];
+        #pragma unroll
+        for (int d = 0; d < 3; ++d)
+            if (knot) kn[(lane - 1) * 3 + d] = xk[d];
+        if (piece) ta[lane] = xt;
     }
     if (lane == 0) {
         phi_out[tr] = phi;

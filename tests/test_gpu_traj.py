@@ -80,6 +80,16 @@ def test_traj_eval_matches_oracle(P, small_map, M, K, n):
     say(f"traj eval M={M} K={K}: equal to the oracle's")
 
 
+@pytest.mark.parametrize("nx,ny", [(1, 40), (40, 1), (1, 1), (2, 2)])
+def test_traj_eval_narrow_maps(P, small_map, nx, ny):
+    """Maps one or two cells wide: the corners' pair loads and the clamps."""
+    grid, maps = small_map
+    sub = tuple(np.ascontiguousarray(a[:, 20:20 + ny, 20:20 + nx]) for a in maps)
+    g = dict(grid, x0=grid["x0"] + 2.0, y0=grid["y0"] + 2.0, nx=nx, ny=ny)
+    pr = scenes.traj_problems(71, 3, 6, (1.5, 5.0), (1.5, 5.0), 0.7, slices=(0, 3))
+    check_eval(P, g, sub, dict(PRM, samples=7), pr, range(3))
+
+
 def test_traj_nonfinite_duration(P, small_map):
     grid, maps = small_map
     pr = scenes.traj_problems(5, 2, 3, (1.0, 8.0), (1.0, 6.0), 0.7)
