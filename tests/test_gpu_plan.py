@@ -111,6 +111,18 @@ def test_serpentine_and_edges(P, oracle_lib):
     check_against_oracle(P, oracle_lib, cT, eG, [0, 1], (299, 0, 0), [(0, 0, 0), (5, 0, 1)], "one row")
 
 
+@pytest.mark.parametrize("ny,nx,pitch", [(63, 64, 2), (64, 65, 2), (65, 63, 2), (128, 1, 3), (40, 130, 2)])
+def test_visits_cut_short(P, oracle_lib, ny, nx, pitch):
+    """Corridors one cell wide that wind many times within a tile, so that a
+    visit's sweeps end before the tile is at its fixed point, at the edges of
+    tiles and on narrow maps; two layers with gateways between them."""
+    cT, eG = scenes.plan_serpentine(5, ny, nx, pitch=pitch, gap=1)
+    two = np.concatenate([cT, np.minimum(cT + 0.5, CB)]).astype(np.float32)
+    two[1, ::4] = np.minimum(two[1, ::4], two[0, ::4] * 0.5)
+    check_against_oracle(P, oracle_lib, two, np.concatenate([eG, eG]), [0, 1], (0, 0, 0),
+                         [(nx - 1, ny - 1, 0), (0, ny - 1, 1), (nx // 2, ny // 2, 0)], "winding tile")
+
+
 def test_tomogram_building(P, oracle_lib):
     """The section's setting: slices kept by the oracle's slice test of a
     three-storey building with stairs, Table I quadruped; the path climbs
