@@ -87,50 +87,58 @@ PlanGeom make_plan_geom(int nx, int ny, int L) {
     return g;
 }
 
-// Node cost (+inf where the node cannot be entered) and gateway bits.
+// Node cost (+inf where the node cannot be entered), gateway bits and the
+// distances' first value (+inf; the start takes 0 on its tile's first visit),
+// and an active flag for the start's tile alone.  A lane takes kPrepLayers
+// layers of its cell, so that a layer's ground and cost are read 1.25 times
+// instead of three (one node per thread: 295 us for the building's 30 layers,
+// distances included).
+constexpr int kPrepLayers = 8;
+
 __global__ __launch_bounds__(256) void k_plan_prep(const float* __restrict__ cost, const float* __restrict__ ground,
                                                    const int* __restrict__ layers, PlanGeom g, float cB,
-                                                   float* __restrict__ cn, uint8_t* __restrict__ gw) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.plane * g.L) return;
-    const int l = (int)(i / g.plane);
-    const long long c = i - (long long)l * g.plane;
-    const long long o = (long long)layers[l] * g.plane + c;
-    const float e = ground[o], t = cost[o];
-    float n = t;
-    unsigned bits = 0;
-    if (l + 1 < g.L) {
-        const long long a = (long long)layers[l + 1] * g.plane + c;
-        const float ea = ground[a], ta = cost[a];
-        if (ea == e) {
-            n = fminf(n, ta);
-            if (ta < t) bits |= kOutUp;
-            if (t < ta) bits |= kInFromAbove;
+                                                   float* __restrict__ cn, uint8_t* __restrict__ gw,
+                                                   double* __restrict__ dist, unsigned* __restrict__ flag,
+                                                   unsigned long long* __restrict__ key, int n_tiles, int t0,
+                                                   PlanStatus* __restrict__ st) {
+    const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long n_threads = (long long)gridDim.x * blockDim.x;
+    if (blockIdx.y == 0) {
+        if (c == 0) *st = PlanStatus{0u, 0u, ~0ull, ~0ull};
+        for (long long i = c; i < n_tiles; i += n_threads) {
+            flag[i] = i == t0 ? 1u : 0u;
+            key[i] = i == t0 ? 0ull : ~0ull;   // bits of +0.0
         }
     }
-    if (l > 0) {
-        const long long b = (long long)layers[l - 1] * g.plane + c;
-        const float eb = ground[b], tb = cost[b];
-        if (eb == e) {
-            n = fminf(n, tb);
-            if (tb < t) bits |= kOutDown;
-            if (t < tb) bits |= kInFromBelow;
-        }
+    if (c >= g.plane) return;
+    const int l0 = (int)blockIdx.y * kPrepLayers;
+    float e[kPrepLayers + 2], t[kPrepLayers + 2];   // layers l0 - 1 .. l0 + kPrepLayers
+#pragma unroll
+    for (int u = 0; u < kPrepLayers + 2; ++u) {
+        const long long o = (long long)layers[min(max(l0 - 1 + u, 0), g.L - 1)] * g.plane + c;
+        e[u] = ground[o];
+        t[u] = cost[o];
     }
-    cn[i] = n < cB ? n : INFINITY;
-    gw[i] = (uint8_t)bits;
-}
-
-__global__ __launch_bounds__(256) void k_plan_init(double* __restrict__ dist, long long n, long long s,
-                                                   unsigned* __restrict__ flag, unsigned long long* __restrict__ key,
-                                                   int n_tiles, int t0, PlanStatus* __restrict__ st) {
-    const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dist[i] = INFINITY;   // the start takes 0 on its tile's first visit
-    (void)s;
-    if (i == 0) *st = PlanStatus{0u, 0u, ~0ull, ~0ull};
-    if (i < n_tiles) {
-        flag[i] = i == t0 ? 1u : 0u;
-        key[i] = i == t0 ? 0ull : ~0ull;   // bits of +0.0
+#pragma unroll
+    for (int u = 1; u <= kPrepLayers; ++u) {
+        const int l = l0 - 1 + u;
+        if (l >= g.L) break;
+        float n = t[u];
+        unsigned bits = 0;
+        if (l + 1 < g.L && e[u + 1] == e[u]) {
+            n = fminf(n, t[u + 1]);
+            if (t[u + 1] < t[u]) bits |= kOutUp;
+            if (t[u] < t[u + 1]) bits |= kInFromAbove;
+        }
+        if (l > 0 && e[u - 1] == e[u]) {
+            n = fminf(n, t[u - 1]);
+            if (t[u - 1] < t[u]) bits |= kOutDown;
+            if (t[u] < t[u - 1]) bits |= kInFromBelow;
+        }
+        const long long i = (long long)l * g.plane + c;
+        cn[i] = n < cB ? n : INFINITY;
+        gw[i] = (uint8_t)bits;
+        dist[i] = INFINITY;
     }
 }
 
@@ -630,17 +638,12 @@ pct_status launch_plan(const float* cost, const float* ground, int nx, int ny, c
     const PlanGeom g = make_plan_geom(nx, ny, L);
     PlanWs w;
     plan_ws_layout(g, &w, ws_base);
-    const long long nn = g.plane * L;
     const int nt = g.ntx * g.nty * L;
     PCT_HIP(hipMemcpyAsync(w.layers, h_layers, sizeof(int) * (size_t)L, hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(k_plan_prep, dim3((unsigned)((nn + 255) / 256)), dim3(256), 0, s, cost, ground, w.layers, g, cB,
-                       w.cn, w.gw);
-    PCT_LAUNCH_CHECK();
     const long long src = (long long)sl * g.plane + (long long)sy * nx + sx;
     const int t0 = (sl * g.nty + sy / kPT) * g.ntx + sx / kPT;
-    const long long ni = std::max<long long>(nn, nt);
-    hipLaunchKernelGGL(k_plan_init, dim3((unsigned)((ni + 255) / 256)), dim3(256), 0, s, dist, nn, src, w.flag, w.key,
-                       nt, t0, w.st);
+    hipLaunchKernelGGL(k_plan_prep, dim3((unsigned)((g.plane + 255) / 256), (unsigned)((L + kPrepLayers - 1) / kPrepLayers)),
+                       dim3(256), 0, s, cost, ground, w.layers, g, cB, w.cn, w.gw, dist, w.flag, w.key, nt, t0, w.st);
     PCT_LAUNCH_CHECK();
     // Rounds take the active tiles whose activating distance lies within
     // a band of width delta above the least one (tiles roughly in order of
