@@ -173,11 +173,7 @@ __device__ __forceinline__ int from_next_i(int v) { return __builtin_amdgcn_upda
 #ifndef PCT_EVAL_PREFETCH
 #define PCT_EVAL_PREFETCH 4
 #endif
-#ifndef PCT_EVAL_STRIP_ROWS
-#define PCT_EVAL_STRIP_ROWS 256
-#endif
 constexpr int kPrefetch = PCT_EVAL_PREFETCH;   // rows fetched ahead per wavefront
-constexpr int kStripRows = PCT_EVAL_STRIP_ROWS; // output rows per strip (upper bound)
 
 struct StripGeom {
     int rows;   // output rows per strip
@@ -558,33 +554,49 @@ EvalShape tuned_shape(const EvalParams& p) {
 
 int strip_outw(int R, int nw) { return kWgOwn * std::max(1, nw) - 2 * R; }
 
-// shape.rows = 0: the tuned shape if one is recorded, else the default
-// (workgroup or wavefront strips as the columns fit best, 256 rows halved
-// while there are fewer than 16384 wavefronts, down to 32).
-StripGeom strip_geom(const EvalParams& p, EvalShape shape = EvalShape{0, 0}, bool two_wave = true) {
+// Strips of at most `rows` rows down a window of wny rows, as even as they
+// come (a short last strip costs its halo rows and ends the launch alone).
+int even_rows(int wny, int rows) {
+    const int n = std::max(1, (wny + rows - 1) / rows);
+    return std::max(1, (wny + n - 1) / n);
+}
+
+// Default strip height of one map: one-wavefront strips of 128 rows, halved
+// while they leave the chip short of wavefronts (its SIMDs hold about 5000),
+// down to 16 rows: a strip walks 2 (R + 2) rows more than it stores, so
+// short strips only pay where there are too few.  One-wavefront strips pass
+// over rows known to be c^B and wait for no other wavefront: over 39 maps of
+// 40 x 40 to 2000 x 2000 cells, sparse and dense, within 1 % of the best
+// shape of each on average; four wavefronts of 256 rows, halved below 16384
+// wavefronts, had 12 % (2000 x 2000 x 56: 761 against 638 us, 200 x 200 x 8:
+// 22.5 against 15.6 us), and gain on large densely sampled maps (1500 x 1500
+// x 51: 425 against 435 us).
+constexpr int kMapRows = 128;
+int default_rows(const EvalParams& p) {
+    const int outw = strip_outw(p.R, 1), wnx = p.wx1 - p.wx0, wny = p.wy1 - p.wy0;
+    int rows = kMapRows;
+    while (rows > 16) {
+        const long long waves = (long long)p.N * ((wnx + outw - 1) / outw) * ((wny + rows - 1) / rows);
+        if (waves >= (rows > 32 ? 5000 : 2500)) break;
+        rows /= 2;
+    }
+    return rows;
+}
+
+// shape.rows = 0: the tuned shape if one is recorded, else one-wavefront
+// strips of `rows` rows (0: default_rows), evened out.
+StripGeom strip_geom(const EvalParams& p, EvalShape shape = EvalShape{0, 0}, bool two_wave = true, int rows = 0) {
     if (shape.rows <= 0) shape = tuned_shape(p);
     const int wnx = p.wx1 - p.wx0, wny = p.wy1 - p.wy0;
-    // default: the kind that spends fewer lanes on the window's columns
-    // (workgroup strips on a tie)
-    auto lanes = [&](int w) { return (long long)(wnx + strip_outw(p.R, w) - 1) / strip_outw(p.R, w) * 64 * w; };
-    int nw = shape.rows > 0 ? std::max(1, shape.nw) : kDefaultWaves;
-    if (shape.rows <= 0)
-        for (int w : {2, 1})
-            if ((w != 2 || two_wave) && lanes(w) < lanes(nw)) nw = w;
+    int nw = shape.rows > 0 ? std::max(1, shape.nw) : 1;
     if (nw == 2 && !two_wave) nw = kDefaultWaves;
     const int outw = strip_outw(p.R, nw);
     StripGeom g{};
     g.nw = nw;
     g.n_sx = (wnx + outw - 1) / outw;
-    auto work = [&](int r) { return (long long)p.N * g.n_sx * ((wny + r - 1) / r); };
-    if (shape.rows > 0) {
-        g.rows = shape.rows;
-    } else {
-        g.rows = kStripRows;
-        while (g.rows > 32 && work(g.rows) * nw < 16384) g.rows /= 2;
-    }
+    g.rows = shape.rows > 0 ? shape.rows : even_rows(wny, rows > 0 ? rows : default_rows(p));
     g.n_sy = (wny + g.rows - 1) / g.rows;
-    g.n_work = (int)work(g.rows);
+    g.n_work = (int)((long long)p.N * g.n_sx * g.n_sy);
     return g;
 }
 
@@ -1122,9 +1134,17 @@ void autotune_reset() {
     g_batch_build.clear();
 }
 
+// Strips of a batch without tuned shapes: 256 rows, halved while the whole
+// batch has fewer wavefronts than kBatchWaves (down to 16): its maps share
+// the chip, so taller strips than a lone map's of their size pay (512
+// submaps of 50 - 400 cells a side: 7.37 ms with each map's own shape, 6.03 /
+// 5.95 / 6.22 ms with 128 / 256 / 512 rows).
+constexpr int kBatchRows = 256;
+constexpr long long kBatchWaves = 10000;
+
 void batch_strip_signature(const EvalParams& p, EvalShape shape, int out[4]) {
     const StripGeom g = strip_geom(p, shape.rows > 0 ? shape : batch_eval_shape(size_class(p.nx), size_class(p.ny), p.R),
-                                   false);
+                                   false, kBatchRows);
     out[0] = g.nw;
     out[1] = g.n_sx;
     out[2] = g.n_sy;
@@ -1324,9 +1344,26 @@ pct_status plan_jobs(const pct_item* items, int n_items, const pct_robot* robots
             EvalJob jb{};
             pct_status st = make_eval_params(robots[r], items[i].grid, N, &jb.p);
             if (st != PCT_OK) return st;
+            jp->jobs.push_back(jb);
+        }
+    int rows = kBatchRows;
+    for (; rows > 16; rows /= 2) {
+        long long waves = 0;
+        for (const EvalJob& jb : jp->jobs) {
+            const int outw = strip_outw(jb.p.R, 1);
+            waves += (long long)jb.p.N * ((jb.p.nx + outw - 1) / outw) * ((jb.p.ny + rows - 1) / rows);
+        }
+        if (waves >= kBatchWaves) break;
+    }
+    size_t j = 0;
+    for (int r = 0; r < n_robots; ++r)
+        for (int i = 0; i < n_items; ++i) {
+            const int N = items[i].extent.n_slices;
+            if (N <= 0) continue;
+            EvalJob& jb = jp->jobs[j++];
             // blocks of kBlock threads: 1 or 4 wavefronts; the size class's
             // tuned shape if one is recorded
-            jb.sg = strip_geom(jb.p, batch_eval_shape(size_class(jb.p.nx), size_class(jb.p.ny), jb.p.R), false);
+            jb.sg = strip_geom(jb.p, batch_eval_shape(size_class(jb.p.nx), size_class(jb.p.ny), jb.p.R), false, rows);
             jb.in_off = items[i].out_offset;
             jb.out_off = (long long)r * total_cells + items[i].out_offset;
             jb.keep_off = (long long)r * total_slices + items[i].keep_offset;
@@ -1340,7 +1377,6 @@ pct_status plan_jobs(const pct_item* items, int n_items, const pct_robot* robots
             if (jp->R < 0) jp->R = jb.p.R;
             if (jb.p.R != jp->R || !strip_kernel_applies(jb.p)) jp->strip = false;
             if (!weights_follow_pattern(jb.p)) jp->pattern = false;
-            jp->jobs.push_back(jb);
         }
     return PCT_OK;
 }
