@@ -161,23 +161,14 @@ __device__ __forceinline__ bool bin_xyz(float x, float y, float zin, const GridD
     int ix, iy;
     if (!isfinite(z) || !rasterize(x, y, g, ix, iy)) return false;
     z = z + 0.0f;
-    int tx = ix / g.tw, ty = iy / g.th;
-    tile = ty * g.ntx + tx;
-    cell = (unsigned)((iy - ty * g.th) * g.tw + (ix - tx * g.tw));
+    tile = (iy >> g.lth) * g.ntx + (ix >> g.ltw);
+    cell = (unsigned)(((iy & (g.th - 1)) << g.ltw) | (ix & (g.tw - 1)));
     return true;
 }
 
 __device__ __forceinline__ bool bin_point(const float* __restrict__ xyz, int64_t i, const GridDev& g,
                                           int& tile, unsigned& cell, float& z) {
-    float x = xyz[3 * i], y = xyz[3 * i + 1];
-    z = xyz[3 * i + 2];
-    int ix, iy;
-    if (!isfinite(z) || !rasterize(x, y, g, ix, iy)) return false;
-    z = z + 0.0f;
-    int tx = ix / g.tw, ty = iy / g.th;
-    tile = ty * g.ntx + tx;
-    cell = (unsigned)((iy - ty * g.th) * g.tw + (ix - tx * g.tw));
-    return true;
+    return bin_xyz(xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2], g, tile, cell, z);
 }
 
 __global__ __launch_bounds__(kBlock) void k_fill_u32(unsigned* __restrict__ p, int64_t n, unsigned v) {
@@ -267,32 +258,41 @@ constexpr int kMaxSuperG = 8192;        // tiles per super-tile (LDS counters of
 constexpr int kMaxStaged = 1024;        // buckets of a scatter that stages its chunk in LDS
 
 struct BinPlan {
-    int G, S1, CT;     // tiles per super-tile, super-tiles, cells per tile
+    int G, S1;         // tiles per super-tile, super-tiles
+    int lg, lct;       // log2 of G and of the cells per tile
     int nb1;           // level-1 workgroups
     int nb2;           // level-2 workgroups (upper bound; surplus ones exit)
     bool two_level;
     bool staged1, staged2;   // scatters staged in LDS (bucket counts within kMaxStaged)
 };
 
+inline int log2i(int v) {
+    int l = 0;
+    while ((1 << l) < v) ++l;
+    return l;
+}
+
 BinPlan make_bin_plan(int64_t n, const GridDev& g) {
     BinPlan b{};
-    b.CT = g.tw * g.th;
-    int64_t G = (g.ntiles + kSuperTarget - 1) / kSuperTarget;
-    if (G < 1) G = 1;
-    if (G > kMaxSuperG) G = kMaxSuperG;
+    // a power of two, so that tiles and cells come out of keys by shifts
+    int64_t G = 1;
+    while (G * kSuperTarget < g.ntiles && G < kMaxSuperG) G *= 2;
     b.G = (int)G;
+    b.lg = log2i(b.G);
+    b.lct = g.ltw + g.lth;
     b.S1 = (int)((g.ntiles + G - 1) / G);
     b.two_level = b.G > 1;
     b.nb1 = (int)std::max<int64_t>(1, (n + kBinChunk - 1) / kBinChunk);
     b.nb2 = b.two_level ? b.nb1 + b.S1 : 0;
-    b.staged1 = b.S1 <= kMaxStaged;
+    // staged records carry bucket and key in one word
+    b.staged1 = b.S1 <= kMaxStaged && b.lg + b.lct + log2i(b.S1) <= 32;
     b.staged2 = b.G <= kMaxStaged;
     return b;
 }
 
 // Level-1 histogram: column b of cnt1 [S1][nb1].
 __global__ __launch_bounds__(kBinBlock) void k_bin1_hist(const float* __restrict__ xyz, int64_t n, GridDev g,
-                                                         int G, int S1, int nb1, unsigned* __restrict__ cnt1) {
+                                                         int lg, int S1, int nb1, unsigned* __restrict__ cnt1) {
     extern __shared__ unsigned s_cnt[];
     for (int t = threadIdx.x; t < S1; t += kBinBlock) s_cnt[t] = 0;
     __syncthreads();
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(kBinBlock) void k_bin1_hist(const float* __restrict
             int tile;
             unsigned cell;
             float z;
-            if (ok[e] && bin_xyz(px[e], py[e], pz[e], g, tile, cell, z)) atomicAdd(&s_cnt[tile / G], 1u);
+            if (ok[e] && bin_xyz(px[e], py[e], pz[e], g, tile, cell, z)) atomicAdd(&s_cnt[tile >> lg], 1u);
         }
     }
     __syncthreads();
@@ -390,10 +390,10 @@ __global__ __launch_bounds__(1024) void k_bin1_offsets(const unsigned* __restric
 
 // Level-1 scatter.  FINAL (one tile per super-tile): records go straight to
 // the tile arrays as (height, cell-in-tile[, id]); otherwise to the level-1
-// arrays with key = tile-in-super-tile * CT + cell.
+// arrays with key = tile-in-super-tile << lct | cell.
 template <bool IDS, bool FINAL>
 __global__ __launch_bounds__(kBinBlock) void k_bin1_scatter(const float* __restrict__ xyz, int64_t n, GridDev g,
-                                                            int G, int S1, int CT, int nb1,
+                                                            int lg, int S1, int lct, int nb1,
                                                             const unsigned* __restrict__ cnt1,
                                                             const unsigned* __restrict__ off1, float* __restrict__ oz,
                                                             unsigned* __restrict__ okey, int* __restrict__ oid) {
@@ -406,10 +406,10 @@ __global__ __launch_bounds__(kBinBlock) void k_bin1_scatter(const float* __restr
         unsigned cell;
         float z;
         if (!bin_point(xyz, i, g, tile, cell, z)) continue;
-        const int st = tile / G;
+        const int st = tile >> lg;
         const unsigned pos = atomicAdd(&s_cur[st], 1u);
         oz[pos] = z;
-        okey[pos] = FINAL ? cell : (unsigned)(tile - st * G) * (unsigned)CT + cell;
+        okey[pos] = FINAL ? cell : (unsigned)(tile & ((1 << lg) - 1)) << lct | cell;
         if (IDS) oid[pos] = (int)i;
     }
 }
@@ -432,27 +432,20 @@ __device__ __forceinline__ void wave_scan_lds(const unsigned* __restrict__ cnt, 
     if (lane == 0) start[B] = carry;
 }
 
-// The bucket of sorted position p: the last b with start[b] <= p.
-__device__ __forceinline__ int bucket_of(const unsigned* __restrict__ start, int B, unsigned p) {
-    int lo = 0, hi = B - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) / 2;
-        if (start[mid] <= p) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
-// Staged scatter (both levels): the workgroup's records are first sorted by
-// bucket in LDS, then written so that consecutive threads write consecutive
-// addresses of a bucket's run.  LDS: 3 B + 1 counters, then the chunk's
-// heights, keys (and ids).
+// Staged scatter (both levels and batches): the workgroup's records are first
+// sorted by bucket in LDS, then written so that consecutive threads write
+// consecutive addresses of a bucket's run.  A record carries its bucket above
+// the `kb` bits of its key (looking it up by bisection of the bucket starts
+// was nine dependent LDS reads per record; with it, and tiles and cells taken
+// out of keys by shifts, the 20M-point map's scatters take 93 + 72 us instead
+// of 117 + 84).  LDS: 3 B + 1 counters, then the
+// chunk's heights, keys (and ids).
 inline size_t staged_lds_bytes(int B, bool ids) {
     return sizeof(unsigned) * (3 * (size_t)B + 1) + (size_t)kBinChunk * (ids ? 12 : 8);
 }
 
 template <bool IDS>
-__device__ __forceinline__ void staged_write(unsigned* s_mem, int B, const float (&z)[kBinPPT],
+__device__ __forceinline__ void staged_write(unsigned* s_mem, int B, int kb, const float (&z)[kBinPPT],
                                              const unsigned (&key)[kBinPPT], const int (&id)[kBinPPT],
                                              const int (&bk)[kBinPPT], const unsigned (&rank)[kBinPPT],
                                              float* __restrict__ oz, unsigned* __restrict__ okey,
@@ -470,23 +463,26 @@ __device__ __forceinline__ void staged_write(unsigned* s_mem, int B, const float
         if (bk[j] < 0) continue;
         const unsigned p = s_start[bk[j]] + rank[j];
         s_z[p] = z[j];
-        s_key[p] = key[j];
+        s_key[p] = (unsigned)bk[j] << kb | key[j];
         if (IDS) s_id[p] = id[j];
     }
     __syncthreads();
-    const unsigned total = s_start[B];
+    // position p of bucket b goes to p + (global start - local start)
+    for (int t = threadIdx.x; t < B; t += kBinBlock) s_gb[t] -= s_start[t];
+    __syncthreads();
+    const unsigned total = s_start[B], mask = (1u << kb) - 1u;
     for (unsigned p = threadIdx.x; p < total; p += kBinBlock) {
-        const int b = bucket_of(s_start, B, p);
-        const unsigned pos = s_gb[b] + (p - s_start[b]);
+        const unsigned k = s_key[p];
+        const unsigned pos = s_gb[k >> kb] + p;
         oz[pos] = s_z[p];
-        okey[pos] = s_key[p];
+        okey[pos] = k & mask;
         if (IDS) oid[pos] = s_id[p];
     }
 }
 
 template <bool IDS, bool FINAL>
 __global__ __launch_bounds__(kBinBlock) void k_bin1_scatter_staged(const float* __restrict__ xyz, int64_t n, GridDev g,
-                                                                   int G, int S1, int CT, int nb1,
+                                                                   int lg, int S1, int lct, int nb1,
                                                                    const unsigned* __restrict__ cnt1,
                                                                    const unsigned* __restrict__ off1,
                                                                    float* __restrict__ oz, unsigned* __restrict__ okey,
@@ -520,15 +516,15 @@ __global__ __launch_bounds__(kBinBlock) void k_bin1_scatter_staged(const float* 
             bk[j] = -1;
             id[j] = (int)(4 * q + e);
             if (ok[e] && bin_xyz(px[e], py[e], pz[e], g, tile, cell, z[j])) {
-                const int st = tile / G;
+                const int st = tile >> lg;
                 bk[j] = st;
-                key[j] = FINAL ? cell : (unsigned)(tile - st * G) * (unsigned)CT + cell;
+                key[j] = FINAL ? cell : (unsigned)(tile & ((1 << lg) - 1)) << lct | cell;
                 rank[j] = atomicAdd(&s_cnt[st], 1u);
             }
         }
     }
     __syncthreads();
-    staged_write<IDS>(s_mem, S1, z, key, id, bk, rank, oz, okey, oid);
+    staged_write<IDS>(s_mem, S1, FINAL ? lct : lg + lct, z, key, id, bk, rank, oz, okey, oid);
 }
 
 // Level-2 workgroup q covers records [off1[s] + j kBinChunk, ...) of
@@ -546,8 +542,9 @@ __device__ __forceinline__ int bin2_super(const unsigned* __restrict__ cbase, in
 // Level-2 histogram: column q of cnt2 [G][nb2].
 __global__ __launch_bounds__(kBinBlock) void k_bin2_hist(const unsigned* __restrict__ key1,
                                                          const unsigned* __restrict__ off1,
-                                                         const unsigned* __restrict__ cbase, int S1, int G, int CT,
+                                                         const unsigned* __restrict__ cbase, int S1, int lg, int lct,
                                                          int nb2, unsigned* __restrict__ cnt2) {
+    const int G = 1 << lg;
     extern __shared__ unsigned s_cnt[];
     const unsigned q = blockIdx.x;
     if (q >= cbase[S1]) return;   // surplus workgroup (uniform)
@@ -556,7 +553,7 @@ __global__ __launch_bounds__(kBinBlock) void k_bin2_hist(const unsigned* __restr
     const unsigned r1 = min(off1[st + 1], r0 + (unsigned)kBinChunk);
     for (int t = threadIdx.x; t < G; t += kBinBlock) s_cnt[t] = 0;
     __syncthreads();
-    for (unsigned r = r0 + threadIdx.x; r < r1; r += kBinBlock) atomicAdd(&s_cnt[key1[r] / (unsigned)CT], 1u);
+    for (unsigned r = r0 + threadIdx.x; r < r1; r += kBinBlock) atomicAdd(&s_cnt[key1[r] >> lct], 1u);
     __syncthreads();
     for (int t = threadIdx.x; t < G; t += kBinBlock) cnt2[(int64_t)t * nb2 + q] = s_cnt[t];
 }
@@ -565,10 +562,10 @@ __global__ __launch_bounds__(kBinBlock) void k_bin2_hist(const unsigned* __restr
 // columns cbase[st] .. cbase[st+1] of row l of cnt2); the total goes to
 // tot[t].
 __global__ __launch_bounds__(kBlock) void k_bin2_rows(unsigned* __restrict__ cnt2, const unsigned* __restrict__ cbase,
-                                                      int G, int ntiles, int nb2, unsigned* __restrict__ tot) {
+                                                      int lg, int ntiles, int nb2, unsigned* __restrict__ tot) {
     const int t = blockIdx.x * (kBlock / 64) + (int)(threadIdx.x / 64);
     if (t >= ntiles) return;
-    const int st = t / G, l = t - st * G;
+    const int st = t >> lg, l = t & ((1 << lg) - 1);
     const unsigned c0 = cbase[st], c1 = cbase[st + 1];
     const unsigned total = wave_scan_row(cnt2 + (int64_t)l * nb2 + c0, (int)(c1 - c0));
     if ((threadIdx.x & 63) == 0) tot[t] = total;
@@ -580,25 +577,26 @@ __global__ __launch_bounds__(kBinBlock) void k_bin2_scatter(const float* __restr
                                                             const unsigned* __restrict__ key1,
                                                             const int* __restrict__ id1,
                                                             const unsigned* __restrict__ off1,
-                                                            const unsigned* __restrict__ cbase, int S1, int G, int CT,
+                                                            const unsigned* __restrict__ cbase, int S1, int lg, int lct,
                                                             int nb2, const unsigned* __restrict__ cnt2,
                                                             const unsigned* __restrict__ off, float* __restrict__ rz,
                                                             unsigned* __restrict__ rmeta, int* __restrict__ rid) {
+    const int G = 1 << lg;
     extern __shared__ unsigned s_cur[];
     const unsigned q = blockIdx.x;
     if (q >= cbase[S1]) return;
     const int st = bin2_super(cbase, S1, q);
     const unsigned r0 = off1[st] + (q - cbase[st]) * (unsigned)kBinChunk;
     const unsigned r1 = min(off1[st + 1], r0 + (unsigned)kBinChunk);
-    const int tbase = st * G;
+    const int tbase = st << lg;
     for (int t = threadIdx.x; t < G; t += kBinBlock) s_cur[t] = off[tbase + t] + cnt2[(int64_t)t * nb2 + q];
     __syncthreads();
     for (unsigned r = r0 + threadIdx.x; r < r1; r += kBinBlock) {
         const unsigned key = key1[r];
-        const unsigned l = key / (unsigned)CT;
+        const unsigned l = key >> lct;
         const unsigned pos = atomicAdd(&s_cur[l], 1u);
         rz[pos] = z1[r];
-        rmeta[pos] = key - l * (unsigned)CT;
+        rmeta[pos] = key & ((1u << lct) - 1u);
         if (IDS) rid[pos] = id1[r];
     }
 }
@@ -608,18 +606,19 @@ __global__ __launch_bounds__(kBinBlock) void k_bin2_scatter_staged(const float* 
                                                                    const unsigned* __restrict__ key1,
                                                                    const int* __restrict__ id1,
                                                                    const unsigned* __restrict__ off1,
-                                                                   const unsigned* __restrict__ cbase, int S1, int G,
-                                                                   int CT, int nb2, const unsigned* __restrict__ cnt2,
+                                                                   const unsigned* __restrict__ cbase, int S1, int lg,
+                                                                   int lct, int nb2, const unsigned* __restrict__ cnt2,
                                                                    const unsigned* __restrict__ off,
                                                                    float* __restrict__ rz, unsigned* __restrict__ rmeta,
                                                                    int* __restrict__ rid) {
+    const int G = 1 << lg;
     extern __shared__ unsigned s_mem[];
     const unsigned q = blockIdx.x;
     if (q >= cbase[S1]) return;   // surplus workgroup (uniform)
     const int st = bin2_super(cbase, S1, q);
     const unsigned r0 = off1[st] + (q - cbase[st]) * (unsigned)kBinChunk;
     const unsigned r1 = min(off1[st + 1], r0 + (unsigned)kBinChunk);
-    const int tbase = st * G;
+    const int tbase = st << lg;
     unsigned* s_cnt = s_mem;
     unsigned* s_gb = s_cnt + 2 * G + 1;
     for (int t = threadIdx.x; t < G; t += kBinBlock) {
@@ -637,16 +636,16 @@ __global__ __launch_bounds__(kBinBlock) void k_bin2_scatter_staged(const float* 
         id[j] = 0;
         if (r < r1) {
             const unsigned k = key1[r];
-            const unsigned l = k / (unsigned)CT;
+            const unsigned l = k >> lct;
             z[j] = z1[r];
-            key[j] = k - l * (unsigned)CT;
+            key[j] = k & ((1u << lct) - 1u);
             if (IDS) id[j] = id1[r];
             bk[j] = (int)l;
             rank[j] = atomicAdd(&s_cnt[l], 1u);
         }
     }
     __syncthreads();
-    staged_write<IDS>(s_mem, G, z, key, id, bk, rank, rz, rmeta, rid);
+    staged_write<IDS>(s_mem, G, lct, z, key, id, bk, rank, rz, rmeta, rid);
 }
 
 // ------------------------------------------------------------------ reduce
@@ -1109,67 +1108,100 @@ __global__ __launch_bounds__(kBlock) void k_bextent_final(const BuildItemDev* __
 
 // Per-chunk tile counts of the chunk's item: LDS histogram, one global
 // atomic per touched tile.
-__global__ __launch_bounds__(kBlock) void k_bcount(const float* __restrict__ xyz, const BuildItemDev* __restrict__ items,
-                                                   int n_items, unsigned* __restrict__ gcount) {
+__global__ __launch_bounds__(kBinBlock) void k_bcount(const float* __restrict__ xyz,
+                                                      const BuildItemDev* __restrict__ items, int n_items,
+                                                      unsigned* __restrict__ gcount) {
     extern __shared__ unsigned s_cnt[];
     const int c = blockIdx.x;
     const int it = find_base(items, n_items, c, 0);
     const BuildItemDev& d = items[it];
     const bool lds = d.g.ntiles <= kMaxLdsTiles;
     if (lds)
-        for (int t = threadIdx.x; t < d.g.ntiles; t += kBlock) s_cnt[t] = 0;
+        for (int t = threadIdx.x; t < d.g.ntiles; t += kBinBlock) s_cnt[t] = 0;
     __syncthreads();
-    const long long b0 = (long long)(c - d.chunk_base) * kBatchChunk, b1 = min(d.n, b0 + kBatchChunk);
-    for (long long i = b0 + threadIdx.x; i < b1; i += kBlock) {
-        int tile;
-        unsigned cell;
-        float z;
-        if (!bin_point(xyz, d.xyz_off + i, d.g, tile, cell, z)) continue;
-        if (lds) atomicAdd(&s_cnt[tile], 1u);
-        else atomicAdd(&gcount[d.tile_base + tile], 1u);
+    const float* p = xyz + 3 * d.xyz_off;
+    const bool vec = aligned16(p);
+    const int64_t q0 = (int64_t)(c - d.chunk_base) * (kBatchChunk / 4), q1 = min((int64_t)(d.n + 3) / 4, q0 + kBatchChunk / 4);
+    for (int64_t q = q0 + threadIdx.x; q < q1; q += kBinBlock) {
+        float px[4], py[4], pz[4];
+        bool ok[4];
+        load_points4(p, d.n, q, vec, px, py, pz, ok);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            int tile;
+            unsigned cell;
+            float z;
+            if (!ok[e] || !bin_xyz(px[e], py[e], pz[e], d.g, tile, cell, z)) continue;
+            if (lds) atomicAdd(&s_cnt[tile], 1u);
+            else atomicAdd(&gcount[d.tile_base + tile], 1u);
+        }
     }
     __syncthreads();
     if (lds)
-        for (int t = threadIdx.x; t < d.g.ntiles; t += kBlock)
+        for (int t = threadIdx.x; t < d.g.ntiles; t += kBinBlock)
             if (s_cnt[t]) atomicAdd(&gcount[d.tile_base + t], s_cnt[t]);
 }
 
+// Scatter of a chunk into its item's tiles: one global atomic per touched
+// tile reserves the chunk's run, then a staged scatter (items of at most
+// kMaxStaged tiles), else each record goes out by itself.  108 M points of
+// 512 submaps: 3.46 ms with records written in the order of the points, 0.70
+// ms staged.
 template <bool IDS>
-__global__ __launch_bounds__(kBlock) void k_bscatter(const float* __restrict__ xyz, const BuildItemDev* __restrict__ items,
-                                                     int n_items, unsigned* __restrict__ cursor, float* __restrict__ rz,
-                                                     unsigned* __restrict__ rmeta, int* __restrict__ rid) {
+__global__ __launch_bounds__(kBinBlock) void k_bscatter(const float* __restrict__ xyz,
+                                                        const BuildItemDev* __restrict__ items, int n_items,
+                                                        unsigned* __restrict__ cursor, float* __restrict__ rz,
+                                                        unsigned* __restrict__ rmeta, int* __restrict__ rid) {
+    static_assert(kBatchChunk == kBinChunk, "a staged chunk");
     extern __shared__ unsigned s_mem[];
     const int c = blockIdx.x;
     const int it = find_base(items, n_items, c, 0);
     const BuildItemDev& d = items[it];
-    const bool lds = d.g.ntiles <= kMaxLdsTiles;
-    unsigned* s_cnt = s_mem;
-    unsigned* s_base = s_mem + (lds ? d.g.ntiles : 0);
-    if (lds)
-        for (int t = threadIdx.x; t < d.g.ntiles; t += kBlock) s_cnt[t] = 0;
-    __syncthreads();
-    const long long b0 = (long long)(c - d.chunk_base) * kBatchChunk, b1 = min(d.n, b0 + kBatchChunk);
-    if (lds) {
-        for (long long i = b0 + threadIdx.x; i < b1; i += kBlock) {
-            int tile;
-            unsigned cell;
-            float z;
-            if (bin_point(xyz, d.xyz_off + i, d.g, tile, cell, z)) atomicAdd(&s_cnt[tile], 1u);
+    const int B = d.g.ntiles;
+    const float* p = xyz + 3 * d.xyz_off;
+    const bool vec = aligned16(p);
+    const int64_t q0 = (int64_t)(c - d.chunk_base) * (kBatchChunk / 4);
+    if (B <= kMaxStaged) {
+        unsigned* s_cnt = s_mem;
+        unsigned* s_gb = s_cnt + 2 * B + 1;
+        for (int t = threadIdx.x; t < B; t += kBinBlock) s_cnt[t] = 0;
+        __syncthreads();
+        float z[kBinPPT];
+        unsigned key[kBinPPT], rank[kBinPPT];
+        int id[kBinPPT], bk[kBinPPT];
+#pragma unroll
+        for (int m = 0; m < kBinPPT / 4; ++m) {
+            const int64_t q = q0 + (int64_t)m * kBinBlock + threadIdx.x;
+            float px[4], py[4], pz[4];
+            bool ok[4];
+            load_points4(p, d.n, q, vec, px, py, pz, ok);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int j = 4 * m + e;
+                int tile;
+                bk[j] = -1;
+                id[j] = (int)(d.xyz_off + 4 * q + e);
+                if (ok[e] && bin_xyz(px[e], py[e], pz[e], d.g, tile, key[j], z[j])) {
+                    bk[j] = tile;
+                    rank[j] = atomicAdd(&s_cnt[tile], 1u);
+                }
+            }
         }
         __syncthreads();
-        for (int t = threadIdx.x; t < d.g.ntiles; t += kBlock) {
+        for (int t = threadIdx.x; t < B; t += kBinBlock) {
             const unsigned k = s_cnt[t];
-            if (k) s_base[t] = atomicAdd(&cursor[d.tile_base + t], k);
-            s_cnt[t] = 0;
+            s_gb[t] = k ? atomicAdd(&cursor[d.tile_base + t], k) : 0u;
         }
         __syncthreads();
+        staged_write<IDS>(s_mem, B, d.g.ltw + d.g.lth, z, key, id, bk, rank, rz, rmeta, rid);
+        return;
     }
-    for (long long i = b0 + threadIdx.x; i < b1; i += kBlock) {
+    for (int64_t i = 4 * q0 + threadIdx.x; i < min((int64_t)d.n, 4 * q0 + kBatchChunk); i += kBinBlock) {
         int tile;
         unsigned cell;
         float z;
-        if (!bin_point(xyz, d.xyz_off + i, d.g, tile, cell, z)) continue;
-        const unsigned pos = lds ? s_base[tile] + atomicAdd(&s_cnt[tile], 1u) : atomicAdd(&cursor[d.tile_base + tile], 1u);
+        if (!bin_point(p, i, d.g, tile, cell, z)) continue;
+        const unsigned pos = atomicAdd(&cursor[d.tile_base + tile], 1u);
         rz[pos] = z;
         rmeta[pos] = cell;
         if (IDS) rid[pos] = (int)(d.xyz_off + i);
@@ -1308,7 +1340,7 @@ pct_status launch_build(const float* xyz, int64_t n, const GridDev& g, float zmi
     } else {
         // level 1: points -> super-tiles (the tiles themselves when G = 1)
         const size_t l1 = sizeof(unsigned) * (size_t)b.S1;
-        hipLaunchKernelGGL(k_bin1_hist, dim3(b.nb1), dim3(kBinBlock), l1, s, xyz, n, g, b.G, b.S1, b.nb1, w.cnt1);
+        hipLaunchKernelGGL(k_bin1_hist, dim3(b.nb1), dim3(kBinBlock), l1, s, xyz, n, g, b.lg, b.S1, b.nb1, w.cnt1);
         PCT_LAUNCH_CHECK();
         hipLaunchKernelGGL(k_bin1_rows, dim3(b.S1), dim3(1024), 0, s, w.cnt1, b.nb1, w.tot1);
         PCT_LAUNCH_CHECK();
@@ -1318,16 +1350,16 @@ pct_status launch_build(const float* xyz, int64_t n, const GridDev& g, float zmi
             const size_t ls = staged_lds_bytes(b.S1, ids);
             if (b.staged1 && ids)
                 hipLaunchKernelGGL((k_bin1_scatter_staged<true, true>), dim3(b.nb1), dim3(kBinBlock), ls, s, xyz, n, g,
-                                   b.G, b.S1, b.CT, b.nb1, w.cnt1, w.off, w.rz, w.rmeta, w.rid);
+                                   b.lg, b.S1, b.lct, b.nb1, w.cnt1, w.off, w.rz, w.rmeta, w.rid);
             else if (b.staged1)
                 hipLaunchKernelGGL((k_bin1_scatter_staged<false, true>), dim3(b.nb1), dim3(kBinBlock), ls, s, xyz, n, g,
-                                   b.G, b.S1, b.CT, b.nb1, w.cnt1, w.off, w.rz, w.rmeta, w.rid);
+                                   b.lg, b.S1, b.lct, b.nb1, w.cnt1, w.off, w.rz, w.rmeta, w.rid);
             else if (ids)
-                hipLaunchKernelGGL((k_bin1_scatter<true, true>), dim3(b.nb1), dim3(kBinBlock), l1, s, xyz, n, g, b.G,
-                                   b.S1, b.CT, b.nb1, w.cnt1, w.off, w.rz, w.rmeta, w.rid);
+                hipLaunchKernelGGL((k_bin1_scatter<true, true>), dim3(b.nb1), dim3(kBinBlock), l1, s, xyz, n, g, b.lg,
+                                   b.S1, b.lct, b.nb1, w.cnt1, w.off, w.rz, w.rmeta, w.rid);
             else
-                hipLaunchKernelGGL((k_bin1_scatter<false, true>), dim3(b.nb1), dim3(kBinBlock), l1, s, xyz, n, g, b.G,
-                                   b.S1, b.CT, b.nb1, w.cnt1, w.off, w.rz, w.rmeta, w.rid);
+                hipLaunchKernelGGL((k_bin1_scatter<false, true>), dim3(b.nb1), dim3(kBinBlock), l1, s, xyz, n, g, b.lg,
+                                   b.S1, b.lct, b.nb1, w.cnt1, w.off, w.rz, w.rmeta, w.rid);
             PCT_LAUNCH_CHECK();
         } else {
             hipLaunchKernelGGL(k_bin1_offsets, dim3(1), dim3(1024), 0, s, w.tot1, b.S1, w.off1, w.cbase);
@@ -1335,23 +1367,23 @@ pct_status launch_build(const float* xyz, int64_t n, const GridDev& g, float zmi
             const size_t ls = staged_lds_bytes(b.S1, ids);
             if (b.staged1 && ids)
                 hipLaunchKernelGGL((k_bin1_scatter_staged<true, false>), dim3(b.nb1), dim3(kBinBlock), ls, s, xyz, n,
-                                   g, b.G, b.S1, b.CT, b.nb1, w.cnt1, w.off1, w.z1, w.key1, w.id1);
+                                   g, b.lg, b.S1, b.lct, b.nb1, w.cnt1, w.off1, w.z1, w.key1, w.id1);
             else if (b.staged1)
                 hipLaunchKernelGGL((k_bin1_scatter_staged<false, false>), dim3(b.nb1), dim3(kBinBlock), ls, s, xyz, n,
-                                   g, b.G, b.S1, b.CT, b.nb1, w.cnt1, w.off1, w.z1, w.key1, w.id1);
+                                   g, b.lg, b.S1, b.lct, b.nb1, w.cnt1, w.off1, w.z1, w.key1, w.id1);
             else if (ids)
-                hipLaunchKernelGGL((k_bin1_scatter<true, false>), dim3(b.nb1), dim3(kBinBlock), l1, s, xyz, n, g, b.G,
-                                   b.S1, b.CT, b.nb1, w.cnt1, w.off1, w.z1, w.key1, w.id1);
+                hipLaunchKernelGGL((k_bin1_scatter<true, false>), dim3(b.nb1), dim3(kBinBlock), l1, s, xyz, n, g, b.lg,
+                                   b.S1, b.lct, b.nb1, w.cnt1, w.off1, w.z1, w.key1, w.id1);
             else
-                hipLaunchKernelGGL((k_bin1_scatter<false, false>), dim3(b.nb1), dim3(kBinBlock), l1, s, xyz, n, g, b.G,
-                                   b.S1, b.CT, b.nb1, w.cnt1, w.off1, w.z1, w.key1, w.id1);
+                hipLaunchKernelGGL((k_bin1_scatter<false, false>), dim3(b.nb1), dim3(kBinBlock), l1, s, xyz, n, g, b.lg,
+                                   b.S1, b.lct, b.nb1, w.cnt1, w.off1, w.z1, w.key1, w.id1);
             PCT_LAUNCH_CHECK();
             // level 2: each super-tile's records -> its tiles
             const size_t l2 = sizeof(unsigned) * (size_t)b.G;
-            hipLaunchKernelGGL(k_bin2_hist, dim3(b.nb2), dim3(kBinBlock), l2, s, w.key1, w.off1, w.cbase, b.S1, b.G,
-                               b.CT, b.nb2, w.cnt2);
+            hipLaunchKernelGGL(k_bin2_hist, dim3(b.nb2), dim3(kBinBlock), l2, s, w.key1, w.off1, w.cbase, b.S1, b.lg,
+                               b.lct, b.nb2, w.cnt2);
             PCT_LAUNCH_CHECK();
-            hipLaunchKernelGGL(k_bin2_rows, dim3((g.ntiles + 3) / 4), dim3(kBlock), 0, s, w.cnt2, w.cbase, b.G,
+            hipLaunchKernelGGL(k_bin2_rows, dim3((g.ntiles + 3) / 4), dim3(kBlock), 0, s, w.cnt2, w.cbase, b.lg,
                                g.ntiles, b.nb2, w.count);
             PCT_LAUNCH_CHECK();
             hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, s, w.count, g.ntiles, w.off, w.cursor);
@@ -1359,16 +1391,16 @@ pct_status launch_build(const float* xyz, int64_t n, const GridDev& g, float zmi
             const size_t ls2 = staged_lds_bytes(b.G, ids);
             if (b.staged2 && ids)
                 hipLaunchKernelGGL(k_bin2_scatter_staged<true>, dim3(b.nb2), dim3(kBinBlock), ls2, s, w.z1, w.key1,
-                                   w.id1, w.off1, w.cbase, b.S1, b.G, b.CT, b.nb2, w.cnt2, w.off, w.rz, w.rmeta, w.rid);
+                                   w.id1, w.off1, w.cbase, b.S1, b.lg, b.lct, b.nb2, w.cnt2, w.off, w.rz, w.rmeta, w.rid);
             else if (b.staged2)
                 hipLaunchKernelGGL(k_bin2_scatter_staged<false>, dim3(b.nb2), dim3(kBinBlock), ls2, s, w.z1, w.key1,
-                                   w.id1, w.off1, w.cbase, b.S1, b.G, b.CT, b.nb2, w.cnt2, w.off, w.rz, w.rmeta, w.rid);
+                                   w.id1, w.off1, w.cbase, b.S1, b.lg, b.lct, b.nb2, w.cnt2, w.off, w.rz, w.rmeta, w.rid);
             else if (ids)
                 hipLaunchKernelGGL(k_bin2_scatter<true>, dim3(b.nb2), dim3(kBinBlock), l2, s, w.z1, w.key1, w.id1,
-                                   w.off1, w.cbase, b.S1, b.G, b.CT, b.nb2, w.cnt2, w.off, w.rz, w.rmeta, w.rid);
+                                   w.off1, w.cbase, b.S1, b.lg, b.lct, b.nb2, w.cnt2, w.off, w.rz, w.rmeta, w.rid);
             else
                 hipLaunchKernelGGL(k_bin2_scatter<false>, dim3(b.nb2), dim3(kBinBlock), l2, s, w.z1, w.key1, w.id1,
-                                   w.off1, w.cbase, b.S1, b.G, b.CT, b.nb2, w.cnt2, w.off, w.rz, w.rmeta, w.rid);
+                                   w.off1, w.cbase, b.S1, b.lg, b.lct, b.nb2, w.cnt2, w.off, w.rz, w.rmeta, w.rid);
             PCT_LAUNCH_CHECK();
         }
     }
@@ -1475,12 +1507,16 @@ GridDev make_grid_dev(const pct_grid& gr) {
     while (g.th < 8 && (int64_t)g.ntx * ((gr.ny + g.th - 1) / g.th) > kMaxLdsTiles) g.th *= 2;
     g.nty = (gr.ny + g.th - 1) / g.th;
     g.ntiles = g.ntx * g.nty;
+    g.ltw = log2i(g.tw);
+    g.lth = log2i(g.th);
     return g;
 }
 
 GridDev tile_shape(GridDev g, int tw, int th) {
     g.tw = tw;
     g.th = th;
+    g.ltw = log2i(tw);
+    g.lth = log2i(th);
     g.ntx = (g.nx + tw - 1) / tw;
     g.nty = (g.ny + th - 1) / th;
     g.ntiles = g.ntx * g.nty;
@@ -1547,9 +1583,10 @@ pct_status launch_build_batched(const float* xyz, const BuildItemDev* h_items, i
         PCT_HIP(hipMemcpyAsync(w.items, h_items, sizeof(BuildItemDev) * n_items, hipMemcpyHostToDevice, s));
         PCT_HIP(hipStreamSynchronize(s));
     }
-    int max_tiles_lds = 0, cap = 0;
+    int max_tiles_lds = 0, max_staged = 0, cap = 0;
     for (int i = 0; i < n_items; ++i) {
         if (h_items[i].g.ntiles <= kMaxLdsTiles) max_tiles_lds = std::max(max_tiles_lds, h_items[i].g.ntiles);
+        if (h_items[i].g.ntiles <= kMaxStaged) max_staged = std::max(max_staged, h_items[i].g.ntiles);
         cap = std::max(cap, reduce_cap(h_items[i].n, h_items[i].g));
     }
     // the largest tile (tw x th cells) and plane count of any item size the bit matrix
@@ -1561,19 +1598,19 @@ pct_status launch_build_batched(const float* xyz, const BuildItemDev* h_items, i
                        (int64_t)w.total_tiles + 1, 0u);
     PCT_LAUNCH_CHECK();
     if (w.total_chunks > 0) {
-        hipLaunchKernelGGL(k_bcount, dim3(w.total_chunks), dim3(kBlock), sizeof(unsigned) * max_tiles_lds, s, xyz, w.items,
+        hipLaunchKernelGGL(k_bcount, dim3(w.total_chunks), dim3(kBinBlock), sizeof(unsigned) * max_tiles_lds, s, xyz, w.items,
                            n_items, w.count);
         PCT_LAUNCH_CHECK();
     }
     hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, s, w.count, w.total_tiles, w.off, w.cursor);
     PCT_LAUNCH_CHECK();
     if (w.total_chunks > 0) {
-        const size_t lb = 2 * sizeof(unsigned) * max_tiles_lds;
+        const size_t lb = staged_lds_bytes(max_staged, ids);
         if (ids)
-            hipLaunchKernelGGL(k_bscatter<true>, dim3(w.total_chunks), dim3(kBlock), lb, s, xyz, w.items, n_items,
+            hipLaunchKernelGGL(k_bscatter<true>, dim3(w.total_chunks), dim3(kBinBlock), lb, s, xyz, w.items, n_items,
                                w.cursor, w.rz, w.rmeta, w.rid);
         else
-            hipLaunchKernelGGL(k_bscatter<false>, dim3(w.total_chunks), dim3(kBlock), lb, s, xyz, w.items, n_items,
+            hipLaunchKernelGGL(k_bscatter<false>, dim3(w.total_chunks), dim3(kBinBlock), lb, s, xyz, w.items, n_items,
                                w.cursor, w.rz, w.rmeta, w.rid);
         PCT_LAUNCH_CHECK();
     }

@@ -47,6 +47,7 @@ struct GridDev {
     int th, ntx, nty;   // construction tiling
     int ntiles;
     int tw;
+    int ltw, lth;       // log2 of tw and th (both powers of two)
 };
 
 GridDev make_grid_dev(const pct_grid& g);
@@ -114,7 +115,7 @@ struct BuildItemDev {
     int echunk_base;        // first global extent chunk
 };
 
-constexpr int kBatchChunk = 8192;     // points per workgroup in batched binning
+constexpr int kBatchChunk = 4096;     // points per workgroup in batched binning
 constexpr int kBatchEChunk = 65536;   // points per workgroup in batched extents
 
 // ---------------------------------------------------------------- eval

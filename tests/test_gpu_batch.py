@@ -82,6 +82,37 @@ def test_batched_equals_single(P, oracle_lib):
             np.testing.assert_array_equal(bits(g1), tm["ground"].view(np.uint32))
 
 
+
+@pytest.mark.parametrize("ids", [True, False])
+def test_batched_scatter_edges(P, oracle_lib, ids):
+    """Items of one tile, of exactly and one more than the most tiles whose
+    scatter is staged in LDS (1024), chunks of 4095 to 4097 points, and every
+    alignment of an item's points, against the oracle."""
+    import torch
+    rng = np.random.default_rng(8)
+    shapes = [(64, 8, 4095), (300, 1024, 4097), (300, 1026, 9001), (129, 3, 1), (1, 1, 4096), (256, 4, 2), (50, 60, 4099)]
+    specs, pts, off = [], [], 0
+    for nx, ny, n in shapes:
+        p = np.stack([rng.uniform(-0.05, 0.1 * nx + 0.05, n), rng.uniform(-0.05, 0.1 * ny + 0.05, n),
+                      rng.uniform(0.0, 2.5, n)], 1).astype(np.float32)
+        specs.append(dict(xyz_offset=off, n_points=n, grid=dict(x0=0.0, y0=0.0, res=0.1, nx=nx, ny=ny, slice_dz=0.3)))
+        pts.append(p)
+        off += n
+    b = P.Batch(torch.from_numpy(np.concatenate(pts)).cuda(), specs, n_robots=1, with_ids=ids)
+    P.pct_tomogram_extent_batched(b)
+    G, Cc, aG, aC = P.pct_build_tomogram_batched(b, with_ids=ids)
+    for i, (p, sp) in enumerate(zip(pts, specs)):
+        tm = oracle_lib.tomogram(p, sp["grid"])
+        assert b.items[i].extent.n_slices == len(tm["h"])
+        if not len(tm["h"]):
+            continue
+        np.testing.assert_array_equal(bits(b.item_view(G, i)), tm["ground"].view(np.uint32))
+        np.testing.assert_array_equal(bits(b.item_view(Cc, i)), tm["ceil"].view(np.uint32))
+        if ids:
+            for got, want in ((aG, tm["arg_ground"]), (aC, tm["arg_ceil"])):
+                np.testing.assert_array_equal(bits(b.item_view(got, i)), np.where(want >= 0, want + sp["xyz_offset"], -1))
+
+
 def test_batched_many_robots(P):
     """One map, several robot profiles in one launch = one call per robot."""
     import torch
