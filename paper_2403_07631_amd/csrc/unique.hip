@@ -4,9 +4,9 @@
 // order.
 //
 // Two passes over the kept slices: the first counts the unique cells of
-// every 1024-cell block, an exclusive scan turns the counts into output
-// offsets, the second recomputes the flags and writes each block's unique
-// cells at its offset in raster order (ranks from wavefront ballots).
+// every 1024-cell block and keeps the flags, an exclusive scan turns the
+// counts into output offsets, the second reads the flags and writes each
+// block's unique cells at its offset in raster order.
 #include <vector>
 
 #include "pct_internal.h"
@@ -67,13 +67,15 @@ template <bool VEC>
 __global__ __launch_bounds__(kUBlock) void k_uniq_count(const float* __restrict__ ground,
                                                         const float* __restrict__ cost, long long plane, float cB,
                                                         const UniqSlice* __restrict__ slices, int nb,
-                                                        unsigned long long* __restrict__ counts) {
+                                                        unsigned long long* __restrict__ counts,
+                                                        uint8_t* __restrict__ flags) {
     __shared__ unsigned s_wave[kUBlock / 64];
     const int j = blockIdx.y, b = blockIdx.x;
     const long long c0 = (long long)b * kUSpan + (long long)threadIdx.x * kUCells;
     const long long left = plane - c0;
     const int nact = left <= 0 ? 0 : (left < kUCells ? (int)left : kUCells);
     const unsigned f = nact > 0 ? uniq_flags<VEC>(ground, cost, plane, cB, slices[j], c0, nact) : 0u;
+    flags[((long long)j * nb + b) * kUBlock + threadIdx.x] = (uint8_t)f;
     int n = __popc(f);
     for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
     if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x / 64] = (unsigned)n;
@@ -88,12 +90,16 @@ __global__ __launch_bounds__(kUBlock) void k_uniq_count(const float* __restrict_
 // Exclusive scan of n counts in place (one workgroup of 16 wavefronts),
 // 4096 counts at a time: four consecutive counts per thread, an inclusive
 // scan of the thread sums within each wavefront by shuffles, then the
-// wavefront totals across the workgroup.  total[0] receives the sum.
-__global__ __launch_bounds__(1024) void k_uniq_scan(unsigned long long* __restrict__ v, long long n,
-                                                    unsigned long long* __restrict__ total) {
+// wavefront totals across the workgroup.  first[j] receives the offset of
+// count j nb (a slice's first), first[n / nb] the sum.
+__global__ __launch_bounds__(1024) void k_uniq_scan(unsigned long long* __restrict__ v, int nb, int L,
+                                                    unsigned long long* __restrict__ first) {
+    const long long n = (long long)nb * L;
     __shared__ unsigned long long s_wave[16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     unsigned long long carry = 0;
+    int j = 4 * (int)threadIdx.x / nb, r = 4 * (int)threadIdx.x % nb;   // i0 = j nb + r
+    const int dj = 4096 / nb, dr = 4096 % nb;
     for (long long base = 0; base < n; base += 4096) {
         const long long i0 = base + 4 * (long long)threadIdx.x;
         unsigned long long x[4], sum = 0;
@@ -116,33 +122,48 @@ __global__ __launch_bounds__(1024) void k_uniq_scan(unsigned long long* __restri
             chunk += t;
         }
         unsigned long long run = before + incl - sum;
+        int jc = j, rc = r;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            if (i0 + c < n) v[i0 + c] = run;
+            if (i0 + c < n) {
+                v[i0 + c] = run;
+                if (rc == 0) first[jc] = run;
+            }
             run += x[c];
+            if (++rc == nb) {
+                rc = 0;
+                ++jc;
+            }
+        }
+        j += dj;
+        r += dr;
+        if (r >= nb) {
+            r -= nb;
+            ++j;
         }
         carry += chunk;
         __syncthreads();
     }
-    if (threadIdx.x == 0) total[0] = carry;
+    if (threadIdx.x == 0) first[L] = carry;
 }
 
-template <bool VEC>
+// The counting pass leaves each lane's flags, so the maps are only read where
+// a cell is stored (evaluating the rule again read the kept slices and their
+// neighbours a second time: 74 us on the building).
 __global__ __launch_bounds__(kUBlock) void k_uniq_write(const float* __restrict__ ground,
                                                         const float* __restrict__ ceil,
-                                                        const float* __restrict__ cost, long long plane, float cB,
+                                                        const float* __restrict__ cost, long long plane,
                                                         const UniqSlice* __restrict__ slices, int nb,
                                                         const unsigned long long* __restrict__ offs,
-                                                        int* __restrict__ cell, float* __restrict__ g_out,
-                                                        float* __restrict__ c_out, float* __restrict__ t_out) {
+                                                        const uint8_t* __restrict__ flags, int* __restrict__ cell,
+                                                        float* __restrict__ g_out, float* __restrict__ c_out,
+                                                        float* __restrict__ t_out) {
     __shared__ unsigned s_wave[kUBlock / 64];
     const int j = blockIdx.y, b = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x / 64;
     const long long c0 = (long long)b * kUSpan + (long long)threadIdx.x * kUCells;
-    const long long left = plane - c0;
-    const int nact = left <= 0 ? 0 : (left < kUCells ? (int)left : kUCells);
     const UniqSlice sl = slices[j];
-    const unsigned f = nact > 0 ? uniq_flags<VEC>(ground, cost, plane, cB, sl, c0, nact) : 0u;
+    const unsigned f = flags[((long long)j * nb + b) * kUBlock + threadIdx.x];
     // rank of this lane's first unique cell within the workgroup (raster order)
     const int n = __popc(f);
     int incl = n;
@@ -167,18 +188,13 @@ __global__ __launch_bounds__(kUBlock) void k_uniq_write(const float* __restrict_
     }
 }
 
-__global__ void k_uniq_firsts(const unsigned long long* __restrict__ offs, int nb, int L,
-                              unsigned long long* __restrict__ first) {
-    for (int j = threadIdx.x; j < L; j += blockDim.x) first[j] = offs[(long long)j * nb];
-}
-
 }  // namespace
 
 size_t unique_ws_bytes(int nx, int ny, int N) {
     const long long plane = (long long)nx * ny;
     const long long nb = (plane + kUSpan - 1) / kUSpan;
     return align_up(sizeof(UniqSlice) * (size_t)N) + align_up(sizeof(unsigned long long) * (size_t)(nb * N)) +
-           align_up(sizeof(unsigned long long) * (size_t)(N + 1));
+           align_up(sizeof(unsigned long long) * (size_t)(N + 1)) + align_up((size_t)(nb * kUBlock) * (size_t)N);
 }
 
 pct_status launch_unique(const float* ground, const float* ceil, const float* cost, int nx, int ny, int N, float cB,
@@ -200,17 +216,18 @@ pct_status launch_unique(const float* ground, const float* ceil, const float* co
     unsigned long long* offs = (unsigned long long*)((char*)ws + align_up(sizeof(UniqSlice) * (size_t)N));
     unsigned long long* d_first =
         (unsigned long long*)((char*)offs + align_up(sizeof(unsigned long long) * (size_t)((long long)nb * N)));
+    uint8_t* flags = (uint8_t*)((char*)d_first + align_up(sizeof(unsigned long long) * (size_t)(N + 1)));
     const dim3 grid((unsigned)nb, (unsigned)L);
     if (L > 0) {
         PCT_HIP(hipMemcpyAsync(d_sl, h_sl, sizeof(UniqSlice) * L, hipMemcpyHostToDevice, s));
         if (vec)
-            hipLaunchKernelGGL(k_uniq_count<true>, grid, dim3(kUBlock), 0, s, ground, cost, plane, cB, d_sl, nb, offs);
+            hipLaunchKernelGGL(k_uniq_count<true>, grid, dim3(kUBlock), 0, s, ground, cost, plane, cB, d_sl, nb, offs,
+                               flags);
         else
-            hipLaunchKernelGGL(k_uniq_count<false>, grid, dim3(kUBlock), 0, s, ground, cost, plane, cB, d_sl, nb, offs);
+            hipLaunchKernelGGL(k_uniq_count<false>, grid, dim3(kUBlock), 0, s, ground, cost, plane, cB, d_sl, nb, offs,
+                               flags);
         PCT_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_uniq_scan, dim3(1), dim3(1024), 0, s, offs, (long long)nb * L, d_first + L);
-        PCT_LAUNCH_CHECK();
-        hipLaunchKernelGGL(k_uniq_firsts, dim3(1), dim3(256), 0, s, offs, nb, L, d_first);
+        hipLaunchKernelGGL(k_uniq_scan, dim3(1), dim3(1024), 0, s, offs, nb, L, d_first);
         PCT_LAUNCH_CHECK();
         // the host copy of h_sl must outlive the upload: wait here
         PCT_HIP(hipMemcpyAsync(first.data(), d_first, sizeof(unsigned long long) * (size_t)(L + 1),
@@ -232,12 +249,8 @@ pct_status launch_unique(const float* ground, const float* ceil, const float* co
         return fail(PCT_ERR_CAPACITY, "%lld unique cells exceed the capacity %lld", total, capacity);
     }
     if (cell && total > 0) {
-        if (vec)
-            hipLaunchKernelGGL(k_uniq_write<true>, grid, dim3(kUBlock), 0, s, ground, ceil, cost, plane, cB, d_sl, nb,
-                               offs, cell, g_out, c_out, t_out);
-        else
-            hipLaunchKernelGGL(k_uniq_write<false>, grid, dim3(kUBlock), 0, s, ground, ceil, cost, plane, cB, d_sl, nb,
-                               offs, cell, g_out, c_out, t_out);
+        hipLaunchKernelGGL(k_uniq_write, grid, dim3(kUBlock), 0, s, ground, ceil, cost, plane, d_sl, nb, offs, flags,
+                           cell, g_out, c_out, t_out);
         PCT_LAUNCH_CHECK();
     }
     *h_count = total;
