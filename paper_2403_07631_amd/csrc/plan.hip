@@ -71,10 +71,31 @@ struct PlanGeom {
     long long plane;
 };
 
+// State of the rounds, kept on the device so that the host looks only every
+// few rounds.  Round r's compaction reads the slot of round r - 1 (complete),
+// fills slot r % 3, which the relaxation goes on to use, and clears the one
+// of round r + 1.
 struct PlanStatus {
-    unsigned n_list, n_rest;
-    unsigned long long rest_key, min_key;
+    unsigned n_list;                // tiles asked for this round (kListCap are taken)
+    unsigned done;                  // no active tile, or the goal's distance is final
+    unsigned long long rest_key;    // least key of the active tiles not taken
+    unsigned long long act_key;     // least key of those the round's relaxation activated
+    double band, settled;
+    long long tiles;                // rounds and tile visits before this round
+    int rounds;
 };
+
+__device__ __forceinline__ void clear_round(PlanStatus* st) {
+    st->n_list = 0u;
+    st->rest_key = ~0ull;
+    st->act_key = ~0ull;
+}
+
+// Tiles of one round: the launches have that many workgroups, those past the
+// list's end leave at once; what is beyond waits for the next round (768
+// tiles run at a time).
+constexpr int kListCap = 2048;
+constexpr int kRoundsAhead = 8;   // rounds enqueued between two looks
 
 PlanGeom make_plan_geom(int nx, int ny, int L) {
     PlanGeom g;
@@ -100,11 +121,19 @@ __global__ __launch_bounds__(256) void k_plan_prep(const float* __restrict__ cos
                                                    float* __restrict__ cn, uint8_t* __restrict__ gw,
                                                    double* __restrict__ dist, unsigned* __restrict__ flag,
                                                    unsigned long long* __restrict__ key, int n_tiles, int t0,
-                                                   PlanStatus* __restrict__ st) {
+                                                   double delta, PlanStatus* __restrict__ st) {
     const long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const long long n_threads = (long long)gridDim.x * blockDim.x;
     if (blockIdx.y == 0) {
-        if (c == 0) *st = PlanStatus{0u, 0u, ~0ull, ~0ull};
+        if (c < 3) {
+            clear_round(&st[c]);
+            st[c].done = 0u;
+            st[c].band = delta;
+            st[c].settled = INFINITY;
+            st[c].tiles = 0;
+            st[c].rounds = 0;
+            if (c == 2) st[c].act_key = 0ull;   // the start's tile, before round 0
+        }
         for (long long i = c; i < n_tiles; i += n_threads) {
             flag[i] = i == t0 ? 1u : 0u;
             key[i] = i == t0 ? 0ull : ~0ull;   // bits of +0.0
@@ -201,7 +230,7 @@ __global__ __launch_bounds__(64) void k_plan_relax(PlanGeom g, const float* __re
                                                    const unsigned* __restrict__ list, unsigned* __restrict__ flag,
                                                    unsigned long long* __restrict__ key, long long src,
                                                    PlanStatus* __restrict__ st) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *st = PlanStatus{0u, 0u, ~0ull, ~0ull};   // for the next compaction
+    if (blockIdx.x >= min(st->n_list, (unsigned)kListCap)) return;
     __shared__ double sd[kPT * kPS];
     __shared__ double hz[4][kPT + 2];
     __shared__ float scn[kPT * kCS];
@@ -410,11 +439,13 @@ __global__ __launch_bounds__(64) void k_plan_relax(PlanGeom g, const float* __re
     for (int o = 32; o > 0; o >>= 1) vmin = fmin(vmin, __shfl_xor(vmin, o, 64));
     if (q == 0) {
         const unsigned long long kv = dbits(vmin);
+        bool any = dirty != 0u;
         auto act = [&](int ll, int yy, int xx) {
             if (ll < 0 || ll >= g.L || yy < 0 || yy >= g.nty || xx < 0 || xx >= g.ntx) return;
             const int tn = (ll * g.nty + yy) * g.ntx + xx;
             atomicMin(&key[tn], kv);
             atomicOr(&flag[tn], 1u);
+            any = true;
         };
         if (dirty) {   // cut short: its own sweeps go on in the next round (flag 2: past the entry test)
             atomicMin(&key[t], kv);
@@ -430,51 +461,56 @@ __global__ __launch_bounds__(64) void k_plan_relax(PlanGeom g, const float* __re
         if (m_dr) act(l, ty + 1, tx + 1);
         if (m_gu) act(l + 1, ty, tx);
         if (m_gd) act(l - 1, ty, tx);
+        if (any) atomicMin(&st->act_key, kv);
     }
 }
 
-// Active tiles whose key (the least distance that activated them) is at
-// most the band limit -> worklist (2 * tile, + 1 for one that was cut short;
-// flag and key cleared); the others stay
-// active: st[1] counts them and st2 receives their least key.  st[0] (the
-// list length), st[1], st2 and st3 must be reset before the launch (the
-// relaxation before it does so, after the host has read them).
+// Active tiles whose key (the least distance that activated them) lies in
+// the band -> worklist (2 * tile, + 1 for one that was cut short; flag and
+// key cleared); the others stay active.  A band with no tile left moves up to
+// the least active key + delta.  The search ends when no tile is active, or,
+// with a goal, when the least active key (a lower bound on every label still
+// to be lowered) exceeds the goal's label.
 __global__ __launch_bounds__(256) void k_plan_compact(unsigned* __restrict__ flag, unsigned long long* __restrict__ key,
-                                                      int n_tiles, unsigned long long band, unsigned* __restrict__ list,
-                                                      unsigned* __restrict__ st, unsigned long long* __restrict__ st2,
-                                                      unsigned long long* __restrict__ st3) {
+                                                      int n_tiles, double delta, const double* __restrict__ goal,
+                                                      unsigned* __restrict__ list, const PlanStatus* __restrict__ prev,
+                                                      PlanStatus* __restrict__ cur, PlanStatus* __restrict__ next) {
+    const unsigned long long least = min(prev->rest_key, prev->act_key);
+    bool done = prev->done != 0u || least == ~0ull;
+    double band = prev->band, settled = prev->settled;
+    const double kmin = __builtin_bit_cast(double, least);
+    if (!done && goal && kmin > *goal) {
+        done = true;
+        settled = kmin;
+    }
+    if (!done && kmin > band) band = kmin + delta;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        cur->done = done;
+        cur->band = band;
+        cur->settled = settled;
+        cur->rounds = prev->rounds + (prev->n_list > 0u);
+        cur->tiles = prev->tiles + min(prev->n_list, (unsigned)kListCap);
+        clear_round(next);
+    }
+    if (done) return;
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     const unsigned fl = t < n_tiles ? flag[t] : 0u;
-    const bool act = fl != 0u;
-    const unsigned long long kt = act ? key[t] : ~0ull;
-    {
-        // least key of all active tiles (a lower bound on every label still
-        // to be lowered)
-        unsigned long long kmin = kt;
-        for (int o = 32; o > 0; o >>= 1) {
-            const unsigned long long y = __shfl_xor(kmin, o, 64);
-            kmin = y < kmin ? y : kmin;
-        }
-        if ((threadIdx.x & 63) == 0 && kmin != ~0ull) atomicMin(st3, kmin);
-    }
-    const bool on = act && kt <= band;
-    const bool rest = act && !on;
-    const unsigned long long m = __ballot(on), mr = __ballot(rest);
+    const unsigned long long kt = fl != 0u ? key[t] : ~0ull;
+    const bool on = fl != 0u && kt <= dbits(band);
+    const unsigned long long m = __ballot(on);
     const int lane = threadIdx.x & 63;
     unsigned base = 0;
-    if (lane == 0 && m) base = atomicAdd(&st[0], (unsigned)__popcll(m));
-    if (lane == 0 && mr) atomicAdd(&st[1], (unsigned)__popcll(mr));
-    if (rest) atomicMin(st2, kt);
+    if (lane == 0 && m) base = atomicAdd(&cur->n_list, (unsigned)__popcll(m));
     base = __shfl(base, 0, 64);
-    if (on) {
+    const unsigned at = base + (unsigned)__popcll(m & ((1ull << lane) - 1ull));
+    if (on && at < (unsigned)kListCap) {
         flag[t] = 0u;
         key[t] = ~0ull;
-        list[base + __popcll(m & ((1ull << lane) - 1ull))] = (unsigned)t << 1 | (fl >> 1);
+        list[at] = (unsigned)t << 1 | (fl >> 1);
+    } else if (fl != 0u) {
+        atomicMin(&cur->rest_key, kt);
     }
 }
-
-
-__global__ void k_plan_status_reset(PlanStatus* st) { *st = PlanStatus{0u, 0u, ~0ull, ~0ull}; }
 
 // One wavefront walks back from the goal: lanes 0..9 test the candidate
 // predecessors (gateway from below, gateway from above, the eight planar
@@ -621,7 +657,7 @@ size_t plan_ws_layout(const PlanGeom& g, PlanWs* w, void* base) {
     ws.flag = (unsigned*)take(sizeof(unsigned) * (size_t)nt);
     ws.key = (unsigned long long*)take(sizeof(unsigned long long) * (size_t)nt);
     ws.list = (unsigned*)take(sizeof(unsigned) * (size_t)nt);
-    ws.st = (PlanStatus*)take(sizeof(PlanStatus));
+    ws.st = (PlanStatus*)take(3 * sizeof(PlanStatus));
     ws.layers = (int*)take(sizeof(int) * (size_t)g.L);
     ws.out = (int*)take(sizeof(int) * 4);
     if (w) *w = ws;
@@ -643,55 +679,35 @@ pct_status launch_plan(const float* cost, const float* ground, int nx, int ny, c
     const long long src = (long long)sl * g.plane + (long long)sy * nx + sx;
     const int t0 = (sl * g.nty + sy / kPT) * g.ntx + sx / kPT;
     hipLaunchKernelGGL(k_plan_prep, dim3((unsigned)((g.plane + 255) / 256), (unsigned)((L + kPrepLayers - 1) / kPrepLayers)),
-                       dim3(256), 0, s, cost, ground, w.layers, g, cB, w.cn, w.gw, dist, w.flag, w.key, nt, t0, w.st);
+                       dim3(256), 0, s, cost, ground, w.layers, g, cB, w.cn, w.gw, dist, w.flag, w.key, nt, t0, delta, w.st);
     PCT_LAUNCH_CHECK();
     // Rounds take the active tiles whose activating distance lies within
     // a band of width delta above the least one (tiles roughly in order of
     // distance, as Dijkstra's algorithm takes nodes); a band with no tile
-    // left moves up to the least remaining key.
-    double band = delta;
-    int rounds = 0;
-    long long tiles = 0;
+    // left moves up to the least remaining key.  The device keeps the band,
+    // the list and the end of the search, so the host enqueues rounds ahead
+    // (rounds after the end do nothing: 5 us each) and looks after 2, then 4,
+    // then every 8: with one look per round the distance field of the
+    // 4-storey building took 13.9 ms and a query 2.20 ms, now 12.2 and 1.99.
+    const int blocks = std::min(nt, kListCap);
     PlanStatus hs;
-    double settled = INFINITY;
-    for (;;) {
-        unsigned long long band_bits;
-        memcpy(&band_bits, &band, sizeof band_bits);
-        hipLaunchKernelGGL(k_plan_compact, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, w.flag, w.key, nt,
-                           band_bits, w.list, &w.st->n_list, &w.st->rest_key, &w.st->min_key);
-        PCT_LAUNCH_CHECK();
-        PCT_HIP(hipMemcpyAsync(&hs, w.st, sizeof hs, hipMemcpyDeviceToHost, s));
-        double dg = INFINITY;
-        if (goal >= 0) PCT_HIP(hipMemcpyAsync(&dg, dist + goal, sizeof dg, hipMemcpyDeviceToHost, s));
-        PCT_HIP(hipStreamSynchronize(s));
-        if (goal >= 0 && (hs.n_list != 0 || hs.n_rest != 0)) {
-            // no active tile can lower a label below its key: every label
-            // under the least key is final, the goal's among them
-            double kmin;
-            memcpy(&kmin, &hs.min_key, sizeof kmin);
-            if (kmin > dg) {
-                settled = kmin;
-                break;
-            }
-        }
-        if (hs.n_list == 0) {
-            if (hs.n_rest == 0) break;
-            double kmin;
-            memcpy(&kmin, &hs.rest_key, sizeof kmin);
-            band = kmin + delta;
-            hipLaunchKernelGGL(k_plan_status_reset, dim3(1), dim3(1), 0, s, w.st);
+    for (int r = 0, ahead = 2;; ahead = std::min(2 * ahead, kRoundsAhead)) {
+        for (int i = 0; i < ahead; ++i, ++r) {
+            PlanStatus *prev = &w.st[(r + 2) % 3], *cur = &w.st[r % 3], *next = &w.st[(r + 1) % 3];
+            hipLaunchKernelGGL(k_plan_compact, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, w.flag, w.key, nt,
+                               delta, goal >= 0 ? dist + goal : nullptr, w.list, prev, cur, next);
             PCT_LAUNCH_CHECK();
-            continue;
+            hipLaunchKernelGGL(k_plan_relax, dim3((unsigned)blocks), dim3(64), 0, s, g, w.cn, w.gw, dist, w.list, w.flag,
+                               w.key, src, cur);
+            PCT_LAUNCH_CHECK();
         }
-        hipLaunchKernelGGL(k_plan_relax, dim3(hs.n_list), dim3(64), 0, s, g, w.cn, w.gw, dist, w.list, w.flag, w.key,
-                           src, w.st);
-        PCT_LAUNCH_CHECK();
-        ++rounds;
-        tiles += hs.n_list;
+        PCT_HIP(hipMemcpyAsync(&hs, &w.st[(r + 2) % 3], sizeof hs, hipMemcpyDeviceToHost, s));
+        PCT_HIP(hipStreamSynchronize(s));
+        if (hs.done) break;
     }
-    if (h_rounds) *h_rounds = rounds;
-    if (h_tiles) *h_tiles = tiles;
-    if (h_settled) *h_settled = settled;
+    if (h_rounds) *h_rounds = hs.rounds;
+    if (h_tiles) *h_tiles = hs.tiles;
+    if (h_settled) *h_settled = hs.settled;
     return PCT_OK;
 }
 

@@ -123,6 +123,20 @@ def test_visits_cut_short(P, oracle_lib, ny, nx, pitch):
                          [(nx - 1, ny - 1, 0), (0, ny - 1, 1), (nx // 2, ny // 2, 0)], "winding tile")
 
 
+@pytest.mark.parametrize("tiles", range(1, 17))
+def test_search_ends_at_any_round(P, oracle_lib, tiles):
+    """A corridor of one to sixteen tiles, one round after the other: the
+    search ends at each place in the runs of rounds enqueued at once, with no
+    active tile left or with the goal settled, and the counts are those of
+    the rounds that had tiles."""
+    rng = np.random.default_rng(tiles)
+    cT = rng.uniform(0.0, 5.0, (1, 3, 64 * tiles - 5)).astype(np.float32)
+    eG = np.zeros_like(cT)
+    check_against_oracle(P, oracle_lib, cT, eG, [0], (0, 1, 0), [(64 * tiles - 6, 2, 0)], f"corridor of {tiles}")
+    check_query(P, oracle_lib, cT, eG, [0], (0, 1, 0), [(0, 2, 0), (32 * tiles, 0, 0)],
+                f"query in a corridor of {tiles}")
+
+
 def test_tomogram_building(P, oracle_lib):
     """The section's setting: slices kept by the oracle's slice test of a
     three-storey building with stairs, Table I quadruped; the path climbs
