@@ -113,7 +113,7 @@ int plane_count(float zmin, float zmax, float ds, int cap) {
 
 }  // namespace
 
-pct_status make_eval_params(const pct_robot& r, const pct_grid& g, int N, EvalParams* out) {
+pct_status make_eval_params(const pct_robot& r, const pct_grid& g, int N, EvalParams* out, const EvalParams* same) {
     EvalParams p{};
     p.nx = g.nx;
     p.ny = g.ny;
@@ -138,8 +138,12 @@ pct_status make_eval_params(const pct_robot& r, const pct_grid& g, int N, EvalPa
     p.rp = r.patch_radius;
     const int np = (2 * r.patch_radius + 1) * (2 * r.patch_radius + 1) - 1;
     p.kp = (int)floor((double)r.theta_p * (double)np);
-    for (int a = 0; a < kKmax; ++a)
-        for (int j = 0; j < kKmax; ++j) p.K[a][j] = (float)kernel_weight(r, g.res, a, j);
+    if (same) {
+        memcpy(p.K, same->K, sizeof p.K);
+    } else {
+        for (int a = 0; a < kKmax; ++a)
+            for (int j = 0; j < kKmax; ++j) p.K[a][j] = (float)kernel_weight(r, g.res, a, j);
+    }
     *out = p;
     return PCT_OK;
 }

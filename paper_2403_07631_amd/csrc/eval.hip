@@ -1337,15 +1337,20 @@ pct_status plan_jobs(const pct_item* items, int n_items, const pct_robot* robots
                                                            (long long)items[i].extent.n_slices * items[i].grid.nx * items[i].grid.ny);
         total_slices = std::max<long long>(total_slices, items[i].keep_offset + items[i].extent.n_slices);
     }
-    for (int r = 0; r < n_robots; ++r)
+    jp->jobs.reserve((size_t)n_items * n_robots);
+    for (int r = 0; r < n_robots; ++r) {
+        int last = -1;   // the robot's last item with slices: at its resolution the weights are the same
         for (int i = 0; i < n_items; ++i) {
             const int N = items[i].extent.n_slices;
             if (N <= 0) continue;
             EvalJob jb{};
-            pct_status st = make_eval_params(robots[r], items[i].grid, N, &jb.p);
+            const bool same = last >= 0 && items[last].grid.res == items[i].grid.res;
+            pct_status st = make_eval_params(robots[r], items[i].grid, N, &jb.p, same ? &jp->jobs.back().p : nullptr);
             if (st != PCT_OK) return st;
             jp->jobs.push_back(jb);
+            last = i;
         }
+    }
     int rows = kBatchRows;
     for (; rows > 16; rows /= 2) {
         long long waves = 0;

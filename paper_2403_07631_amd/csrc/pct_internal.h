@@ -6,6 +6,7 @@
 #include <limits.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <string.h>
 
 #include "pct.h"
 
@@ -136,7 +137,10 @@ struct EvalParams {
     float K[kKmax][kKmax];  // K[a][j]: Eq. (6) weight at horizontal offset a, vertical offset j
 };
 
-pct_status make_eval_params(const pct_robot& r, const pct_grid& g, int N, EvalParams* out);
+// same: parameters of the same robot at the same resolution, whose weights
+// are taken over (289 roots and divisions otherwise)
+pct_status make_eval_params(const pct_robot& r, const pct_grid& g, int N, EvalParams* out,
+                            const EvalParams* same = nullptr);
 // The weights that are zero become NaN: the adjoints' window maxima pass
 // over the products of such taps without a test per tap.
 void mark_zero_taps(EvalParams& p);
@@ -196,8 +200,14 @@ struct Digest {
     uint64_t h = 1469598103934665603ull;
     template <class T>
     void add(const T& v) {
-        const unsigned char* b = (const unsigned char*)&v;
-        for (size_t i = 0; i < sizeof(T); ++i) h = (h ^ b[i]) * 1099511628211ull;
+        // a value at a time (a batch's items carry 320 values each: byte by
+        // byte the chain of multiplications took 1.3 us an item); the fold
+        // brings high bits down, and each step is a bijection of h
+        static_assert(sizeof(T) <= sizeof(uint64_t), "one word per value");
+        uint64_t w = 0;
+        memcpy(&w, &v, sizeof(T));
+        h = (h ^ w) * 1099511628211ull;
+        h ^= h >> 32;
     }
 };
 void digest_params(Digest& d, const EvalParams& p);

@@ -134,6 +134,34 @@ def test_batched_many_robots(P):
         np.testing.assert_array_equal(bits(keep[r, :ext.n_slices]), bits(ks[0]))
 
 
+@pytest.mark.parametrize("res", [(0.1, 0.2, 0.1, 0.1), (0.2, 0.2, 0.1, 0.25)])
+def test_batched_resolutions(P, res):
+    """Items of several resolutions and an item without points between them,
+    two robots: every item takes its own resolution's weights."""
+    import torch
+    rng = np.random.default_rng(19)
+    specs, pts, off = [], [], 0
+    for i, r in enumerate(res):
+        n = 0 if i == 2 else 9000
+        p = (rng.uniform(0.0, 1.0, (n, 3)) * [70 * r, 50 * r, 2.5]).astype(np.float32)
+        specs.append(dict(xyz_offset=off, n_points=n, grid=dict(x0=0.0, y0=0.0, res=r, nx=70, ny=50, slice_dz=0.3)))
+        pts.append(p)
+        off += n
+    rbs = [P.robot_from_physical(p, 0.1) for p in scenes.robot_profiles(5, 2)]
+    b = P.Batch(torch.from_numpy(np.concatenate(pts)).cuda(), specs, n_robots=2)
+    P.pct_tomogram_extent_batched(b)
+    G, Cc, _, _ = P.pct_build_tomogram_batched(b)
+    cost, keep = P.pct_eval_traversability_batched(b, G, Cc, rbs)
+    for i, sp in enumerate(specs):
+        ext = b.items[i].extent
+        if ext.n_slices == 0:
+            continue
+        for r, rb in enumerate(rbs):
+            cs, _ = P.pct_eval_traversability(b.item_view(G, i).contiguous(), b.item_view(Cc, i).contiguous(),
+                                              sp["grid"], ext, [rb])
+            np.testing.assert_array_equal(bits(b.item_view(cost[r], i)), bits(cs[0]))
+
+
 def test_graph_capture_replays(P):
     """The batched build and evaluation captured in one graph; every replay,
     with eager work and synchronisation in between, equals the eager run."""
