@@ -15,11 +15,14 @@ namespace pct {
 namespace {
 
 constexpr int kBlock = 256;
-// LDS slots of the tile reduce: at least kReduceCap (a cell has at most
-// PCT_MAX_SLICES + 1), at most kReduceBins per cell of a tile.
+// LDS slots of the tile reduce: at least kReduceCap and three per cell (a part
+// of one plane with the bins below and above it), at most kReduceBins per
+// cell of a tile, and no more than the LDS of a CU holds.
 constexpr int kReduceCap = 2048;
 constexpr int kReduceBins = 8;
-static_assert(kReduceCap > PCT_MAX_SLICES, "one cell's bins fit");
+constexpr int kReduceWords = 4;                         // words of bins per cell
+constexpr size_t kReduceLds = 160 * 1024 - 1024;        // of the tile reduce's dynamic LDS
+constexpr int kMaxTileCells = 256 * 8;
 
 __device__ __forceinline__ float wave_min(float v) {
     for (int m = 32; m >= 1; m >>= 1) v = fminf(v, __shfl_xor(v, m, 64));
@@ -663,7 +666,13 @@ __global__ __launch_bounds__(kBinBlock) void k_bin2_scatter_staged(const float* 
 // inserted into it with the window's evaluation 0.68 -> 0.34 ms, the 20M-point
 // map (5 per cell, bound by the stores) 0.80 -> 0.77 ms.  Eight bins per cell
 // keep four workgroups on a CU (two with ids); six to ten measure alike, four
-// or five cut the building's tiles into groups (+10 %).
+// or five cut the building's tiles (+10 %).
+//
+// Planes are taken in parts of at most 126 (127 if one part is all), so that
+// the matrix has at most four words per cell whatever the plane count and
+// tile size; a part whose occupied bins exceed the slots is shortened until
+// they fit.  What lies below a part counts as one bin below its first, what
+// lies above as one past its last, so parts need nothing from one another.
 constexpr int kReduceBlock = 512;   // one cell per thread for the 512-cell tiles
 constexpr int kReduceKeep = 4;      // records per thread kept in registers between the passes
 
@@ -732,22 +741,23 @@ __device__ __forceinline__ void merge_vals(float og, float oc, int oi, int oj, f
     }
 }
 
-// One cell: walk the planes over its occupied bins (bits of `mask`, `words`
-// words `stride` apart) and their extremes smax, smin.  The next occupied
-// bin's extremes are read ahead.  MERGE: combine with the stored values
-// instead of overwriting them (ids are offset by id_base); a cell without
-// records is left as it is.
+// One cell: walk the planes k_lo .. k_lo + P - 1 of a part over the cell's
+// occupied bins (bits of `mask`, words `stride` apart; plane k_lo is bit
+// `lead`, and with lead = 1 bit 0 is the bin of what lies below) and their
+// extremes smax, smin.  The next occupied bin's extremes are read ahead.
+// MERGE: combine with the stored values instead of overwriting them (ids
+// are offset by id_base); a cell without records is left as it is.
 template <bool IDS, bool MERGE>
 __device__ __forceinline__ void sweep_cell(const unsigned* mask, int stride,
                                            const typename SlotKeys<IDS>::T* smax,
                                            const typename SlotKeys<IDS>::T* smin, int n, int ix, int iy,
-                                           const GridDev& g, int N, float* __restrict__ ground,
+                                           const GridDev& g, int lead, int k_lo, int P, float* __restrict__ ground,
                                            float* __restrict__ ceil, int* __restrict__ ag, int* __restrict__ ac,
                                            int id_base) {
     typedef SlotKeys<IDS> S;
     if (MERGE && n == 0) return;
     const int64_t plane = (int64_t)g.nx * g.ny;
-    int64_t o = (int64_t)iy * g.nx + ix;
+    int64_t o = (int64_t)k_lo * plane + (int64_t)iy * g.nx + ix;
     float gz = -INFINITY, cz = INFINITY, nextz = -INFINITY;
     int gi = -1, ci = -1, nexti = -1;
     int j = 0;
@@ -766,35 +776,37 @@ __device__ __forceinline__ void sweep_cell(const unsigned* mask, int stride,
         }
     };
     read_next();
+    unsigned bits = mask[0];
+    auto take = [&]() {
+        gz = nextz;
+        gi = nexti;
+        ++j;
+        read_next();
+    };
+    if (lead && (bits & 1u)) take();
     // MERGE reads the stored values of kAhead planes before it writes
     // any of them, so that their loads overlap
     constexpr int kAhead = MERGE ? 8 : 1;
-    unsigned bits = 0u;
-    for (int k0 = 0; k0 < N; k0 += kAhead) {
+    for (int q0 = lead; q0 < lead + P; q0 += kAhead) {
         float og[kAhead], oc[kAhead];
         int oi[kAhead], oj[kAhead];
-        if ((k0 & 31) == 0) bits = mask[(k0 >> 5) * stride];
         if (MERGE) {
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
-                if (k0 + u >= N) break;
-                const int64_t q = o + u * plane;
-                og[u] = ground[q];
-                oc[u] = ceil[q];
-                oi[u] = IDS ? ag[q] : 0;
-                oj[u] = IDS ? ac[q] : 0;
+                if (q0 + u >= lead + P) break;
+                const int64_t i = o + u * plane;
+                og[u] = ground[i];
+                oc[u] = ceil[i];
+                oi[u] = IDS ? ag[i] : 0;
+                oj[u] = IDS ? ac[i] : 0;
             }
         }
 #pragma unroll
         for (int u = 0; u < kAhead; ++u, o += plane) {
-            const int k = k0 + u;
-            if (k >= N) break;
-            if ((bits >> (k & 31)) & 1u) {
-                gz = nextz;
-                gi = nexti;
-                ++j;
-                read_next();
-            }
+            const int q = q0 + u;
+            if (q >= lead + P) break;
+            if ((q & 31) == 0) bits = mask[(q >> 5) * stride];
+            if ((bits >> (q & 31)) & 1u) take();
             float vg = gz, vc = cz;
             int wg = gi, wc = ci;
             if (MERGE) merge_vals(og[u], oc[u], oi[u], oj[u], vg, wg, vc, wc);
@@ -809,19 +821,28 @@ __device__ __forceinline__ void sweep_cell(const unsigned* mask, int stride,
     }
 }
 
+// Words of bins per cell, and LDS bytes beside the slots: the bit matrix and
+// the cells' first slots.
+__host__ __device__ inline int reduce_words(int N) { return N / 32 + 1 < kReduceWords ? N / 32 + 1 : kReduceWords; }
+__host__ __device__ inline unsigned reduce_fixed_bytes(int cells, int N) {
+    return (unsigned)sizeof(unsigned) * (unsigned)(reduce_words(N) * cells + cells + 1);
+}
+static_assert(sizeof(unsigned) * ((kReduceWords + 1) * kMaxTileCells + 1) + 16 * 3 * kMaxTileCells <= kReduceLds,
+              "three slots per cell fit beside the largest bit matrix");
+
 // One construction tile: records off[tg] .. off[tg+1] of the tile whose
 // position in its grid is tl.  Shared by the single-map and batched kernels.
-// CAP: slots that fit in LDS; a tile with more takes groups of cells in
-// turn, reading its records again for each.
+// lds: bytes of dynamic LDS, at least three slots per cell beside the rest.
 template <bool IDS, bool MERGE = false>
 __device__ void reduce_tile(int tg, int tl, const unsigned* __restrict__ off, const float* __restrict__ rz,
                             const unsigned* __restrict__ rmeta, const int* __restrict__ rid, const GridDev& g,
                             float zmin, float ds, int N, float* __restrict__ ground, float* __restrict__ ceil,
-                            int* __restrict__ ag, int* __restrict__ ac, int CAP, int id_base = 0) {
+                            int* __restrict__ ag, int* __restrict__ ac, unsigned lds, int id_base = 0) {
     typedef SlotKeys<IDS> S;
     extern __shared__ unsigned s_mem[];
     const int cells = g.tw * g.th;
-    const int W = N / 32 + 1;                // bins 0 .. N
+    const int W = reduce_words(N);
+    const int CAP = (int)((lds - reduce_fixed_bytes(cells, N)) / (2 * sizeof(typename S::T)));
     typename S::T* s_max = (typename S::T*)s_mem;
     typename S::T* s_min = s_max + CAP;
     unsigned* s_bits = (unsigned*)(s_min + CAP);   // [W][cells]
@@ -833,17 +854,10 @@ __device__ void reduce_tile(int tg, int tl, const unsigned* __restrict__ off, co
     if (MERGE && r0 == r1) return;   // an insertion leaves tiles without new points alone
 
     const float inv_ds = 1.0f / ds;
-    for (int i = threadIdx.x; i < W * cells; i += kReduceBlock) s_bits[i] = 0u;
-    __syncthreads();
-    // occupied bins; a thread's first kReduceKeep records stay in registers
+    // a thread's first kReduceKeep records stay in registers
     unsigned kc[kReduceKeep];   // cell | bin << 16; ~0: no record
     float kz[kReduceKeep];
     int ki[kReduceKeep];
-    auto mark = [&](unsigned c, float z) -> unsigned {
-        const unsigned b = (unsigned)plane_bin(z, zmin, ds, inv_ds, N);
-        atomicOr(&s_bits[(b >> 5) * cells + c], 1u << (b & 31));
-        return b;
-    };
 #pragma unroll
     for (int q = 0; q < kReduceKeep; ++q) {
         const unsigned r = r0 + q * kReduceBlock + threadIdx.x;
@@ -854,52 +868,79 @@ __device__ void reduce_tile(int tg, int tl, const unsigned* __restrict__ off, co
     }
 #pragma unroll
     for (int q = 0; q < kReduceKeep; ++q)
-        if (kc[q] != ~0u) kc[q] |= mark(kc[q], kz[q]) << 16;
+        if (kc[q] != ~0u) kc[q] |= (unsigned)plane_bin(kz[q], zmin, ds, inv_ds, N) << 16;
     const unsigned r2 = r0 + kReduceKeep * kReduceBlock;
-    for (unsigned r = r2 + threadIdx.x; r < r1; r += kReduceBlock) mark(rmeta[r], rz[r]);
-    __syncthreads();
-    // slots: thread i owns a contiguous run of cells
-    {
-        const int per = (cells + kReduceBlock - 1) / kReduceBlock;
-        const int b = min((int)threadIdx.x * per, cells), e = min(b + per, cells);
-        unsigned sum = 0, total;
-        for (int c = b; c < e; ++c)
-            for (int w = 0; w < W; ++w) sum += (unsigned)__popc(s_bits[w * cells + c]);
-        unsigned run = block_scan_excl(sum, s_w, total);
-        for (int c = b; c < e; ++c) {
-            s_base[c] = run;
-            for (int w = 0; w < W; ++w) run += (unsigned)__popc(s_bits[w * cells + c]);
-        }
-        if (threadIdx.x == 0) s_base[cells] = total;
-    }
-    __syncthreads();
+    const int parts = N < 32 * kReduceWords ? 1 : (N + 32 * kReduceWords - 3) / (32 * kReduceWords - 2);
+    const int even = (N + parts - 1) / parts;
 
-    int c_lo = 0;
-    while (c_lo < cells) {
-        // largest group [c_lo, c_hi) whose slots fit in LDS; one cell has at
-        // most N + 1 <= CAP
-        int c_hi = cells;
-        const unsigned g0 = s_base[c_lo];
-        if (s_base[cells] - g0 > (unsigned)CAP) {
-            int lo = c_lo + 1;
-            while (lo < c_hi) {
-                const int mid = (lo + c_hi + 1) / 2;
-                if (s_base[mid] - g0 <= (unsigned)CAP) lo = mid;
-                else c_hi = mid - 1;
+    for (int k_lo = 0; k_lo < N;) {
+        const int lead = k_lo > 0 ? 1 : 0;
+        int P = min(even, N - k_lo);
+        auto place = [&](unsigned b) -> unsigned {   // bit of bin b in this part
+            return (int)b < k_lo ? 0u : (unsigned)(min((int)b - k_lo, P) + lead);
+        };
+        for (int i = threadIdx.x; i < W * cells; i += kReduceBlock) s_bits[i] = 0u;
+        __syncthreads();
+        auto mark = [&](unsigned c, unsigned b) {
+            const unsigned q = place(b);
+            atomicOr(&s_bits[(q >> 5) * cells + c], 1u << (q & 31));
+        };
+#pragma unroll
+        for (int q = 0; q < kReduceKeep; ++q)
+            if (kc[q] != ~0u) mark(kc[q] & 0xffffu, kc[q] >> 16);
+        for (unsigned r = r2 + threadIdx.x; r < r1; r += kReduceBlock)
+            mark(rmeta[r], (unsigned)plane_bin(rz[r], zmin, ds, inv_ds, N));
+        __syncthreads();
+        // slots: thread i owns a contiguous run of cells; bins from bit
+        // lead + P on share the last slot
+        const int per = (cells + kReduceBlock - 1) / kReduceBlock;
+        const int cb = min((int)threadIdx.x * per, cells), ce = min(cb + per, cells);
+        const int marked = P;
+        auto slots_of = [&](int c) -> unsigned {
+            const int tw = (lead + P) >> 5;
+            const unsigned low = (1u << ((lead + P) & 31)) - 1u;
+            unsigned n = 0u, past = 0u;
+            for (int w = 0; w < W; ++w) {
+                const unsigned v = s_bits[w * cells + c];
+                const unsigned in = w < tw ? v : (w == tw ? v & low : 0u);
+                n += (unsigned)__popc(in);
+                past |= v & ~in;
+            }
+            return n + (past != 0u ? 1u : 0u);
+        };
+        unsigned run, total;
+        for (;;) {
+            unsigned sum = 0;
+            for (int c = cb; c < ce; ++c) sum += slots_of(c);
+            run = block_scan_excl(sum, s_w, total);
+            if (total <= (unsigned)CAP) break;
+            // the planes' share of the slots, in proportion; CAP / cells - 2
+            // planes always fit, so this ends
+            const int share = (int)((long long)P * (CAP - 2 * cells) / ((int)total - 2 * cells));
+            P = max(CAP / cells - 2, min(P - 1, share));
+        }
+        for (int c = cb; c < ce; ++c) {
+            s_base[c] = run;
+            run += slots_of(c);
+            if (P < marked) {
+                const int top = lead + P, tw = top >> 5;
+                const unsigned low = (1u << (top & 31)) - 1u;
+                unsigned past = s_bits[tw * cells + c] & ~low;
+                for (int w = tw + 1; w < W; ++w) past |= s_bits[w * cells + c];
+                s_bits[tw * cells + c] = (s_bits[tw * cells + c] & low) | (past != 0u ? 1u << (top & 31) : 0u);
             }
         }
-        const int ns = (int)(s_base[c_hi] - g0);
-        for (int i = threadIdx.x; i < ns; i += kReduceBlock) {
+        if (threadIdx.x == 0) s_base[cells] = total;
+        for (int i = threadIdx.x; i < (int)total; i += kReduceBlock) {
             s_max[i] = S::none_max();
             s_min[i] = S::none_min();
         }
         __syncthreads();
         auto put = [&](unsigned c, unsigned b, float z, int id) {
-            if ((int)c < c_lo || (int)c >= c_hi) return;
-            unsigned slot = s_base[c] - g0;
-            const unsigned w = b >> 5;
+            const unsigned q = place(b), w = q >> 5;
+            unsigned slot = s_base[c];
             for (unsigned v = 0; v < w; ++v) slot += (unsigned)__popc(s_bits[v * cells + c]);
-            slot += (unsigned)__popc(s_bits[w * cells + c] & ((1u << (b & 31)) - 1u));
+            slot += (unsigned)__popc(s_bits[w * cells + c] & ((1u << (q & 31)) - 1u));
             atomicMax(&s_max[slot], S::max_key(z, id));
             atomicMin(&s_min[slot], S::min_key(z, id));
         };
@@ -911,16 +952,16 @@ __device__ void reduce_tile(int tg, int tl, const unsigned* __restrict__ off, co
             put(rmeta[r], (unsigned)plane_bin(z, zmin, ds, inv_ds, N), z, IDS ? rid[r] : 0);
         }
         __syncthreads();
-        for (int c = c_lo + threadIdx.x; c < c_hi; c += kReduceBlock) {
+        for (int c = threadIdx.x; c < cells; c += kReduceBlock) {
             const int ix = tx * g.tw + (c % g.tw);
             const int iy = ty * g.th + c / g.tw;
             if (ix >= g.nx || iy >= g.ny) continue;
-            const unsigned s = s_base[c] - g0;
-            sweep_cell<IDS, MERGE>(s_bits + c, cells, s_max + s, s_min + s, (int)(s_base[c + 1] - s_base[c]), ix, iy, g,
-                                   N, ground, ceil, ag, ac, id_base);
+            const unsigned s = s_base[c];
+            sweep_cell<IDS, MERGE>(s_bits + c, cells, s_max + s, s_min + s, (int)(s_base[c + 1] - s), ix, iy, g, lead,
+                                   k_lo, P, ground, ceil, ag, ac, id_base);
         }
-        __syncthreads();
-        c_lo = c_hi;
+        k_lo += P;
+        if (k_lo < N) __syncthreads();   // the next part clears the bits
     }
 }
 
@@ -931,24 +972,22 @@ __global__ __launch_bounds__(kReduceBlock, MERGE || IDS ? 4 : 8) void k_tile_red
                                                         const int* __restrict__ rid, GridDev g, float zmin,
                                                         float ds, int N, float* __restrict__ ground,
                                                         float* __restrict__ ceil, int* __restrict__ ag,
-                                                        int* __restrict__ ac, int cap, int id_base) {
+                                                        int* __restrict__ ac, unsigned lds, int id_base) {
     reduce_tile<IDS, MERGE>((int)blockIdx.x, (int)blockIdx.x, off, rz, rmeta, rid, g, zmin, ds, N, ground, ceil, ag,
-                            ac, cap, id_base);
+                            ac, lds, id_base);
 }
 
-// Slots per tile in LDS: 1.25x the mean records per tile (rounded up to
-// 1024), which a tile's occupied bins seldom exceed, at most kReduceBins bins
-// per cell (storeyed scenes occupy two or three bins per surface), and at
-// least one cell's N + 1.
-inline int reduce_cap(int64_t n, const GridDev& g) {
+// Dynamic LDS of a tile's reduce: slots for 1.25x the mean records per tile
+// (rounded up to 1024), which a tile's occupied bins seldom exceed, at most
+// kReduceBins bins per cell (storeyed scenes occupy two or three bins per
+// surface), within the LDS of a CU.
+inline unsigned reduce_lds_bytes(int64_t n, const GridDev& g, int N, bool ids) {
+    const int64_t cells = (int64_t)g.tw * g.th, slot = ids ? 16 : 8, fixed = reduce_fixed_bytes((int)cells, N);
     const int64_t mean = g.ntiles > 0 ? n / g.ntiles : 0;
     const int64_t want = (mean + mean / 4 + 1023) / 1024 * 1024;
-    return (int)std::min<int64_t>((int64_t)kReduceBins * g.tw * g.th, std::max<int64_t>(kReduceCap, want));
-}
-
-inline size_t reduce_lds_bytes(const GridDev& g, int N, bool ids, int cap) {
-    const int cells = g.tw * g.th;
-    return sizeof(unsigned) * ((size_t)(N / 32 + 1) * cells + cells + 1) + (size_t)cap * (ids ? 16 : 8);
+    int64_t cap = std::min<int64_t>(kReduceBins * cells, std::max<int64_t>(kReduceCap, want));
+    cap = std::min<int64_t>(cap, ((int64_t)kReduceLds - fixed) / slot);
+    return (unsigned)(fixed + slot * std::max<int64_t>(cap, 3 * cells));
 }
 
 // Kernels may take more than 64 KB of LDS only once asked for.
@@ -1213,14 +1252,14 @@ __global__ __launch_bounds__(kReduceBlock, IDS ? 4 : 8) void k_breduce(const uns
                                                     const unsigned* __restrict__ rmeta, const int* __restrict__ rid,
                                                     const BuildItemDev* __restrict__ items, int n_items,
                                                     float* __restrict__ ground, float* __restrict__ ceil,
-                                                    int* __restrict__ ag, int* __restrict__ ac, int cap) {
+                                                    int* __restrict__ ag, int* __restrict__ ac, unsigned lds) {
     const int tg = blockIdx.x;
     const int it = find_base(items, n_items, tg, 1);
     const BuildItemDev& d = items[it];
     if (d.N <= 0) return;
     const long long o = d.out_off;
     reduce_tile<IDS>(tg, tg - d.tile_base, off, rz, rmeta, rid, d.g, d.zmin, d.ds, d.N, ground + o, ceil + o,
-                     IDS ? ag + o : nullptr, IDS ? ac + o : nullptr, cap);
+                     IDS ? ag + o : nullptr, IDS ? ac + o : nullptr, lds);
 }
 
 struct BatchWs {
@@ -1404,24 +1443,23 @@ pct_status launch_build(const float* xyz, int64_t n, const GridDev& g, float zmi
             PCT_LAUNCH_CHECK();
         }
     }
-    const int cap = reduce_cap(n, g);
-    const size_t rl = reduce_lds_bytes(g, N, ids, cap);
+    const unsigned rl = reduce_lds_bytes(n, g, N, ids);
     if (ids && merge) {
         if (pct_status st = allow_lds((const void*)k_tile_reduce<true, true>, rl)) return st;
         hipLaunchKernelGGL((k_tile_reduce<true, true>), dim3(g.ntiles), dim3(kReduceBlock), rl, s, w.off, w.rz, w.rmeta,
-                           w.rid, g, zmin, ds, N, ground, ceil, ag, ac, cap, id_base);
+                           w.rid, g, zmin, ds, N, ground, ceil, ag, ac, rl, id_base);
     } else if (merge) {
         if (pct_status st = allow_lds((const void*)k_tile_reduce<false, true>, rl)) return st;
         hipLaunchKernelGGL((k_tile_reduce<false, true>), dim3(g.ntiles), dim3(kReduceBlock), rl, s, w.off, w.rz, w.rmeta,
-                           w.rid, g, zmin, ds, N, ground, ceil, ag, ac, cap, id_base);
+                           w.rid, g, zmin, ds, N, ground, ceil, ag, ac, rl, id_base);
     } else if (ids) {
         if (pct_status st = allow_lds((const void*)k_tile_reduce<true, false>, rl)) return st;
         hipLaunchKernelGGL((k_tile_reduce<true, false>), dim3(g.ntiles), dim3(kReduceBlock), rl, s, w.off, w.rz, w.rmeta,
-                           w.rid, g, zmin, ds, N, ground, ceil, ag, ac, cap, 0);
+                           w.rid, g, zmin, ds, N, ground, ceil, ag, ac, rl, 0);
     } else {
         if (pct_status st = allow_lds((const void*)k_tile_reduce<false, false>, rl)) return st;
         hipLaunchKernelGGL((k_tile_reduce<false, false>), dim3(g.ntiles), dim3(kReduceBlock), rl, s, w.off, w.rz,
-                           w.rmeta, w.rid, g, zmin, ds, N, ground, ceil, ag, ac, cap, 0);
+                           w.rmeta, w.rid, g, zmin, ds, N, ground, ceil, ag, ac, rl, 0);
     }
     PCT_LAUNCH_CHECK();
     return PCT_OK;
@@ -1583,16 +1621,14 @@ pct_status launch_build_batched(const float* xyz, const BuildItemDev* h_items, i
         PCT_HIP(hipMemcpyAsync(w.items, h_items, sizeof(BuildItemDev) * n_items, hipMemcpyHostToDevice, s));
         PCT_HIP(hipStreamSynchronize(s));
     }
-    int max_tiles_lds = 0, max_staged = 0, cap = 0;
+    int max_tiles_lds = 0, max_staged = 0;
+    unsigned reduce_lds = 0;   // the largest of any item; the others get more slots
     for (int i = 0; i < n_items; ++i) {
         if (h_items[i].g.ntiles <= kMaxLdsTiles) max_tiles_lds = std::max(max_tiles_lds, h_items[i].g.ntiles);
         if (h_items[i].g.ntiles <= kMaxStaged) max_staged = std::max(max_staged, h_items[i].g.ntiles);
-        cap = std::max(cap, reduce_cap(h_items[i].n, h_items[i].g));
+        reduce_lds = std::max(reduce_lds, reduce_lds_bytes(h_items[i].n, h_items[i].g, h_items[i].N, ids));
     }
-    // the largest tile (tw x th cells) and plane count of any item size the bit matrix
-    size_t max_reduce_lds = 0;
-    for (int i = 0; i < n_items; ++i) max_reduce_lds = std::max(max_reduce_lds, reduce_lds_bytes(h_items[i].g, h_items[i].N, ids, cap));
-    if (pct_status st = allow_lds(ids ? (const void*)k_breduce<true> : (const void*)k_breduce<false>, max_reduce_lds))
+    if (pct_status st = allow_lds(ids ? (const void*)k_breduce<true> : (const void*)k_breduce<false>, reduce_lds))
         return st;
     hipLaunchKernelGGL(k_fill_u32, dim3(std::min(1024, w.total_tiles / kBlock + 1)), dim3(kBlock), 0, s, w.count,
                        (int64_t)w.total_tiles + 1, 0u);
@@ -1616,11 +1652,11 @@ pct_status launch_build_batched(const float* xyz, const BuildItemDev* h_items, i
     }
     if (w.total_tiles > 0) {
         if (ids)
-            hipLaunchKernelGGL(k_breduce<true>, dim3(w.total_tiles), dim3(kReduceBlock), max_reduce_lds, s, w.off, w.rz, w.rmeta,
-                               w.rid, w.items, n_items, ground, ceil, ag, ac, cap);
+            hipLaunchKernelGGL(k_breduce<true>, dim3(w.total_tiles), dim3(kReduceBlock), reduce_lds, s, w.off, w.rz, w.rmeta,
+                               w.rid, w.items, n_items, ground, ceil, ag, ac, reduce_lds);
         else
-            hipLaunchKernelGGL(k_breduce<false>, dim3(w.total_tiles), dim3(kReduceBlock), max_reduce_lds, s, w.off, w.rz,
-                               w.rmeta, w.rid, w.items, n_items, ground, ceil, ag, ac, cap);
+            hipLaunchKernelGGL(k_breduce<false>, dim3(w.total_tiles), dim3(kReduceBlock), reduce_lds, s, w.off, w.rz,
+                               w.rmeta, w.rid, w.items, n_items, ground, ceil, ag, ac, reduce_lds);
         PCT_LAUNCH_CHECK();
     }
     return PCT_OK;

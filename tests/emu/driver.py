@@ -366,6 +366,121 @@ def case_dense_tiles():
         check_batch(maps, pts, specs, [robot()], ids)
 
 
+def planes_scene(seed, nx, ny, n_planes, per_cell, dz=0.25, rows=None):
+    """Points uniform over a grid's cells (or its first `rows` rows) and over
+    the heights of exactly n_planes planes, some on planes and some in pairs
+    of equal heights."""
+    rng = np.random.default_rng(seed)
+    grid = dict(x0=0.0, y0=0.0, res=0.1, nx=nx, ny=ny, slice_dz=dz)
+    top = dz * (n_planes - 1) + 0.5 * dz
+    n = per_cell * nx * (rows or ny)
+    z = rng.uniform(0.0, top, n)
+    z[1::7] = z[0::7][:len(z[1::7])]
+    z[2::7] = np.floor(z[2::7] / dz) * dz
+    z[:2] = 0.0, top
+    pts = np.column_stack([rng.uniform(0.0, 0.1 * nx, n), rng.uniform(0.0, 0.1 * (rows or ny), n), z])
+    return scenes.Scene(pts.astype(np.float32), grid)
+
+
+def most_slots(sc, tw, th):
+    """The most occupied (cell, bin) pairs of any tile of tw x th cells: what
+    the tile reduce needs slots for when it takes all planes at once."""
+    p, g = sc.points, sc.grid
+    ix = np.floor(p[:, 0] / np.float32(g["res"])).astype(int).clip(0, g["nx"] - 1)
+    iy = np.floor(p[:, 1] / np.float32(g["res"])).astype(int).clip(0, g["ny"] - 1)
+    k = np.searchsorted(oracle.tomogram(p, g)["h"], p[:, 2])
+    occ = np.unique((iy * g["nx"] + ix) * 2048 + k) // 2048
+    tile = (occ // g["nx"]) // th * 1000 + occ % g["nx"] // tw
+    return int(np.unique(tile, return_counts=True)[1].max())
+
+
+def batch_build_case(maps, ids):
+    """The batched construction of maps equals the oracle's tomograms."""
+    specs, off = (abi.pct_item * len(maps))(), 0
+    for it, sc in zip(specs, maps):
+        it.xyz_offset, it.n_points, it.grid = off, len(sc.points), grid_s(sc.grid)
+        off += len(sc.points)
+    pts = np.ascontiguousarray(np.concatenate([sc.points for sc in maps]))
+    xb = Buf.of(pts)
+    tc, ts = C.c_int64(), C.c_int64()
+    ws = Buf(L.pct_batch_workspace_bytes(specs, len(maps), 1, int(ids)))
+    check("extent_batched", L.pct_tomogram_extent_batched(P(xb), len(pts), specs, len(maps), C.byref(tc), C.byref(ts),
+                                                          P(ws), ws.nbytes, None))
+    ws = Buf(L.pct_batch_workspace_bytes(specs, len(maps), 1, int(ids)))
+    out = [Buf(4 * tc.value) for _ in range(4 if ids else 2)]
+    check("build_batched", L.pct_build_tomogram_batched(P(xb), len(pts), specs, len(maps), *map(P, out),
+                                                        *(() if ids else (None, None)), 0, P(ws), ws.nbytes, None))
+    for it, sc in zip(specs, maps):
+        tm = oracle.tomogram(sc.points, sc.grid)
+        sl = slice(it.out_offset, it.out_offset + tm["ground"].size)
+        for buf, name in zip(out, ("ground", "ceil", "arg_ground", "arg_ceil")):
+            want = tm[name].ravel()
+            if want.dtype == np.int32:
+                want = np.where(want >= 0, want + it.xyz_offset, -1)
+            np.testing.assert_array_equal(bits(buf.get(tc.value, want.dtype)[sl]), bits(want))
+    say(f"batch of {len(maps)} maps of {[len(oracle.tomogram(sc.points, sc.grid)['h']) for sc in maps]} planes, "
+        f"ids={ids}: bit-exact")
+
+
+def case_plane_parts():
+    """Tiles whose occupied bins exceed the tile reduce's slots, and plane
+    counts around the parts that it takes them in (126 planes; 127 when one
+    part is all): single maps, a batch of them, and insertion."""
+    maps = []
+    for n_planes, per_cell, both in ((33, 40, True), (126, 4, False), (127, 24, True), (128, 24, False),
+                                     (129, 4, False), (379, 24, False)):
+        sc = planes_scene(n_planes, 130, 5, n_planes, per_cell)
+        if per_cell > 20:
+            assert most_slots(sc, 256, 2) > 8 * 512     # no launch has more slots for 512 cells
+        for ids in (True, False) if both else (True,):
+            e, _, _ = tomogram_case(sc.points, sc.grid, ids, f"{n_planes} planes, {per_cell} points a cell")
+            assert e.n_slices == n_planes
+        maps.append(sc)
+    batch_build_case([maps[0], maps[2], maps[5]], True)
+    batch_build_case([maps[1], maps[3]], False)
+    # insertion: half the points first, the others (all heights, every cell) added
+    for sc, ids in ((maps[2], False), (maps[5], True)):
+        g = grid_s(sc.grid)
+        first = np.ascontiguousarray(np.concatenate([sc.points[::2], sc.points[1:2]]))   # with the highest point
+        new = np.ascontiguousarray(sc.points[1::2])
+        xa, xb = Buf.of(first), Buf.of(new)
+        e = extent(xa, len(first), sc.grid)
+        G, Cc, aG, aC = build(xa, len(first), sc.grid, e, ids)
+        ws = Buf(L.pct_insert_workspace_bytes(len(new), C.byref(g)))
+        bb = (C.c_int32 * 4)()
+        check("insert", L.pct_tomogram_insert(P(xb), len(new), len(first), C.byref(g), C.byref(e), P(G), P(Cc),
+                                              P(aG), P(aC), bb, P(ws), ws.nbytes, None))
+        tm = oracle.tomogram(np.concatenate([first, new]), sc.grid)
+        shape = tm["ground"].shape
+        assert e.n_slices == shape[0]
+        np.testing.assert_array_equal(bits(G.get(shape, np.float32)), bits(tm["ground"]))
+        np.testing.assert_array_equal(bits(Cc.get(shape, np.float32)), bits(tm["ceil"]))
+        if ids:
+            np.testing.assert_array_equal(aG.get(shape, np.int32), tm["arg_ground"])
+            np.testing.assert_array_equal(aC.get(shape, np.int32), tm["arg_ceil"])
+        say(f"insert: {len(new)} points into {len(first)} under {e.n_slices} planes equal the union's tomogram")
+
+
+def case_tall_tiles():
+    """Construction tiles of 2048 cells (a batch tuned to eight rows), sparse
+    and with more occupied bins than slots, at plane counts whose bit matrix
+    alone would pass the LDS of a CU."""
+    import tempfile
+    maps = [planes_scene(71, 140, 8, 25, 60), planes_scene(72, 140, 9, 1000, 2), planes_scene(73, 140, 17, 520, 2)]
+    assert most_slots(maps[0], 256, 8) > 7680       # ids: what 160 KB hold beside 2048 cells' bits
+    path = os.path.join(tempfile.mkdtemp(), "tune.txt")
+    with open(path, "w") as fp:
+        for cls in sorted({tuple((sc.grid[k] - 1).bit_length() for k in ("nx", "ny")) for sc in maps}):
+            fp.write(f"cpu-emulator batch_build {cls[0]} {cls[1]} 8\n")
+    n_ap = C.c_int32()
+    check("reset", L.pct_autotune_reset())
+    check("autotune_load", L.pct_autotune_load(path.encode(), C.byref(n_ap)))
+    assert n_ap.value == 3
+    batch_build_case(maps, True)
+    batch_build_case(maps, False)
+    check("reset", L.pct_autotune_reset())
+
+
 def case_multirobot():
     sc = scenes.multistorey_scene(33, 4.3, 3.1, 60_000, n_floors=2)
     rs = [robot(), robot(d_min=0.7, theta_s=0.3), robot(d_inf=0.5, d_sm=0.7)]

@@ -405,3 +405,24 @@ def test_extent_on_device_matches_host(P):
     got = P.extent_from_bytes(rec)
     assert (got.z_min, got.z_max, got.n_slices, got.n_used) == (moved.z_min, moved.z_max, moved.n_slices, moved.n_used)
     del graph
+
+
+@pytest.mark.parametrize("nx,ny,planes,per_cell,rows", [
+    (300, 7, 127, 40, 7), (300, 7, 128, 40, 7), (61, 30, 1024, 60, 30),   # parts cut by the plane count and by the slots
+    (3, 16500, 260, 300, 8),                                              # tiles of 1024 cells
+    (3, 33000, 500, 500, 8), (33, 33000, 30, 90, 24)])                   # tiles of 2048 cells, sparse beside crowded
+@pytest.mark.parametrize("ids", [True, False])
+def test_build_many_planes_and_tall_tiles(P, oracle_lib, nx, ny, planes, per_cell, rows, ids):
+    """Maps whose tiles are taken in parts: more planes than a part holds, or
+    more occupied bins than the reduce has slots for."""
+    rng = np.random.default_rng(planes)
+    grid = dict(x0=0.0, y0=0.0, res=0.1, nx=nx, ny=ny, slice_dz=0.25)
+    n = per_cell * nx * rows
+    z = rng.uniform(0.0, 0.25 * (planes - 1) + 0.1, n)
+    z[1::7] = z[0::7][:len(z[1::7])]
+    z[2::7] = np.floor(z[2::7] * 4.0) / 4.0
+    z[:2] = 0.0, 0.25 * (planes - 1) + 0.1
+    pts = np.column_stack([rng.uniform(0.0, 0.1 * nx, n), rng.uniform(0.0, 0.1 * rows, n), z])
+    pts[-50:, 1] = rng.uniform(0.0, 0.1 * ny, 50)
+    ext, _, _ = check_tomogram(P, oracle_lib, pts.astype(np.float32), grid, ids)
+    assert ext.n_slices == planes
