@@ -696,7 +696,7 @@ pct_status make_items(const pct_item* h, int n_items, int64_t n_total, bool need
                       bool tuned = false) {
     if (n_items < 1 || !h) return fail(PCT_ERR_ARG, "a batch needs at least one item");
     out->resize(n_items);
-    int tile_base = 0, chunk_base = 0, echunk_base = 0;
+    int tile_base = 0, chunk_base = 0, echunk_base = 0, reduce_base = 0;
     for (int i = 0; i < n_items; ++i) {
         pct_status st = check_grid(&h[i].grid);
         char msg[512];
@@ -738,7 +738,9 @@ pct_status make_items(const pct_item* h, int n_items, int64_t n_total, bool need
         d.tile_base = tile_base;
         d.chunk_base = chunk_base;
         d.echunk_base = echunk_base;
+        d.reduce_base = reduce_base;
         tile_base += d.g.ntiles;
+        reduce_base += d.g.ntiles * reduce_windows(d.N);
         chunk_base += (int)((d.n + kBatchChunk - 1) / kBatchChunk);
         echunk_base += (int)std::max<int64_t>(1, (d.n + kBatchEChunk - 1) / kBatchEChunk);
     }

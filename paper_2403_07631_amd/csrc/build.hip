@@ -15,14 +15,15 @@ namespace pct {
 namespace {
 
 constexpr int kBlock = 256;
-// LDS slots of the tile reduce: at least kReduceCap and three per cell (a part
-// of one plane with the bins below and above it), at most kReduceBins per
-// cell of a tile, and no more than the LDS of a CU holds.
+// LDS of the tile reduce: slots for the occupied bins, at least kReduceCap
+// and three per cell, at most kReduceBins per cell, or what a launch too
+// small to fill the chip has for each workgroup.
 constexpr int kReduceCap = 2048;
 constexpr int kReduceBins = 8;
-constexpr int kReduceWords = 4;                         // words of bins per cell
-constexpr size_t kReduceLds = 160 * 1024 - 1024;        // of the tile reduce's dynamic LDS
+constexpr size_t kReduceLds = 160 * 1024;               // of a CU
+constexpr size_t kReduceStatic = 256;                   // at least the kernels' static LDS
 constexpr int kMaxTileCells = 256 * 8;
+constexpr int kCus = 256;
 
 __device__ __forceinline__ float wave_min(float v) {
     for (int m = 32; m >= 1; m >>= 1) v = fminf(v, __shfl_xor(v, m, 64));
@@ -668,13 +669,20 @@ __global__ __launch_bounds__(kBinBlock) void k_bin2_scatter_staged(const float* 
 // keep four workgroups on a CU (two with ids); six to ten measure alike, four
 // or five cut the building's tiles (+10 %).
 //
-// Planes are taken in parts of at most 126 (127 if one part is all), so that
-// the matrix has at most four words per cell whatever the plane count and
-// tile size; a part whose occupied bins exceed the slots is shortened until
-// they fit.  What lies below a part counts as one bin below its first, what
-// lies above as one past its last, so parts need nothing from one another.
+// Planes are taken in windows of at most 126 (127 if one window is all),
+// each by a workgroup of its own, so that the matrix has at most four words
+// per cell whatever the plane count and tile size, and a small map of many
+// planes spreads over the chip.  What lies below a window counts as one bin
+// below its first, what lies above as one past its last.  A window whose
+// occupied bins exceed the slots is walked in parts that fit; each part reads
+// the tile's records again and keeps what lies below and above it beside
+// the slots.  300 x 300 cells under 1001 planes, 60 points a cell: 5.6 ms with
+// one matrix of 32 words per cell, walked for every record's slot, and tiles
+// cut by cells (short rows of stores), 1.1 ms so; under 101 planes 0.71 and
+// 0.43 ms; 60 x 60 under 1001 planes, 10 a cell: 210 and 48 us.
 constexpr int kReduceBlock = 512;   // one cell per thread for the 512-cell tiles
 constexpr int kReduceKeep = 4;      // records per thread kept in registers between the passes
+constexpr int kReduceAhead = 2;     // other records per thread read together
 
 // Heights as integers of the same order (finite; -0 has become +0).
 __device__ __forceinline__ int height_key(float z) {
@@ -741,25 +749,30 @@ __device__ __forceinline__ void merge_vals(float og, float oc, int oi, int oj, f
     }
 }
 
-// One cell: walk the planes k_lo .. k_lo + P - 1 of a part over the cell's
-// occupied bins (bits of `mask`, words `stride` apart; plane k_lo is bit
-// `lead`, and with lead = 1 bit 0 is the bin of what lies below) and their
-// extremes smax, smin.  The next occupied bin's extremes are read ahead.
-// MERGE: combine with the stored values instead of overwriting them (ids
-// are offset by id_base); a cell without records is left as it is.
+// What lies below and above the planes that a cell walks.
+template <bool IDS>
+struct Beyond {
+    float gz, cz;
+    int gi, ci;
+};
+
+// One cell: walk P planes from plane k_lo over the cell's occupied bins
+// (bits q0 .. q0 + P - 1 of `mask`, words `stride` apart) and their extremes
+// smax, smin; `far` is the ground before them and the ceiling after them.
+// The next occupied bin's extremes are read ahead.  MERGE: combine with the
+// stored values instead of overwriting them (ids are offset by id_base).
 template <bool IDS, bool MERGE>
-__device__ __forceinline__ void sweep_cell(const unsigned* mask, int stride,
+__device__ __forceinline__ void sweep_cell(const unsigned* mask, int stride, int q0,
                                            const typename SlotKeys<IDS>::T* smax,
-                                           const typename SlotKeys<IDS>::T* smin, int n, int ix, int iy,
-                                           const GridDev& g, int lead, int k_lo, int P, float* __restrict__ ground,
+                                           const typename SlotKeys<IDS>::T* smin, int n, Beyond<IDS> far, int ix,
+                                           int iy, const GridDev& g, int k_lo, int P, float* __restrict__ ground,
                                            float* __restrict__ ceil, int* __restrict__ ag, int* __restrict__ ac,
                                            int id_base) {
     typedef SlotKeys<IDS> S;
-    if (MERGE && n == 0) return;
     const int64_t plane = (int64_t)g.nx * g.ny;
     int64_t o = (int64_t)k_lo * plane + (int64_t)iy * g.nx + ix;
-    float gz = -INFINITY, cz = INFINITY, nextz = -INFINITY;
-    int gi = -1, ci = -1, nexti = -1;
+    float gz = far.gz, cz = far.cz, nextz = -INFINITY;
+    int gi = far.gi, ci = far.ci, nexti = -1;
     int j = 0;
     auto read_next = [&]() {
         if (j < n) {
@@ -771,29 +784,22 @@ __device__ __forceinline__ void sweep_cell(const unsigned* mask, int stride,
                 ci = S::min_id(lo) + id_base;
             }
         } else {
-            cz = INFINITY;
-            ci = -1;
+            cz = far.cz;
+            ci = far.ci;
         }
     };
     read_next();
-    unsigned bits = mask[0];
-    auto take = [&]() {
-        gz = nextz;
-        gi = nexti;
-        ++j;
-        read_next();
-    };
-    if (lead && (bits & 1u)) take();
+    unsigned bits = mask[(q0 >> 5) * stride];
     // MERGE reads the stored values of kAhead planes before it writes
     // any of them, so that their loads overlap
     constexpr int kAhead = MERGE ? 8 : 1;
-    for (int q0 = lead; q0 < lead + P; q0 += kAhead) {
+    for (int k0 = 0; k0 < P; k0 += kAhead) {
         float og[kAhead], oc[kAhead];
         int oi[kAhead], oj[kAhead];
         if (MERGE) {
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
-                if (q0 + u >= lead + P) break;
+                if (k0 + u >= P) break;
                 const int64_t i = o + u * plane;
                 og[u] = ground[i];
                 oc[u] = ceil[i];
@@ -803,10 +809,15 @@ __device__ __forceinline__ void sweep_cell(const unsigned* mask, int stride,
         }
 #pragma unroll
         for (int u = 0; u < kAhead; ++u, o += plane) {
-            const int q = q0 + u;
-            if (q >= lead + P) break;
+            const int k = k0 + u, q = q0 + k;
+            if (k >= P) break;
             if ((q & 31) == 0) bits = mask[(q >> 5) * stride];
-            if ((bits >> (q & 31)) & 1u) take();
+            if ((bits >> (q & 31)) & 1u) {
+                gz = nextz;
+                gi = nexti;
+                ++j;
+                read_next();
+            }
             float vg = gz, vc = cz;
             int wg = gi, wc = ci;
             if (MERGE) merge_vals(og[u], oc[u], oi[u], oj[u], vg, wg, vc, wc);
@@ -827,17 +838,19 @@ __host__ __device__ inline int reduce_words(int N) { return N / 32 + 1 < kReduce
 __host__ __device__ inline unsigned reduce_fixed_bytes(int cells, int N) {
     return (unsigned)sizeof(unsigned) * (unsigned)(reduce_words(N) * cells + cells + 1);
 }
-static_assert(sizeof(unsigned) * ((kReduceWords + 1) * kMaxTileCells + 1) + 16 * 3 * kMaxTileCells <= kReduceLds,
-              "three slots per cell fit beside the largest bit matrix");
+static_assert(sizeof(unsigned) * ((kReduceWords + 1) * kMaxTileCells + 1) + 16 * 3 * kMaxTileCells + kReduceStatic <=
+                  kReduceLds, "three slots per cell fit beside the largest bit matrix");
 
-// One construction tile: records off[tg] .. off[tg+1] of the tile whose
-// position in its grid is tl.  Shared by the single-map and batched kernels.
-// lds: bytes of dynamic LDS, at least three slots per cell beside the rest.
+// One construction tile and window of planes: records off[tg] .. off[tg+1]
+// of the tile whose position in its grid is tl.  Shared by the single-map
+// and batched kernels.  lds: bytes of dynamic LDS, at least three slots per
+// cell beside the rest.
 template <bool IDS, bool MERGE = false>
-__device__ void reduce_tile(int tg, int tl, const unsigned* __restrict__ off, const float* __restrict__ rz,
-                            const unsigned* __restrict__ rmeta, const int* __restrict__ rid, const GridDev& g,
-                            float zmin, float ds, int N, float* __restrict__ ground, float* __restrict__ ceil,
-                            int* __restrict__ ag, int* __restrict__ ac, unsigned lds, int id_base = 0) {
+__device__ void reduce_tile(int tg, int tl, int window, const unsigned* __restrict__ off,
+                            const float* __restrict__ rz, const unsigned* __restrict__ rmeta,
+                            const int* __restrict__ rid, const GridDev& g, float zmin, float ds, int N,
+                            float* __restrict__ ground, float* __restrict__ ceil, int* __restrict__ ag,
+                            int* __restrict__ ac, unsigned lds, int id_base = 0) {
     typedef SlotKeys<IDS> S;
     extern __shared__ unsigned s_mem[];
     const int cells = g.tw * g.th;
@@ -852,12 +865,28 @@ __device__ void reduce_tile(int tg, int tl, const unsigned* __restrict__ off, co
     const int tx = tl % g.ntx, ty = tl / g.ntx;
     const unsigned r0 = off[tg], r1 = off[tg + 1];
     if (MERGE && r0 == r1) return;   // an insertion leaves tiles without new points alone
+    // the window's planes p0 .. p1 - 1 are bits lead .. of a cell
+    const int windows = reduce_windows(N), even = (N + windows - 1) / windows;
+    const int p0 = window * even, p1 = min(N, p0 + even), lead = p0 > 0 ? 1 : 0;
+    const int end = lead + p1 - p0;                // bit of what lies above
+    if (p0 >= p1) return;
 
     const float inv_ds = 1.0f / ds;
-    // a thread's first kReduceKeep records stay in registers
-    unsigned kc[kReduceKeep];   // cell | bin << 16; ~0: no record
+    for (int i = threadIdx.x; i < W * cells; i += kReduceBlock) s_bits[i] = 0u;
+    __syncthreads();
+    // occupied bins; a thread's first kReduceKeep records stay in registers
+    unsigned kc[kReduceKeep];   // cell | bit << 16; ~0: no record
     float kz[kReduceKeep];
     int ki[kReduceKeep];
+    auto bit_of = [&](float z) -> unsigned {
+        const int b = plane_bin(z, zmin, ds, inv_ds, N);
+        return b < p0 ? 0u : (unsigned)(min(b, p1) - p0 + lead);
+    };
+    auto mark = [&](unsigned c, float z) -> unsigned {
+        const unsigned q = bit_of(z);
+        atomicOr(&s_bits[(q >> 5) * cells + c], 1u << (q & 31));
+        return q;
+    };
 #pragma unroll
     for (int q = 0; q < kReduceKeep; ++q) {
         const unsigned r = r0 + q * kReduceBlock + threadIdx.x;
@@ -868,100 +897,163 @@ __device__ void reduce_tile(int tg, int tl, const unsigned* __restrict__ off, co
     }
 #pragma unroll
     for (int q = 0; q < kReduceKeep; ++q)
-        if (kc[q] != ~0u) kc[q] |= (unsigned)plane_bin(kz[q], zmin, ds, inv_ds, N) << 16;
+        if (kc[q] != ~0u) kc[q] |= mark(kc[q], kz[q]) << 16;
+    // the others, kReduceAhead at a time so that their loads overlap
     const unsigned r2 = r0 + kReduceKeep * kReduceBlock;
-    const int parts = N < 32 * kReduceWords ? 1 : (N + 32 * kReduceWords - 3) / (32 * kReduceWords - 2);
-    const int even = (N + parts - 1) / parts;
-
-    for (int k_lo = 0; k_lo < N;) {
-        const int lead = k_lo > 0 ? 1 : 0;
-        int P = min(even, N - k_lo);
-        auto place = [&](unsigned b) -> unsigned {   // bit of bin b in this part
-            return (int)b < k_lo ? 0u : (unsigned)(min((int)b - k_lo, P) + lead);
-        };
-        for (int i = threadIdx.x; i < W * cells; i += kReduceBlock) s_bits[i] = 0u;
-        __syncthreads();
-        auto mark = [&](unsigned c, unsigned b) {
-            const unsigned q = place(b);
-            atomicOr(&s_bits[(q >> 5) * cells + c], 1u << (q & 31));
-        };
+    auto others = [&](auto f) {
+        for (unsigned r = r2 + threadIdx.x; r < r1; r += kReduceAhead * kReduceBlock) {
+            unsigned c[kReduceAhead];
+            float z[kReduceAhead];
 #pragma unroll
-        for (int q = 0; q < kReduceKeep; ++q)
-            if (kc[q] != ~0u) mark(kc[q] & 0xffffu, kc[q] >> 16);
-        for (unsigned r = r2 + threadIdx.x; r < r1; r += kReduceBlock)
-            mark(rmeta[r], (unsigned)plane_bin(rz[r], zmin, ds, inv_ds, N));
-        __syncthreads();
-        // slots: thread i owns a contiguous run of cells; bins from bit
-        // lead + P on share the last slot
-        const int per = (cells + kReduceBlock - 1) / kReduceBlock;
-        const int cb = min((int)threadIdx.x * per, cells), ce = min(cb + per, cells);
-        const int marked = P;
-        auto slots_of = [&](int c) -> unsigned {
-            const int tw = (lead + P) >> 5;
-            const unsigned low = (1u << ((lead + P) & 31)) - 1u;
-            unsigned n = 0u, past = 0u;
-            for (int w = 0; w < W; ++w) {
-                const unsigned v = s_bits[w * cells + c];
-                const unsigned in = w < tw ? v : (w == tw ? v & low : 0u);
-                n += (unsigned)__popc(in);
-                past |= v & ~in;
+            for (int u = 0; u < kReduceAhead; ++u) {
+                const unsigned i = r + u * kReduceBlock;
+                c[u] = i < r1 ? rmeta[i] : ~0u;
+                z[u] = i < r1 ? rz[i] : 0.0f;
             }
-            return n + (past != 0u ? 1u : 0u);
-        };
-        unsigned run, total;
-        for (;;) {
-            unsigned sum = 0;
-            for (int c = cb; c < ce; ++c) sum += slots_of(c);
-            run = block_scan_excl(sum, s_w, total);
-            if (total <= (unsigned)CAP) break;
-            // the planes' share of the slots, in proportion; CAP / cells - 2
-            // planes always fit, so this ends
-            const int share = (int)((long long)P * (CAP - 2 * cells) / ((int)total - 2 * cells));
-            P = max(CAP / cells - 2, min(P - 1, share));
+#pragma unroll
+            for (int u = 0; u < kReduceAhead; ++u)
+                if (c[u] != ~0u) f(c[u], z[u], r + u * kReduceBlock);
         }
+    };
+    others([&](unsigned c, float z, unsigned) { mark(c, z); });
+    __syncthreads();
+
+    // slots: thread i owns a contiguous run of cells
+    const int per = (cells + kReduceBlock - 1) / kReduceBlock;
+    const int cb = min((int)threadIdx.x * per, cells), ce = min(cb + per, cells);
+    unsigned total;
+    {
+        unsigned sum = 0;
+        for (int c = cb; c < ce; ++c)
+            for (int w = 0; w < W; ++w) sum += (unsigned)__popc(s_bits[w * cells + c]);
+        unsigned run = block_scan_excl(sum, s_w, total);
         for (int c = cb; c < ce; ++c) {
             s_base[c] = run;
-            run += slots_of(c);
-            if (P < marked) {
-                const int top = lead + P, tw = top >> 5;
-                const unsigned low = (1u << (top & 31)) - 1u;
-                unsigned past = s_bits[tw * cells + c] & ~low;
-                for (int w = tw + 1; w < W; ++w) past |= s_bits[w * cells + c];
-                s_bits[tw * cells + c] = (s_bits[tw * cells + c] & low) | (past != 0u ? 1u << (top & 31) : 0u);
-            }
+            for (int w = 0; w < W; ++w) run += (unsigned)__popc(s_bits[w * cells + c]);
         }
         if (threadIdx.x == 0) s_base[cells] = total;
+    }
+    if (total <= (unsigned)CAP) {   // the whole window at once; what lies below and above has slots like the others
         for (int i = threadIdx.x; i < (int)total; i += kReduceBlock) {
             s_max[i] = S::none_max();
             s_min[i] = S::none_min();
         }
         __syncthreads();
-        auto put = [&](unsigned c, unsigned b, float z, int id) {
-            const unsigned q = place(b), w = q >> 5;
+        auto put = [&](unsigned c, unsigned q, float z, int id) {
             unsigned slot = s_base[c];
+            const unsigned w = q >> 5;
             for (unsigned v = 0; v < w; ++v) slot += (unsigned)__popc(s_bits[v * cells + c]);
             slot += (unsigned)__popc(s_bits[w * cells + c] & ((1u << (q & 31)) - 1u));
+            // of what lies below only the maximum counts, above the minimum
+            if ((int)q < end) atomicMax(&s_max[slot], S::max_key(z, id));
+            if ((int)q >= lead) atomicMin(&s_min[slot], S::min_key(z, id));
+        };
+#pragma unroll
+        for (int q = 0; q < kReduceKeep; ++q)
+            if (kc[q] != ~0u) put(kc[q] & 0xffffu, kc[q] >> 16, kz[q], ki[q]);
+        others([&](unsigned c, float z, unsigned r) { put(c, bit_of(z), z, IDS ? rid[r] : 0); });
+        __syncthreads();
+        for (int c = threadIdx.x; c < cells; c += kReduceBlock) {
+            const int ix = tx * g.tw + (c % g.tw);
+            const int iy = ty * g.th + c / g.tw;
+            if (ix >= g.nx || iy >= g.ny) continue;
+            unsigned s = s_base[c];
+            int n = (int)(s_base[c + 1] - s);
+            if (MERGE && n == 0) continue;   // a cell without records stays as it is
+            Beyond<IDS> far{-INFINITY, INFINITY, -1, -1};
+            if (lead && (s_bits[c] & 1u)) {
+                far.gz = S::height(s_max[s]);
+                if (IDS) far.gi = S::max_id(s_max[s]) + id_base;
+                ++s;
+                --n;
+            }
+            sweep_cell<IDS, MERGE>(s_bits + c, cells, lead, s_max + s, s_min + s, n, far, ix, iy, g, p0, p1 - p0,
+                                   ground, ceil, ag, ac, id_base);
+        }
+        return;
+    }
+
+    // Parts of the window: the slots' first `cells` take what lies below the
+    // part (maxima) and above it (minima), the others its occupied bins.
+    const int room = CAP - cells;
+    const unsigned whole = total;
+    auto in_part = [&](int w, int qa, int qb) -> unsigned {   // bits qa .. qb - 1 in word w
+        const int a = qa - 32 * w, b = qb - 32 * w;
+        const unsigned lo = a <= 0 ? ~0u : (a >= 32 ? 0u : ~0u << a);
+        const unsigned hi = b <= 0 ? 0u : (b >= 32 ? ~0u : ~(~0u << b));
+        return lo & hi;
+    };
+    for (int qa = lead; qa < end;) {
+        int P = min(end - qa, max(1, (int)((long long)(p1 - p0) * room / (int)whole)));
+        unsigned run;
+        for (;;) {
+            unsigned sum = 0;
+            for (int w = qa >> 5; w <= (qa + P - 1) >> 5; ++w) {
+                const unsigned m = in_part(w, qa, qa + P);
+                for (int c = cb; c < ce; ++c) sum += (unsigned)__popc(s_bits[w * cells + c] & m);
+            }
+            __syncthreads();   // the part before is done with its slots (and s_base)
+            run = block_scan_excl(sum, s_w, total);
+            if (total <= (unsigned)room) break;
+            // a plane has at most `cells` bins, which fit, so this ends
+            P = max(1, min(P - 1, (int)((long long)P * room / (int)total)));
+        }
+        const int qb = qa + P;
+        for (int c = cb; c < ce; ++c) {
+            s_base[c] = run;
+            for (int w = qa >> 5; w <= (qb - 1) >> 5; ++w)
+                run += (unsigned)__popc(s_bits[w * cells + c] & in_part(w, qa, qb));
+        }
+        if (threadIdx.x == 0) s_base[cells] = total;
+        for (int i = threadIdx.x; i < cells + (int)total; i += kReduceBlock) {
+            s_max[i] = S::none_max();
+            s_min[i] = S::none_min();
+        }
+        __syncthreads();
+        auto put = [&](unsigned c, unsigned bit, float z, int id) {
+            const int q = (int)bit;
+            if (q < qa) {
+                // mostly lower than what is there: look before the atomic
+                const typename S::T k = S::max_key(z, id);
+                if (k > *(volatile typename S::T*)&s_max[c]) atomicMax(&s_max[c], k);
+                return;
+            }
+            if (q >= qb) {
+                const typename S::T k = S::min_key(z, id);
+                if (k < *(volatile typename S::T*)&s_min[c]) atomicMin(&s_min[c], k);
+                return;
+            }
+            unsigned slot = (unsigned)cells + s_base[c];
+            for (int v = qa >> 5; v <= q >> 5; ++v) slot += (unsigned)__popc(s_bits[v * cells + c] & in_part(v, qa, q));
             atomicMax(&s_max[slot], S::max_key(z, id));
             atomicMin(&s_min[slot], S::min_key(z, id));
         };
 #pragma unroll
         for (int q = 0; q < kReduceKeep; ++q)
             if (kc[q] != ~0u) put(kc[q] & 0xffffu, kc[q] >> 16, kz[q], ki[q]);
-        for (unsigned r = r2 + threadIdx.x; r < r1; r += kReduceBlock) {
-            const float z = rz[r];
-            put(rmeta[r], (unsigned)plane_bin(z, zmin, ds, inv_ds, N), z, IDS ? rid[r] : 0);
-        }
+        others([&](unsigned c, float z, unsigned r) { put(c, bit_of(z), z, IDS ? rid[r] : 0); });
         __syncthreads();
         for (int c = threadIdx.x; c < cells; c += kReduceBlock) {
             const int ix = tx * g.tw + (c % g.tw);
             const int iy = ty * g.th + c / g.tw;
             if (ix >= g.nx || iy >= g.ny) continue;
             const unsigned s = s_base[c];
-            sweep_cell<IDS, MERGE>(s_bits + c, cells, s_max + s, s_min + s, (int)(s_base[c + 1] - s), ix, iy, g, lead,
-                                   k_lo, P, ground, ceil, ag, ac, id_base);
+            const int n = (int)(s_base[c + 1] - s);
+            const bool below = s_max[c] != S::none_max(), above = s_min[c] != S::none_min();
+            if (MERGE && n == 0 && !below && !above) continue;
+            Beyond<IDS> far{-INFINITY, INFINITY, -1, -1};
+            if (below) {
+                far.gz = S::height(s_max[c]);
+                if (IDS) far.gi = S::max_id(s_max[c]) + id_base;
+            }
+            if (above) {
+                far.cz = S::height(s_min[c]);
+                if (IDS) far.ci = S::min_id(s_min[c]) + id_base;
+            }
+            sweep_cell<IDS, MERGE>(s_bits + c, cells, qa, s_max + cells + s, s_min + cells + s, n, far, ix, iy, g,
+                                   p0 + qa - lead, P, ground, ceil, ag, ac, id_base);
         }
-        k_lo += P;
-        if (k_lo < N) __syncthreads();   // the next part clears the bits
+        qa = qb;
     }
 }
 
@@ -973,21 +1065,25 @@ __global__ __launch_bounds__(kReduceBlock, MERGE || IDS ? 4 : 8) void k_tile_red
                                                         float ds, int N, float* __restrict__ ground,
                                                         float* __restrict__ ceil, int* __restrict__ ag,
                                                         int* __restrict__ ac, unsigned lds, int id_base) {
-    reduce_tile<IDS, MERGE>((int)blockIdx.x, (int)blockIdx.x, off, rz, rmeta, rid, g, zmin, ds, N, ground, ceil, ag,
+    const int windows = reduce_windows(N), t = (int)blockIdx.x / windows;
+    reduce_tile<IDS, MERGE>(t, t, (int)blockIdx.x - t * windows, off, rz, rmeta, rid, g, zmin, ds, N, ground, ceil, ag,
                             ac, lds, id_base);
 }
 
 // Dynamic LDS of a tile's reduce: slots for 1.25x the mean records per tile
 // (rounded up to 1024), which a tile's occupied bins seldom exceed, at most
-// kReduceBins bins per cell (storeyed scenes occupy two or three bins per
-// surface), within the LDS of a CU.
-inline unsigned reduce_lds_bytes(int64_t n, const GridDev& g, int N, bool ids) {
+// kReduceBins per cell (storeyed scenes occupy two or three bins per
+// surface), or more where a launch of `groups` workgroups has the LDS of the
+// CUs to itself, and no more than a CU holds.
+inline unsigned reduce_lds_bytes(int64_t n, const GridDev& g, int N, bool ids, int64_t groups) {
     const int64_t cells = (int64_t)g.tw * g.th, slot = ids ? 16 : 8, fixed = reduce_fixed_bytes((int)cells, N);
     const int64_t mean = g.ntiles > 0 ? n / g.ntiles : 0;
-    const int64_t want = (mean + mean / 4 + 1023) / 1024 * 1024;
-    int64_t cap = std::min<int64_t>(kReduceBins * cells, std::max<int64_t>(kReduceCap, want));
-    cap = std::min<int64_t>(cap, ((int64_t)kReduceLds - fixed) / slot);
-    return (unsigned)(fixed + slot * std::max<int64_t>(cap, 3 * cells));
+    const int64_t want = std::max<int64_t>(kReduceCap, (mean + mean / 4 + 1023) / 1024 * 1024);
+    auto fits = [&](int64_t per_cu) { return ((int64_t)kReduceLds / per_cu - (int64_t)kReduceStatic - fixed) / slot; };
+    int64_t cap = kReduceBins * cells;
+    if (groups <= 4 * kCus) cap = std::max(cap, fits(std::max<int64_t>(1, (groups + kCus - 1) / kCus)));
+    cap = std::min(std::min(cap, want), fits(1));
+    return (unsigned)(fixed + slot * std::max<int64_t>(cap, std::max<int64_t>(kReduceCap, 3 * cells)));
 }
 
 // Kernels may take more than 64 KB of LDS only once asked for.
@@ -1056,7 +1152,7 @@ __device__ __forceinline__ int find_base(const BuildItemDev* __restrict__ items,
     int lo = 0, hi = n_items - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) / 2;
-        const int b = which == 0 ? items[mid].chunk_base : (which == 1 ? items[mid].tile_base : items[mid].echunk_base);
+        const int b = which == 0 ? items[mid].chunk_base : (which == 1 ? items[mid].reduce_base : items[mid].echunk_base);
         if (b <= v) lo = mid;
         else hi = mid - 1;
     }
@@ -1253,12 +1349,12 @@ __global__ __launch_bounds__(kReduceBlock, IDS ? 4 : 8) void k_breduce(const uns
                                                     const BuildItemDev* __restrict__ items, int n_items,
                                                     float* __restrict__ ground, float* __restrict__ ceil,
                                                     int* __restrict__ ag, int* __restrict__ ac, unsigned lds) {
-    const int tg = blockIdx.x;
-    const int it = find_base(items, n_items, tg, 1);
+    const int it = find_base(items, n_items, (int)blockIdx.x, 1);
     const BuildItemDev& d = items[it];
     if (d.N <= 0) return;
     const long long o = d.out_off;
-    reduce_tile<IDS>(tg, tg - d.tile_base, off, rz, rmeta, rid, d.g, d.zmin, d.ds, d.N, ground + o, ceil + o,
+    const int windows = reduce_windows(d.N), q = (int)blockIdx.x - d.reduce_base, tl = q / windows;
+    reduce_tile<IDS>(d.tile_base + tl, tl, q - tl * windows, off, rz, rmeta, rid, d.g, d.zmin, d.ds, d.N, ground + o, ceil + o,
                      IDS ? ag + o : nullptr, IDS ? ac + o : nullptr, lds);
 }
 
@@ -1443,22 +1539,23 @@ pct_status launch_build(const float* xyz, int64_t n, const GridDev& g, float zmi
             PCT_LAUNCH_CHECK();
         }
     }
-    const unsigned rl = reduce_lds_bytes(n, g, N, ids);
+    const unsigned groups = (unsigned)(g.ntiles * reduce_windows(N));
+    const unsigned rl = reduce_lds_bytes(n, g, N, ids, groups);
     if (ids && merge) {
         if (pct_status st = allow_lds((const void*)k_tile_reduce<true, true>, rl)) return st;
-        hipLaunchKernelGGL((k_tile_reduce<true, true>), dim3(g.ntiles), dim3(kReduceBlock), rl, s, w.off, w.rz, w.rmeta,
+        hipLaunchKernelGGL((k_tile_reduce<true, true>), dim3(groups), dim3(kReduceBlock), rl, s, w.off, w.rz, w.rmeta,
                            w.rid, g, zmin, ds, N, ground, ceil, ag, ac, rl, id_base);
     } else if (merge) {
         if (pct_status st = allow_lds((const void*)k_tile_reduce<false, true>, rl)) return st;
-        hipLaunchKernelGGL((k_tile_reduce<false, true>), dim3(g.ntiles), dim3(kReduceBlock), rl, s, w.off, w.rz, w.rmeta,
+        hipLaunchKernelGGL((k_tile_reduce<false, true>), dim3(groups), dim3(kReduceBlock), rl, s, w.off, w.rz, w.rmeta,
                            w.rid, g, zmin, ds, N, ground, ceil, ag, ac, rl, id_base);
     } else if (ids) {
         if (pct_status st = allow_lds((const void*)k_tile_reduce<true, false>, rl)) return st;
-        hipLaunchKernelGGL((k_tile_reduce<true, false>), dim3(g.ntiles), dim3(kReduceBlock), rl, s, w.off, w.rz, w.rmeta,
+        hipLaunchKernelGGL((k_tile_reduce<true, false>), dim3(groups), dim3(kReduceBlock), rl, s, w.off, w.rz, w.rmeta,
                            w.rid, g, zmin, ds, N, ground, ceil, ag, ac, rl, 0);
     } else {
         if (pct_status st = allow_lds((const void*)k_tile_reduce<false, false>, rl)) return st;
-        hipLaunchKernelGGL((k_tile_reduce<false, false>), dim3(g.ntiles), dim3(kReduceBlock), rl, s, w.off, w.rz,
+        hipLaunchKernelGGL((k_tile_reduce<false, false>), dim3(groups), dim3(kReduceBlock), rl, s, w.off, w.rz,
                            w.rmeta, w.rid, g, zmin, ds, N, ground, ceil, ag, ac, rl, 0);
     }
     PCT_LAUNCH_CHECK();
@@ -1612,7 +1709,7 @@ pct_status launch_build_batched(const float* xyz, const BuildItemDev* h_items, i
         const BuildItemDev& d = h_items[i];
         dg.add(d.g.x0), dg.add(d.g.y0), dg.add(d.g.res), dg.add(d.g.nx), dg.add(d.g.ny), dg.add(d.g.th), dg.add(d.g.tw);
         dg.add(d.g.ntiles), dg.add(d.xyz_off), dg.add(d.n), dg.add(d.zmin), dg.add(d.ds), dg.add(d.N);
-        dg.add(d.out_off), dg.add(d.tile_base), dg.add(d.chunk_base), dg.add(d.echunk_base);
+        dg.add(d.out_off), dg.add(d.tile_base), dg.add(d.chunk_base), dg.add(d.echunk_base), dg.add(d.reduce_base);
     }
     if (pct_status st = resident_tables(w.items, 0, dg.h, upload != 0)) return st;
     if (upload) {
@@ -1626,8 +1723,11 @@ pct_status launch_build_batched(const float* xyz, const BuildItemDev* h_items, i
     for (int i = 0; i < n_items; ++i) {
         if (h_items[i].g.ntiles <= kMaxLdsTiles) max_tiles_lds = std::max(max_tiles_lds, h_items[i].g.ntiles);
         if (h_items[i].g.ntiles <= kMaxStaged) max_staged = std::max(max_staged, h_items[i].g.ntiles);
-        reduce_lds = std::max(reduce_lds, reduce_lds_bytes(h_items[i].n, h_items[i].g, h_items[i].N, ids));
     }
+    int groups = 0;
+    for (int i = 0; i < n_items; ++i) groups += h_items[i].g.ntiles * reduce_windows(h_items[i].N);
+    for (int i = 0; i < n_items; ++i)
+        reduce_lds = std::max(reduce_lds, reduce_lds_bytes(h_items[i].n, h_items[i].g, h_items[i].N, ids, groups));
     if (pct_status st = allow_lds(ids ? (const void*)k_breduce<true> : (const void*)k_breduce<false>, reduce_lds))
         return st;
     hipLaunchKernelGGL(k_fill_u32, dim3(std::min(1024, w.total_tiles / kBlock + 1)), dim3(kBlock), 0, s, w.count,
@@ -1652,10 +1752,10 @@ pct_status launch_build_batched(const float* xyz, const BuildItemDev* h_items, i
     }
     if (w.total_tiles > 0) {
         if (ids)
-            hipLaunchKernelGGL(k_breduce<true>, dim3(w.total_tiles), dim3(kReduceBlock), reduce_lds, s, w.off, w.rz, w.rmeta,
+            hipLaunchKernelGGL(k_breduce<true>, dim3(groups), dim3(kReduceBlock), reduce_lds, s, w.off, w.rz, w.rmeta,
                                w.rid, w.items, n_items, ground, ceil, ag, ac, reduce_lds);
         else
-            hipLaunchKernelGGL(k_breduce<false>, dim3(w.total_tiles), dim3(kReduceBlock), reduce_lds, s, w.off, w.rz,
+            hipLaunchKernelGGL(k_breduce<false>, dim3(groups), dim3(kReduceBlock), reduce_lds, s, w.off, w.rz,
                                w.rmeta, w.rid, w.items, n_items, ground, ceil, ag, ac, reduce_lds);
         PCT_LAUNCH_CHECK();
     }

@@ -114,7 +114,16 @@ struct BuildItemDev {
     int tile_base;          // first global construction tile
     int chunk_base;         // first global binning chunk
     int echunk_base;        // first global extent chunk
+    int reduce_base;        // first workgroup of the tile reduce
 };
+
+// The tile reduce takes the planes in windows, one workgroup per tile and
+// window: the occupied bins of at most kReduceWords words per cell (its
+// planes, and in windows after the first the bin of what lies below).
+constexpr int kReduceWords = 4;
+__host__ __device__ inline int reduce_windows(int N) {
+    return N < 32 * kReduceWords ? 1 : (N + 32 * kReduceWords - 3) / (32 * kReduceWords - 2);
+}
 
 constexpr int kBatchChunk = 4096;     // points per workgroup in batched binning
 constexpr int kBatchEChunk = 65536;   // points per workgroup in batched extents
