@@ -1277,11 +1277,14 @@ __global__ __launch_bounds__(kBinBlock) void k_bcount(const float* __restrict__ 
             if (s_cnt[t]) atomicAdd(&gcount[d.tile_base + t], s_cnt[t]);
 }
 
-// Scatter of a chunk into its item's tiles: one global atomic per touched
-// tile reserves the chunk's run, then a staged scatter (items of at most
-// kMaxStaged tiles), else each record goes out by itself.  108 M points of
-// 512 submaps: 3.46 ms with records written in the order of the points, 0.70
-// ms staged.
+// Scatter of a chunk into its item's tiles: LDS counts rank the chunk's
+// records in their tiles, one global atomic per touched tile reserves its
+// run, then a staged scatter (items of at most kMaxStaged tiles), else the
+// records go out in their own order; items of more than kMaxLdsTiles tiles
+// reserve record by record.  108 M points of 512 submaps: 3.46 ms with
+// records written in the order of the points, 0.70 ms staged.  48 M points on
+// eight maps of 2000 tiles, construction: 4.8 ms reserved record by record,
+// 1.7 ms by counts.
 template <bool IDS>
 __global__ __launch_bounds__(kBinBlock) void k_bscatter(const float* __restrict__ xyz,
                                                         const BuildItemDev* __restrict__ items, int n_items,
@@ -1296,9 +1299,10 @@ __global__ __launch_bounds__(kBinBlock) void k_bscatter(const float* __restrict_
     const float* p = xyz + 3 * d.xyz_off;
     const bool vec = aligned16(p);
     const int64_t q0 = (int64_t)(c - d.chunk_base) * (kBatchChunk / 4);
-    if (B <= kMaxStaged) {
+    if (B <= kMaxLdsTiles) {
+        const bool staged = B <= kMaxStaged;
         unsigned* s_cnt = s_mem;
-        unsigned* s_gb = s_cnt + 2 * B + 1;
+        unsigned* s_gb = staged ? s_cnt + 2 * B + 1 : s_cnt;   // the runs' places; over the counts if not staged
         for (int t = threadIdx.x; t < B; t += kBinBlock) s_cnt[t] = 0;
         __syncthreads();
         float z[kBinPPT];
@@ -1328,7 +1332,18 @@ __global__ __launch_bounds__(kBinBlock) void k_bscatter(const float* __restrict_
             s_gb[t] = k ? atomicAdd(&cursor[d.tile_base + t], k) : 0u;
         }
         __syncthreads();
-        staged_write<IDS>(s_mem, B, d.g.ltw + d.g.lth, z, key, id, bk, rank, rz, rmeta, rid);
+        if (staged) {
+            staged_write<IDS>(s_mem, B, d.g.ltw + d.g.lth, z, key, id, bk, rank, rz, rmeta, rid);
+            return;
+        }
+#pragma unroll
+        for (int j = 0; j < kBinPPT; ++j) {
+            if (bk[j] < 0) continue;
+            const unsigned pos = s_gb[bk[j]] + rank[j];
+            rz[pos] = z[j];
+            rmeta[pos] = key[j];
+            if (IDS) rid[pos] = id[j];
+        }
         return;
     }
     for (int64_t i = 4 * q0 + threadIdx.x; i < min((int64_t)d.n, 4 * q0 + kBatchChunk); i += kBinBlock) {
@@ -1741,7 +1756,7 @@ pct_status launch_build_batched(const float* xyz, const BuildItemDev* h_items, i
     hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, s, w.count, w.total_tiles, w.off, w.cursor);
     PCT_LAUNCH_CHECK();
     if (w.total_chunks > 0) {
-        const size_t lb = staged_lds_bytes(max_staged, ids);
+        const size_t lb = std::max(staged_lds_bytes(max_staged, ids), sizeof(unsigned) * max_tiles_lds);
         if (ids)
             hipLaunchKernelGGL(k_bscatter<true>, dim3(w.total_chunks), dim3(kBinBlock), lb, s, xyz, w.items, n_items,
                                w.cursor, w.rz, w.rmeta, w.rid);

@@ -358,3 +358,31 @@ def test_full_size_submap_batch(P, oracle_lib):
             lo, hi, _ = oracle_lib.envelope(tm["ground"], tm["ceil"], 0.1, rb.as_dict())
             c = cs[0].cpu().numpy().astype(np.float64)
             assert np.all(c >= lo - 1e-5) and np.all(c <= hi + 1e-5)
+
+
+@pytest.mark.parametrize("ids", [True, False])
+def test_batched_scatter_of_many_tiles(P, oracle_lib, ids):
+    """Items of more tiles than a staged scatter takes, up to the most whose
+    tiles are counted in LDS (8192) and beyond, beside a small one."""
+    import torch
+    rng = np.random.default_rng(9)
+    shapes = [(300, 1026, 4096), (129, 16384, 9001), (300, 33000, 12289), (40, 30, 700)]   # 1026, 8192, 8250, 4 tiles
+    specs, pts, off = [], [], 0
+    for nx, ny, n in shapes:
+        p = np.stack([rng.uniform(-0.05, 0.1 * nx + 0.05, n), rng.uniform(-0.05, 0.1 * ny + 0.05, n),
+                      rng.uniform(0.0, 0.5, n)], 1).astype(np.float32)
+        p[: n // 2, 1] = rng.uniform(0.0, 0.4, n // 2)       # many records in few tiles as well
+        specs.append(dict(xyz_offset=off, n_points=n, grid=dict(x0=0.0, y0=0.0, res=0.1, nx=nx, ny=ny, slice_dz=0.3)))
+        pts.append(p)
+        off += n
+    b = P.Batch(torch.from_numpy(np.concatenate(pts)).cuda(), specs, n_robots=1, with_ids=ids)
+    P.pct_tomogram_extent_batched(b)
+    G, Cc, aG, aC = P.pct_build_tomogram_batched(b, with_ids=ids)
+    for i, (p, sp) in enumerate(zip(pts, specs)):
+        tm = oracle_lib.tomogram(p, sp["grid"])
+        assert b.items[i].extent.n_slices == len(tm["h"])
+        np.testing.assert_array_equal(bits(b.item_view(G, i)), tm["ground"].view(np.uint32))
+        np.testing.assert_array_equal(bits(b.item_view(Cc, i)), tm["ceil"].view(np.uint32))
+        if ids:
+            for got, want in ((aG, tm["arg_ground"]), (aC, tm["arg_ceil"])):
+                np.testing.assert_array_equal(bits(b.item_view(got, i)), np.where(want >= 0, want + sp["xyz_offset"], -1))
