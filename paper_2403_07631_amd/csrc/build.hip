@@ -672,17 +672,15 @@ __global__ __launch_bounds__(kBinBlock) void k_bin2_scatter_staged(const float* 
 // Planes are taken in windows of at most 126 (127 if one window is all),
 // each by a workgroup of its own, so that the matrix has at most four words
 // per cell whatever the plane count and tile size, and a small map of many
-// planes spreads over the chip.  What lies below a window counts as one bin
-// below its first, what lies above as one past its last.  A window whose
-// occupied bins exceed the slots is walked in parts that fit; each part reads
-// the tile's records again and keeps what lies below and above it beside
-// the slots.  300 x 300 cells under 1001 planes, 60 points a cell: 5.6 ms with
+// planes spreads over the chip.  A window whose occupied bins exceed the
+// slots is walked in parts that fit; each part reads the tile's records again.
+// One slot per cell takes what lies below and above a part.  300 x 300 cells under 1001 planes, 60 points a cell: 5.6 ms with
 // one matrix of 32 words per cell, walked for every record's slot, and tiles
 // cut by cells (short rows of stores), 1.1 ms so; under 101 planes 0.71 and
 // 0.43 ms; 60 x 60 under 1001 planes, 10 a cell: 210 and 48 us.
 constexpr int kReduceBlock = 512;   // one cell per thread for the 512-cell tiles
-constexpr int kReduceKeep = 4;      // records per thread kept in registers between the passes
-constexpr int kReduceAhead = 2;     // other records per thread read together
+constexpr int kReduceKeep = 2;      // records per thread kept in registers between the passes (4 spill)
+constexpr int kReduceAhead = 4;     // other records per thread read together
 
 // Heights as integers of the same order (finite; -0 has become +0).
 __device__ __forceinline__ int height_key(float z) {
@@ -749,30 +747,27 @@ __device__ __forceinline__ void merge_vals(float og, float oc, int oi, int oj, f
     }
 }
 
-// What lies below and above the planes that a cell walks.
-template <bool IDS>
-struct Beyond {
-    float gz, cz;
-    int gi, ci;
-};
-
 // One cell: walk P planes from plane k_lo over the cell's occupied bins
 // (bits q0 .. q0 + P - 1 of `mask`, words `stride` apart) and their extremes
-// smax, smin; `far` is the ground before them and the ceiling after them.
-// The next occupied bin's extremes are read ahead.  MERGE: combine with the
-// stored values instead of overwriting them (ids are offset by id_base).
+// smax, smin; below and above are the extremes beyond them.  The next occupied
+// bin's extremes are read ahead.  MERGE: combine with the stored values
+// instead of overwriting them (ids are offset by id_base); a cell without
+// records is left as it is.
 template <bool IDS, bool MERGE>
 __device__ __forceinline__ void sweep_cell(const unsigned* mask, int stride, int q0,
+                                           typename SlotKeys<IDS>::T below, typename SlotKeys<IDS>::T above,
                                            const typename SlotKeys<IDS>::T* smax,
-                                           const typename SlotKeys<IDS>::T* smin, int n, Beyond<IDS> far, int ix,
-                                           int iy, const GridDev& g, int k_lo, int P, float* __restrict__ ground,
+                                           const typename SlotKeys<IDS>::T* smin, int n, int ix, int iy,
+                                           const GridDev& g, int k_lo, int P, float* __restrict__ ground,
                                            float* __restrict__ ceil, int* __restrict__ ag, int* __restrict__ ac,
                                            int id_base) {
     typedef SlotKeys<IDS> S;
+    const bool under = below != S::none_max(), over = above != S::none_min();
+    if (MERGE && n == 0 && !under && !over) return;
     const int64_t plane = (int64_t)g.nx * g.ny;
     int64_t o = (int64_t)k_lo * plane + (int64_t)iy * g.nx + ix;
-    float gz = far.gz, cz = far.cz, nextz = -INFINITY;
-    int gi = far.gi, ci = far.ci, nexti = -1;
+    float gz = under ? S::height(below) : -INFINITY, nextz = -INFINITY, cz;
+    int gi = IDS && under ? S::max_id(below) + id_base : -1, nexti = -1, ci = -1;
     int j = 0;
     auto read_next = [&]() {
         if (j < n) {
@@ -784,8 +779,8 @@ __device__ __forceinline__ void sweep_cell(const unsigned* mask, int stride, int
                 ci = S::min_id(lo) + id_base;
             }
         } else {
-            cz = far.cz;
-            ci = far.ci;
+            cz = over ? S::height(above) : INFINITY;
+            if (IDS) ci = over ? S::min_id(above) + id_base : -1;
         }
     };
     read_next();
@@ -918,93 +913,45 @@ __device__ void reduce_tile(int tg, int tl, int window, const unsigned* __restri
     others([&](unsigned c, float z, unsigned) { mark(c, z); });
     __syncthreads();
 
-    // slots: thread i owns a contiguous run of cells
+    // Parts of the window, one if its bins fit: the slots' first `cells` take
+    // what lies below the part (maxima) and above it (minima), the others
+    // its occupied bins; thread i owns a contiguous run of cells.
     const int per = (cells + kReduceBlock - 1) / kReduceBlock;
     const int cb = min((int)threadIdx.x * per, cells), ce = min(cb + per, cells);
-    unsigned total;
-    {
-        unsigned sum = 0;
-        for (int c = cb; c < ce; ++c)
-            for (int w = 0; w < W; ++w) sum += (unsigned)__popc(s_bits[w * cells + c]);
-        unsigned run = block_scan_excl(sum, s_w, total);
-        for (int c = cb; c < ce; ++c) {
-            s_base[c] = run;
-            for (int w = 0; w < W; ++w) run += (unsigned)__popc(s_bits[w * cells + c]);
-        }
-        if (threadIdx.x == 0) s_base[cells] = total;
-    }
-    if (total <= (unsigned)CAP) {   // the whole window at once; what lies below and above has slots like the others
-        for (int i = threadIdx.x; i < (int)total; i += kReduceBlock) {
-            s_max[i] = S::none_max();
-            s_min[i] = S::none_min();
-        }
-        __syncthreads();
-        auto put = [&](unsigned c, unsigned q, float z, int id) {
-            unsigned slot = s_base[c];
-            const unsigned w = q >> 5;
-            for (unsigned v = 0; v < w; ++v) slot += (unsigned)__popc(s_bits[v * cells + c]);
-            slot += (unsigned)__popc(s_bits[w * cells + c] & ((1u << (q & 31)) - 1u));
-            // of what lies below only the maximum counts, above the minimum
-            if ((int)q < end) atomicMax(&s_max[slot], S::max_key(z, id));
-            if ((int)q >= lead) atomicMin(&s_min[slot], S::min_key(z, id));
-        };
-#pragma unroll
-        for (int q = 0; q < kReduceKeep; ++q)
-            if (kc[q] != ~0u) put(kc[q] & 0xffffu, kc[q] >> 16, kz[q], ki[q]);
-        others([&](unsigned c, float z, unsigned r) { put(c, bit_of(z), z, IDS ? rid[r] : 0); });
-        __syncthreads();
-        for (int c = threadIdx.x; c < cells; c += kReduceBlock) {
-            const int ix = tx * g.tw + (c % g.tw);
-            const int iy = ty * g.th + c / g.tw;
-            if (ix >= g.nx || iy >= g.ny) continue;
-            unsigned s = s_base[c];
-            int n = (int)(s_base[c + 1] - s);
-            if (MERGE && n == 0) continue;   // a cell without records stays as it is
-            Beyond<IDS> far{-INFINITY, INFINITY, -1, -1};
-            if (lead && (s_bits[c] & 1u)) {
-                far.gz = S::height(s_max[s]);
-                if (IDS) far.gi = S::max_id(s_max[s]) + id_base;
-                ++s;
-                --n;
-            }
-            sweep_cell<IDS, MERGE>(s_bits + c, cells, lead, s_max + s, s_min + s, n, far, ix, iy, g, p0, p1 - p0,
-                                   ground, ceil, ag, ac, id_base);
-        }
-        return;
-    }
-
-    // Parts of the window: the slots' first `cells` take what lies below the
-    // part (maxima) and above it (minima), the others its occupied bins.
     const int room = CAP - cells;
-    const unsigned whole = total;
-    auto in_part = [&](int w, int qa, int qb) -> unsigned {   // bits qa .. qb - 1 in word w
-        const int a = qa - 32 * w, b = qb - 32 * w;
-        const unsigned lo = a <= 0 ? ~0u : (a >= 32 ? 0u : ~0u << a);
-        const unsigned hi = b <= 0 ? 0u : (b >= 32 ? ~0u : ~(~0u << b));
-        return lo & hi;
-    };
-    for (int qa = lead; qa < end;) {
-        int P = min(end - qa, max(1, (int)((long long)(p1 - p0) * room / (int)whole)));
-        unsigned run;
+    int P = end - lead;
+    for (int qa = lead; qa < end; qa += P) {
+        P = min(P, end - qa);
+        const int w0 = qa >> 5;
+        const unsigned m0 = ~0u << (qa & 31);      // the part's bits of its first word
+        unsigned run, total;
+        auto bins_of = [&](int c) -> unsigned {
+            const int w1 = (qa + P - 1) >> 5;
+            const unsigned m1 = ~0u >> (31 - ((qa + P - 1) & 31));
+            unsigned n = 0;
+#pragma nounroll
+            for (int w = w0; w <= w1; ++w)
+                n += (unsigned)__popc(s_bits[w * cells + c] & (w == w0 ? m0 : ~0u) & (w == w1 ? m1 : ~0u));
+            return n;
+        };
         for (;;) {
             unsigned sum = 0;
-            for (int w = qa >> 5; w <= (qa + P - 1) >> 5; ++w) {
-                const unsigned m = in_part(w, qa, qa + P);
-                for (int c = cb; c < ce; ++c) sum += (unsigned)__popc(s_bits[w * cells + c] & m);
-            }
-            __syncthreads();   // the part before is done with its slots (and s_base)
+#pragma nounroll
+            for (int c = cb; c < ce; ++c) sum += bins_of(c);
+            __syncthreads();   // the part before is done with its slots
             run = block_scan_excl(sum, s_w, total);
             if (total <= (unsigned)room) break;
-            // a plane has at most `cells` bins, which fit, so this ends
+            // in proportion; a plane has at most `cells` bins, which fit
             P = max(1, min(P - 1, (int)((long long)P * room / (int)total)));
         }
         const int qb = qa + P;
+#pragma nounroll
         for (int c = cb; c < ce; ++c) {
             s_base[c] = run;
-            for (int w = qa >> 5; w <= (qb - 1) >> 5; ++w)
-                run += (unsigned)__popc(s_bits[w * cells + c] & in_part(w, qa, qb));
+            run += bins_of(c);
         }
         if (threadIdx.x == 0) s_base[cells] = total;
+#pragma nounroll
         for (int i = threadIdx.x; i < cells + (int)total; i += kReduceBlock) {
             s_max[i] = S::none_max();
             s_min[i] = S::none_min();
@@ -1023,8 +970,14 @@ __device__ void reduce_tile(int tg, int tl, int window, const unsigned* __restri
                 if (k < *(volatile typename S::T*)&s_min[c]) atomicMin(&s_min[c], k);
                 return;
             }
-            unsigned slot = (unsigned)cells + s_base[c];
-            for (int v = qa >> 5; v <= q >> 5; ++v) slot += (unsigned)__popc(s_bits[v * cells + c] & in_part(v, qa, q));
+            const int w = q >> 5;
+            unsigned slot = (unsigned)cells + s_base[c], m = m0;
+#pragma nounroll
+            for (int v = w0; v < w; ++v) {
+                slot += (unsigned)__popc(s_bits[v * cells + c] & m);
+                m = ~0u;
+            }
+            slot += (unsigned)__popc(s_bits[w * cells + c] & m & ((1u << (q & 31)) - 1u));
             atomicMax(&s_max[slot], S::max_key(z, id));
             atomicMin(&s_min[slot], S::min_key(z, id));
         };
@@ -1038,22 +991,10 @@ __device__ void reduce_tile(int tg, int tl, int window, const unsigned* __restri
             const int iy = ty * g.th + c / g.tw;
             if (ix >= g.nx || iy >= g.ny) continue;
             const unsigned s = s_base[c];
-            const int n = (int)(s_base[c + 1] - s);
-            const bool below = s_max[c] != S::none_max(), above = s_min[c] != S::none_min();
-            if (MERGE && n == 0 && !below && !above) continue;
-            Beyond<IDS> far{-INFINITY, INFINITY, -1, -1};
-            if (below) {
-                far.gz = S::height(s_max[c]);
-                if (IDS) far.gi = S::max_id(s_max[c]) + id_base;
-            }
-            if (above) {
-                far.cz = S::height(s_min[c]);
-                if (IDS) far.ci = S::min_id(s_min[c]) + id_base;
-            }
-            sweep_cell<IDS, MERGE>(s_bits + c, cells, qa, s_max + cells + s, s_min + cells + s, n, far, ix, iy, g,
-                                   p0 + qa - lead, P, ground, ceil, ag, ac, id_base);
+            sweep_cell<IDS, MERGE>(s_bits + c, cells, qa, s_max[c], s_min[c], s_max + cells + s, s_min + cells + s,
+                                   (int)(s_base[c + 1] - s), ix, iy, g, p0 + qa - lead, P, ground, ceil, ag, ac,
+                                   id_base);
         }
-        qa = qb;
     }
 }
 
