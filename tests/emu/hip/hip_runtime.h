@@ -229,6 +229,7 @@ inline void emu_raw_buffer_store_b32(unsigned v, emu_buffer_rsrc r, int voff, in
 inline void emu_wave_barrier() { (void)emu::wave_op(emu::OP_BALLOT, 1u, 0, 0); }
 #define __builtin_amdgcn_wave_barrier emu_wave_barrier
 #define __builtin_amdgcn_fence(order, scope) ((void)0)
+#define __builtin_amdgcn_s_sleep(n) ((void)0)
 
 // Fibers switch only at the operations above, so read-modify-write needs no
 // further protection.
