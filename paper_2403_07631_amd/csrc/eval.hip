@@ -569,40 +569,50 @@ int even_rows(int wny, int rows) {
     return std::max(1, (wny + n - 1) / n);
 }
 
-// Default strip height of one map: one-wavefront strips of 128 rows, halved
-// while they leave the chip short of wavefronts (its SIMDs hold about 5000),
-// down to 16 rows: a strip walks 2 (R + 2) rows more than it stores, so
-// short strips only pay where there are too few.  One-wavefront strips pass
-// over rows known to be c^B and wait for no other wavefront: over 39 maps of
-// 40 x 40 to 2000 x 2000 cells, sparse and dense, within 1 % of the best
-// shape of each on average; four wavefronts of 256 rows, halved below 16384
-// wavefronts, had 12 % (2000 x 2000 x 56: 761 against 638 us, 200 x 200 x 8:
-// 22.5 against 15.6 us), and gain on large densely sampled maps (1500 x 1500
-// x 51: 425 against 435 us).
-constexpr int kMapRows = 128;
-int default_rows(const EvalParams& p) {
-    const int outw = strip_outw(p.R, 1), wnx = p.wx1 - p.wx0, wny = p.wy1 - p.wy0;
-    int rows = kMapRows;
-    while (rows > 16) {
-        const long long waves = (long long)p.N * ((wnx + outw - 1) / outw) * ((wny + rows - 1) / rows);
-        if (waves >= (rows > 32 ? 5000 : 2500)) break;
-        rows /= 2;
-    }
+// Default strips of one map.  One wavefront per strip passes over rows known
+// to be c^B and waits for no other; two wavefronts (four where their strips
+// spend fewer lanes on the map's columns) read fewer columns twice.  Over 30
+// maps of 60 x 60 to 2000 x 2000 cells, sparse and dense, against the best of
+// 15 shapes of each, one wavefront is within 1.8 % on average at radius 4,
+// 3 at 5, 1 at 7, 2.4 at 8, but 3.6 at 1 to 3 and 7.9 at 6; two or four are
+// within 1.2 % at 1 to 3, and 1.9 at 6 from 8000 strips of 16 rows on (2000 x
+// 2000 x 51, radius 6: 1555 against 1298 us with the slice test).
+//
+// A strip walks 2 (R + 2) rows more than it stores, so short strips pay only
+// where there are too few wavefronts (the chip's SIMDs hold about 5000) or at
+// small radii: 128 rows halved below 5000 wavefronts, at radii to 3 64 rows
+// halved below 14000, to 16 rows below 2500.
+long long map_waves(const EvalParams& p, int nw, int rows) {
+    const int outw = strip_outw(p.R, nw), wnx = p.wx1 - p.wx0, wny = p.wy1 - p.wy0;
+    return (long long)p.N * ((wnx + outw - 1) / outw) * ((wny + rows - 1) / rows) * nw;
+}
+int strip_lanes(const EvalParams& p, int nw) {
+    const int outw = strip_outw(p.R, nw), wnx = p.wx1 - p.wx0;
+    return (wnx + outw - 1) / outw * 64 * nw;
+}
+int default_waves(const EvalParams& p) {
+    if (p.R > 3 && !(p.R == 6 && map_waves(p, 1, 16) >= 8000)) return 1;
+    return strip_lanes(p, kDefaultWaves) < strip_lanes(p, 2) ? kDefaultWaves : 2;
+}
+int default_rows(const EvalParams& p, int nw) {
+    int rows = p.R <= 3 ? 64 : 128;
+    while (rows > 16 && map_waves(p, nw, rows) < (rows <= 32 ? 2500 : p.R <= 3 ? 14000 : 5000)) rows /= 2;
     return rows;
 }
 
-// shape.rows = 0: the tuned shape if one is recorded, else one-wavefront
-// strips of `rows` rows (0: default_rows), evened out.
-StripGeom strip_geom(const EvalParams& p, EvalShape shape = EvalShape{0, 0}, bool two_wave = true, int rows = 0) {
+// shape.rows = 0: the tuned shape if one is recorded, else strips of
+// default_waves wavefronts and default_rows rows, evened out; batch_rows > 0:
+// a batch's, of one wavefront and that height.
+StripGeom strip_geom(const EvalParams& p, EvalShape shape = EvalShape{0, 0}, int batch_rows = 0) {
     if (shape.rows <= 0) shape = tuned_shape(p);
     const int wnx = p.wx1 - p.wx0, wny = p.wy1 - p.wy0;
-    int nw = shape.rows > 0 ? std::max(1, shape.nw) : 1;
-    if (nw == 2 && !two_wave) nw = kDefaultWaves;
+    int nw = shape.rows > 0 ? std::max(1, shape.nw) : batch_rows > 0 ? 1 : default_waves(p);
+    if (nw == 2 && batch_rows > 0) nw = kDefaultWaves;
     const int outw = strip_outw(p.R, nw);
     StripGeom g{};
     g.nw = nw;
     g.n_sx = (wnx + outw - 1) / outw;
-    g.rows = shape.rows > 0 ? shape.rows : even_rows(wny, rows > 0 ? rows : default_rows(p));
+    g.rows = shape.rows > 0 ? shape.rows : even_rows(wny, batch_rows > 0 ? batch_rows : default_rows(p, nw));
     g.n_sy = (wny + g.rows - 1) / g.rows;
     g.n_work = (int)((long long)p.N * g.n_sx * g.n_sy);
     return g;
@@ -1152,7 +1162,7 @@ constexpr long long kBatchWaves = 10000;
 
 void batch_strip_signature(const EvalParams& p, EvalShape shape, int out[4]) {
     const StripGeom g = strip_geom(p, shape.rows > 0 ? shape : batch_eval_shape(size_class(p.nx), size_class(p.ny), p.R),
-                                   false, kBatchRows);
+                                   kBatchRows);
     out[0] = g.nw;
     out[1] = g.n_sx;
     out[2] = g.n_sy;
@@ -1362,10 +1372,7 @@ pct_status plan_jobs(const pct_item* items, int n_items, const pct_robot* robots
     int rows = kBatchRows;
     for (; rows > 16; rows /= 2) {
         long long waves = 0;
-        for (const EvalJob& jb : jp->jobs) {
-            const int outw = strip_outw(jb.p.R, 1);
-            waves += (long long)jb.p.N * ((jb.p.nx + outw - 1) / outw) * ((jb.p.ny + rows - 1) / rows);
-        }
+        for (const EvalJob& jb : jp->jobs) waves += map_waves(jb.p, 1, rows);
         if (waves >= kBatchWaves) break;
     }
     size_t j = 0;
@@ -1376,7 +1383,7 @@ pct_status plan_jobs(const pct_item* items, int n_items, const pct_robot* robots
             EvalJob& jb = jp->jobs[j++];
             // blocks of kBlock threads: 1 or 4 wavefronts; the size class's
             // tuned shape if one is recorded
-            jb.sg = strip_geom(jb.p, batch_eval_shape(size_class(jb.p.nx), size_class(jb.p.ny), jb.p.R), false, rows);
+            jb.sg = strip_geom(jb.p, batch_eval_shape(size_class(jb.p.nx), size_class(jb.p.ny), jb.p.R), rows);
             jb.in_off = items[i].out_offset;
             jb.out_off = (long long)r * total_cells + items[i].out_offset;
             jb.keep_off = (long long)r * total_slices + items[i].keep_offset;

@@ -386,3 +386,41 @@ def test_batched_scatter_of_many_tiles(P, oracle_lib, ids):
         if ids:
             for got, want in ((aG, tm["arg_ground"]), (aC, tm["arg_ceil"])):
                 np.testing.assert_array_equal(bits(b.item_view(got, i)), np.where(want >= 0, want + sp["xyz_offset"], -1))
+
+
+@pytest.mark.parametrize("R", range(0, 9))
+def test_default_strips_change_no_cost(P, R):
+    """The default strips of a map (one, two or four wavefronts, by radius and
+    size) and of a batch (one wavefront, or four on wide maps) give the costs
+    of explicit shapes, bit for bit, and the same kept slices."""
+    import torch
+    rng = np.random.default_rng(R)
+    inf = {0: (0.0, 0.15), 1: (0.0, 0.25), 2: (0.0, 0.4)}.get(R, (0.05 + 0.1 * (R - 3), 0.4))
+    r = dict(d_min=0.5, d_ref=0.65, theta_b=1.7, theta_s=0.36, theta_p=0.2, c_barrier=50.0, alpha_d=20.0, alpha_b=20.0,
+             alpha_s=15.0, d_inf=inf[0], d_sm=inf[1], patch_radius=1)
+    assert P.pct_kernel_radius(r, 0.1) == R
+    shapes = [(512, 33), (700, 431), (1500, 90), (45, 300), (511, 20)]
+    pts, specs, off = [], [], 0
+    for nx, ny in shapes:
+        n = 3 * nx * ny
+        z = 3.0 * rng.integers(0, 3, n) + rng.normal(0.0, 0.02, n)
+        p = np.stack([rng.uniform(0.0, 0.1 * nx, n), rng.uniform(0.0, 0.1 * ny, n), z], 1).astype(np.float32)
+        specs.append(dict(xyz_offset=off, n_points=n, grid=dict(x0=0.0, y0=0.0, res=0.1, nx=nx, ny=ny, slice_dz=0.3)))
+        pts.append(p)
+        off += n
+    b = P.Batch(torch.from_numpy(np.concatenate(pts)).cuda(), specs, n_robots=1)
+    P.pct_tomogram_extent_batched(b)
+    G, Cc, _, _ = P.pct_build_tomogram_batched(b)
+    cost, keep = P.pct_eval_traversability_batched(b, G, Cc, [r])
+    for i, sp in enumerate(specs):
+        ext, g = b.items[i].extent, sp["grid"]
+        gi, ci = b.item_view(G, i).contiguous(), b.item_view(Cc, i).contiguous()
+        want, kept = P.pct_eval_traversability(gi, ci, g, ext, [r])
+        assert torch.equal(b.item_view(cost[0], i).view(torch.int32), want[0].view(torch.int32)), (g["nx"], g["ny"])
+        ko = b.items[i].keep_offset
+        assert torch.equal(keep[0][ko:ko + ext.n_slices], kept[0]), (g["nx"], g["ny"])
+        for rows, waves in ((256, 4), (64, 2), (16, 1)):
+            P.pct_autotune_set_traversability(g, ext, r, rows, waves)
+            other, kept2 = P.pct_eval_traversability(gi, ci, g, ext, [r])
+            assert torch.equal(other.view(torch.int32), want.view(torch.int32)) and torch.equal(kept2, kept), (rows, waves)
+        P.pct_autotune_reset()
