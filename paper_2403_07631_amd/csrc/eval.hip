@@ -600,13 +600,27 @@ int default_rows(const EvalParams& p, int nw) {
     return rows;
 }
 
+// Default strips of a batch, in blocks of kDefaultWaves wavefronts: one per
+// strip, or one strip per block on maps of at least 512 cells across where it
+// spends no more lanes on their columns (four maps of
+// 2000 x 2000 x 21, radius 5: 2.40 ms with one per strip, 1.68 so).
+// Heights: 256 rows, halved while the whole batch has fewer wavefronts than
+// kBatchWaves (down to 16): its maps share the chip, so taller strips than a
+// lone map's of their size pay (512 submaps of 50 - 400 cells a side: 7.37 ms
+// with each map's own shape, 6.03 / 5.95 / 6.22 ms with 128 / 256 / 512 rows).
+constexpr int kBatchRows = 256;
+constexpr long long kBatchWaves = 10000;
+int batch_waves(const EvalParams& p) {
+    return p.nx >= 512 && strip_lanes(p, kDefaultWaves) <= strip_lanes(p, 1) ? kDefaultWaves : 1;
+}
+
 // shape.rows = 0: the tuned shape if one is recorded, else strips of
 // default_waves wavefronts and default_rows rows, evened out; batch_rows > 0:
-// a batch's, of one wavefront and that height.
+// a batch's, with strips of one or kDefaultWaves wavefronts and that height.
 StripGeom strip_geom(const EvalParams& p, EvalShape shape = EvalShape{0, 0}, int batch_rows = 0) {
     if (shape.rows <= 0) shape = tuned_shape(p);
     const int wnx = p.wx1 - p.wx0, wny = p.wy1 - p.wy0;
-    int nw = shape.rows > 0 ? std::max(1, shape.nw) : batch_rows > 0 ? 1 : default_waves(p);
+    int nw = shape.rows > 0 ? std::max(1, shape.nw) : batch_rows > 0 ? batch_waves(p) : default_waves(p);
     if (nw == 2 && batch_rows > 0) nw = kDefaultWaves;
     const int outw = strip_outw(p.R, nw);
     StripGeom g{};
@@ -1152,14 +1166,6 @@ void autotune_reset() {
     g_batch_build.clear();
 }
 
-// Strips of a batch without tuned shapes: 256 rows, halved while the whole
-// batch has fewer wavefronts than kBatchWaves (down to 16): its maps share
-// the chip, so taller strips than a lone map's of their size pay (512
-// submaps of 50 - 400 cells a side: 7.37 ms with each map's own shape, 6.03 /
-// 5.95 / 6.22 ms with 128 / 256 / 512 rows).
-constexpr int kBatchRows = 256;
-constexpr long long kBatchWaves = 10000;
-
 void batch_strip_signature(const EvalParams& p, EvalShape shape, int out[4]) {
     const StripGeom g = strip_geom(p, shape.rows > 0 ? shape : batch_eval_shape(size_class(p.nx), size_class(p.ny), p.R),
                                    kBatchRows);
@@ -1372,7 +1378,7 @@ pct_status plan_jobs(const pct_item* items, int n_items, const pct_robot* robots
     int rows = kBatchRows;
     for (; rows > 16; rows /= 2) {
         long long waves = 0;
-        for (const EvalJob& jb : jp->jobs) waves += map_waves(jb.p, 1, rows);
+        for (const EvalJob& jb : jp->jobs) waves += map_waves(jb.p, batch_waves(jb.p), rows);
         if (waves >= kBatchWaves) break;
     }
     size_t j = 0;
