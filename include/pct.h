@@ -409,7 +409,8 @@ typedef struct {
     int32_t class_x;   /* ceil(log2 nx) of the class's items */
     int32_t class_y;   /* ceil(log2 ny) */
     int32_t radius;    /* the evaluation's inflation radius R in cells; -1 for the construction */
-    int32_t rows;      /* construction: tile height in cells; evaluation: strip rows (0: the default shape) */
+    int32_t rows;      /* construction: tile height in cells; evaluation: strip rows (0: the default
+                        * shape, whose height goes by the whole batch) */
     int32_t waves;     /* evaluation: wavefronts per workgroup (1 or PCT_STRIP_WAVES); 0 for the construction */
     int32_t n_items;   /* items in the class */
     int32_t chosen;    /* 1 for the choice recorded for the class */

@@ -948,7 +948,14 @@ pct_status pct_autotune_batched(const float* d_xyz, int64_t n_total, const pct_i
             return pct_eval_traversability_batched(G, Cc, sub.data(), ns, h_robot, 1, cost, nullptr, flags, ws,
                                                    ws_bytes, s);
         };
-        EvalParams p0;
+        std::vector<EvalParams> ps(ns);
+        std::vector<const EvalParams*> pps;
+        for (int i = 0; i < ns; ++i) {
+            st = make_eval_params(*h_robot, sub[i].grid, sub[i].extent.n_slices, &ps[i]);
+            if (st != PCT_OK) return st;
+            pps.push_back(&ps[i]);
+        }
+        const int rows = batch_default_rows(pps);   // of the trial batch
         const EvalShape old = batch_eval_shape(cx, cy, R);
         set_batch_eval_shape(cx, cy, R, EvalShape{0, 0});   // {0, 0} below: the default shape
         const EvalShape shapes[] = {{0, 0},  {32, 1},  {64, 1},  {128, 1}, {256, 1},
@@ -960,15 +967,10 @@ pct_status pct_autotune_batched(const float* d_xyz, int64_t n_total, const pct_i
         for (const EvalShape& sh : shapes) {
             bool fits = true;
             std::vector<int> sig;
-            for (const pct_item& t : sub) {
-                st = make_eval_params(*h_robot, t.grid, t.extent.n_slices, &p0);
-                if (st != PCT_OK) {
-                    set_batch_eval_shape(cx, cy, R, old);
-                    return st;
-                }
-                if (sh.rows > 0 && !strip_shape_fits(p0, sh)) fits = false;
+            for (const EvalParams& p : ps) {
+                if (sh.rows > 0 && !strip_shape_fits(p, sh)) fits = false;
                 int g4[4];
-                batch_strip_signature(p0, sh, g4);
+                batch_strip_signature(p, sh, rows, g4);
                 sig.insert(sig.end(), g4, g4 + 4);
             }
             if (!fits || std::find(tried.begin(), tried.end(), sig) != tried.end()) continue;

@@ -614,6 +614,20 @@ int batch_waves(const EvalParams& p) {
     return p.nx >= 512 && strip_lanes(p, kDefaultWaves) <= strip_lanes(p, 1) ? kDefaultWaves : 1;
 }
 
+}  // namespace
+
+int batch_default_rows(const std::vector<const EvalParams*>& jobs) {
+    int rows = kBatchRows;
+    for (; rows > 16; rows /= 2) {
+        long long waves = 0;
+        for (const EvalParams* p : jobs) waves += map_waves(*p, batch_waves(*p), rows);
+        if (waves >= kBatchWaves) break;
+    }
+    return rows;
+}
+
+namespace {
+
 // shape.rows = 0: the tuned shape if one is recorded, else strips of
 // default_waves wavefronts and default_rows rows, evened out; batch_rows > 0:
 // a batch's, with strips of one or kDefaultWaves wavefronts and that height.
@@ -1166,9 +1180,9 @@ void autotune_reset() {
     g_batch_build.clear();
 }
 
-void batch_strip_signature(const EvalParams& p, EvalShape shape, int out[4]) {
+void batch_strip_signature(const EvalParams& p, EvalShape shape, int rows, int out[4]) {
     const StripGeom g = strip_geom(p, shape.rows > 0 ? shape : batch_eval_shape(size_class(p.nx), size_class(p.ny), p.R),
-                                   kBatchRows);
+                                   rows);
     out[0] = g.nw;
     out[1] = g.n_sx;
     out[2] = g.n_sy;
@@ -1375,12 +1389,9 @@ pct_status plan_jobs(const pct_item* items, int n_items, const pct_robot* robots
             last = i;
         }
     }
-    int rows = kBatchRows;
-    for (; rows > 16; rows /= 2) {
-        long long waves = 0;
-        for (const EvalJob& jb : jp->jobs) waves += map_waves(jb.p, batch_waves(jb.p), rows);
-        if (waves >= kBatchWaves) break;
-    }
+    std::vector<const EvalParams*> ps;
+    for (const EvalJob& jb : jp->jobs) ps.push_back(&jb.p);
+    const int rows = batch_default_rows(ps);
     size_t j = 0;
     for (int r = 0; r < n_robots; ++r)
         for (int i = 0; i < n_items; ++i) {

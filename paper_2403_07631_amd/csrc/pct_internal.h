@@ -8,6 +8,8 @@
 #include <stddef.h>
 #include <string.h>
 
+#include <vector>
+
 #include "pct.h"
 
 namespace pct {
@@ -195,10 +197,13 @@ EvalShape batch_eval_shape(int cx, int cy, int R);
 void set_batch_eval_shape(int cx, int cy, int R, EvalShape shape);
 int batch_build_th(int cx, int cy);
 void set_batch_build_th(int cx, int cy, int th);
+// The height of the default strips of a batch of these jobs.
+int batch_default_rows(const std::vector<const EvalParams*>& jobs);
 // What a batched launch of a job with parameters p does with strip shape
-// `shape` ({0, 0}: the shape batched calls use now): wavefronts per
-// workgroup, strips across and down, and the strip height when it matters.
-void batch_strip_signature(const EvalParams& p, EvalShape shape, int out[4]);
+// `shape` ({0, 0}: the shape batched calls use now, with default strips of
+// `rows` rows): wavefronts per workgroup, strips across and down, and the
+// strip height when it matters.
+void batch_strip_signature(const EvalParams& p, EvalShape shape, int rows, int out[4]);
 pct_status tune_save(const char* path, const char* arch);
 pct_status tune_load(const char* path, const char* arch, int* n_applied);
 

@@ -787,6 +787,31 @@ def case_batch_tune():
     say("batch tuning tables: loaded shapes change no output, stale resident tables refused, save/load round trip")
 
 
+def case_batch_tune_shapes():
+    """The tuner times every candidate that launches other strips than those
+    tried before: the default of a small class is 16 rows, so strips as tall
+    as the maps are candidates of their own, in one and in four wavefronts."""
+    maps = [planes_scene(81, 60, 40, 4, 2), planes_scene(82, 50, 38, 4, 2)]
+    specs, off = (abi.pct_item * 2)(), 0
+    for it, sc in zip(specs, maps):
+        it.xyz_offset, it.n_points, it.grid = off, len(sc.points), grid_s(sc.grid)
+        off += len(sc.points)
+    pts = np.ascontiguousarray(np.concatenate([sc.points for sc in maps]))
+    xb = Buf.of(pts)
+    tc, ts, cnt = C.c_int64(), C.c_int64(), C.c_int32()
+    ws = Buf(L.pct_batch_workspace_bytes(specs, 2, 1, 0))
+    check("extent_batched", L.pct_tomogram_extent_batched(P(xb), len(pts), specs, 2, C.byref(tc), C.byref(ts), P(ws),
+                                                          ws.nbytes, None))
+    ent = (abi.pct_tune_entry * 64)()
+    check("reset", L.pct_autotune_reset())
+    check("autotune_batched", L.pct_autotune_batched(P(xb), len(pts), specs, 2, (abi.pct_robot * 1)(robot_s(robot())),
+                                                     ent, 64, C.byref(cnt), None))
+    check("reset", L.pct_autotune_reset())
+    shapes = [(e.rows, e.waves) for e in ent[:cnt.value] if e.stage == 1]
+    assert shapes == [(0, 0), (32, 1), (64, 1), (32, 4), (64, 4)], shapes
+    say(f"batch tuner: shapes {shapes}")
+
+
 def case_config1_build():
     """The 20 M-point 2000 x 2000 map, tomogram with ids (slow: minutes)."""
     sc = scenes.config1_scene()

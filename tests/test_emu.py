@@ -68,7 +68,7 @@ GROUPS = [
     (("plan", "unique"), "rand"),
     (("plan_query",), "fwd"),
     (("insert", "traj_opt"), "rev"),
-    (("plane_parts", "tall_tiles"), "rand"),
+    (("plane_parts", "tall_tiles", "batch_tune_shapes"), "rand"),
 ]
 
 
