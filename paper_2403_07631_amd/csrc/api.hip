@@ -1044,13 +1044,13 @@ pct_status pct_trajectory_cost_multi(const float* d_ground, const float* d_ceil,
     const size_t need = pct_trajectory_multi_workspace_bytes(n_profiles);
     if (!d_ws || ws_bytes < need) return fail(PCT_ERR_WORKSPACE, "workspace too small: %zu < %zu", ws_bytes, need);
     std::vector<EvalParams> ps(n_profiles);
-    bool boxes = true;
+    int kinds = 0;
     for (int i = 0; i < n_profiles; ++i) {
         pct_status st = make_eval_params(h_robots[i], *grid, std::max(N, 1), &ps[i]);
         if (st != PCT_OK) return st;
         ps[i].N = N;
         mark_zero_taps(ps[i]);
-        boxes = boxes && boxes_apply(ps[i]);
+        kinds |= box_kind(ps[i]);
     }
     hipStream_t s = (hipStream_t)stream;
     const bool fixed = flags & PCT_FIXED_POINT;
@@ -1077,7 +1077,7 @@ pct_status pct_trajectory_cost_multi(const float* d_ground, const float* d_ceil,
     }
     return launch_traj_value_grad(d_ground, d_ceil, d_arg_ground, d_arg_ceil, *grid, N, d_ps, n_profiles, w_z, d_wp,
                                   d_wp_slice, n_traj, n_wp, d_gf, d_f, d_gwp, d_gground, d_gceil, d_gz, n_points,
-                                  fixed, boxes, s);
+                                  fixed, kinds, s);
 }
 
 pct_status pct_fixed_to_float(const int64_t* d_acc, int64_t n, float* d_out, void* stream) {

@@ -248,14 +248,19 @@ __device__ __forceinline__ void wave_lds_sync() {
 // 10 KB per wavefront cuts fewer groups but leaves three workgroups per CU:
 // 3.1 ms, and 1.8 ms for the values alone.
 constexpr int kBoxFloats = 2472;     // 4 workgroups of 4 wavefronts per CU
-constexpr int kBoxR = 8;             // largest inflation radius of the box path
+constexpr int kBoxR = 8;             // largest radius of a staged box; above, the weights take part of the box
 constexpr int kBoxWeights = (kBoxR + 1) * (kBoxR + 1);
+constexpr int kWideWeights = kKmax * kKmax;
 struct BoxLds {
-    alignas(8) float v[kBoxFloats];  // gradient sums, e^G with halo, c^init
-    float K[kBoxWeights];            // K[a * (R + 1) + j]; NaN for zero weights
-    float pad[1];
+    // gradient sums, e^G with halo, c^init; then the weights K[a * (R + 1) + j],
+    // NaN where zero
+    alignas(8) float v[kBoxFloats + kBoxWeights + 1];
 };
 static_assert(4 * sizeof(BoxLds) * 4 <= 160 * 1024, "four workgroups per CU");
+
+__device__ __forceinline__ int box_room(int R) {
+    return R <= kBoxR ? kBoxFloats : kBoxFloats + kBoxWeights - kWideWeights;
+}
 
 struct Box {
     unsigned long long* acc;   // ground gradients, rows of w + 2 cells, first cell (x0 - 1, y0 - 1)
@@ -266,7 +271,7 @@ struct Box {
     __device__ __forceinline__ float G(int x, int y) const { return g[(y - y0 + halo) * wg + x - x0 + halo]; }
 };
 
-// Whether a box of w x h cells fits (halo: patch radius + 1).
+// Whether a staged box of w x h cells fits (halo: patch radius + 1).
 __host__ __device__ __forceinline__ bool box_fits(int w, int h, int halo, bool sums) {
     if (w > kBoxFloats || h > kBoxFloats) return false;
     const int e = 2 * halo;
@@ -354,6 +359,28 @@ __device__ __forceinline__ void fill_cinit(const Box& b, const float* __restrict
     wave_lds_sync();
 }
 
+// A box of c^init alone, w x h cells at (x0, y0), formed from the map.
+__device__ __forceinline__ void bare_box(Box& b, BoxLds& lds, const float* __restrict__ gk,
+                                         const float* __restrict__ ck, int x0, int y0, int w, int h,
+                                         const EvalParams& p) {
+    const int lane = threadIdx.x & 63;
+    b.k = -1;
+    b.x0 = x0;
+    b.y0 = y0;
+    b.w = w;
+    b.h = h;
+    b.c = lds.v;
+    BoxWalk q(lane, w);
+    for (int i = lane; i < w * h; i += 64) {
+        const int x = x0 + q.u, y = y0 + q.v;
+        float ci = __builtin_nanf("");
+        if (x >= 0 && y >= 0 && x < p.nx && y < p.ny) ci = cinit_at(gk, ck, x, y, p).ci;
+        b.c[i] = ci;
+        q.next();
+    }
+    wave_lds_sync();
+}
+
 // The box's gradient sums to the sink (fixed point).
 __device__ __forceinline__ void flush_box(const Box& b, const Sink& s, long long plane, int nx) {
     if (b.k < 0) return;
@@ -382,12 +409,12 @@ __device__ __forceinline__ void flush_box(const Box& b, const Sink& s, long long
 // passes over and no comparison selects.  Each window row is reduced to its
 // maximum and the first row with a greater one is remembered; the tap is
 // then found in that row alone, when `taps` is set.  RT: the inflation radius
-// when known at compile time (unrolled rows), 0: p.R.
+// when known at compile time, -1: p.R.
 template <int RT, int C2>
 __device__ __forceinline__ void window_max_box(const Box& b, const float* __restrict__ sK, int x, int y,
                                                const EvalParams& p, bool taps, WinMax (&o)[C2 * C2]) {
     constexpr int NC = C2 * C2;
-    const int R = RT > 0 ? RT : p.R, K1 = R + 1;
+    const int R = RT >= 0 ? RT : p.R, K1 = R + 1;
     const float* base = b.c + (y - R - b.y0) * b.w + (x - R - b.x0);
     float best[NC];
     int brow[NC];
@@ -396,8 +423,9 @@ __device__ __forceinline__ void window_max_box(const Box& b, const float* __rest
         best[c] = -INFINITY;
         brow[c] = 0;
     }
-    if constexpr (RT > 0) {
-#pragma unroll
+    if constexpr (RT >= 0) {
+        constexpr int kRows = RT == 2 || RT == 4 || RT == 5 ? 2 * RT + C2 : 1;
+#pragma unroll kRows
         for (int n = 0; n < 2 * RT + C2; ++n) {
             float v[2 * RT + C2];
 #pragma unroll
@@ -405,16 +433,14 @@ __device__ __forceinline__ void window_max_box(const Box& b, const float* __rest
 #pragma unroll
             for (int r = 0; r < C2; ++r) {
                 const int dy = n - RT - r;
-                if (dy < -RT || dy > RT) continue;
+                if (dy < -RT || dy > RT) continue;   // uniform
                 const int j = dy < 0 ? -dy : dy;
 #pragma unroll
                 for (int q = 0; q < C2; ++q) {
                     float rm = -INFINITY;
 #pragma unroll
-                    for (int m = 0; m <= 2 * RT; ++m) {
-                        const int a = m < RT ? RT - m : m - RT;
-                        rm = fmaxf(rm, sK[a * (RT + 1) + j] * v[m + q]);
-                    }
+                    for (int m = 0; m <= 2 * RT; ++m)
+                        rm = fmaxf(rm, sK[(m < RT ? RT - m : m - RT) * (RT + 1) + j] * v[m + q]);
                     const int c = C2 * r + q;
                     if (rm > best[c]) {
                         best[c] = rm;
@@ -470,22 +496,32 @@ __device__ __forceinline__ void window_max_box(const Box& b, const float* __rest
     }
 }
 
-// The common radii have unrolled windows; p.R is uniform over the wavefront.
-template <int C2>
+// How the radii's windows are walked: 2, 4 and 5 (the usual 0.3 m and the
+// quadruped's 0.2 m of inflation on 0.1 m grids, and on 0.2 m) unrolled as a
+// whole, 3 and 6 to 8 by unrolled rows, the others by run-time loops.  By rows
+// the three take 5 to 10 % longer; more whole windows in one kernel spill its
+// registers (64 profiles' kernel: 32 instead of 14), so the radii walked by
+// rows and those above have kernels of their own.
+__host__ __device__ constexpr bool wide_radius(int R) { return R == 3 || R > 5; }
+
+// p.R is uniform over the wavefront.  WIDE: wide radii may come, else others.
+template <int C2, bool NARROW, bool WIDE>
 __device__ __forceinline__ void window_max_any(const Box& b, const float* __restrict__ sK, int x, int y,
                                                const EvalParams& p, bool taps, WinMax (&o)[C2 * C2]) {
-    switch (p.R) {
-    case 5: window_max_box<5, C2>(b, sK, x, y, p, taps, o); break;
-    case 4: window_max_box<4, C2>(b, sK, x, y, p, taps, o); break;
-    case 2: window_max_box<2, C2>(b, sK, x, y, p, taps, o); break;
-    default: window_max_box<0, C2>(b, sK, x, y, p, taps, o); break;
-    }
+#define PCT_W(RT)                                                        \
+    if constexpr (wide_radius(RT) ? WIDE : NARROW)                       \
+        if (p.R == RT) return window_max_box<RT, C2>(b, sK, x, y, p, taps, o);
+    PCT_W(5) PCT_W(4) PCT_W(2) PCT_W(3) PCT_W(6) PCT_W(7) PCT_W(8)
+#undef PCT_W
+    window_max_box<-1, C2>(b, sK, x, y, p, taps, o);
 }
 
-// The wavefront's weight table for the parameters it works with.
+// The wavefront's weight table for the parameters it works with.  Above
+// kBoxR it takes part of the box: no staged box may be there.
 __device__ __forceinline__ void fill_weights(BoxLds& lds, const EvalParams& p) {
     const int lane = threadIdx.x & 63, K1 = p.R + 1;
-    for (int i = lane; i < K1 * K1; i += 64) lds.K[i] = p.K[i / K1][i % K1];
+    float* K = lds.v + box_room(p.R);
+    for (int i = lane; i < K1 * K1; i += 64) K[i] = p.K[i / K1][i % K1];
     wave_lds_sync();
 }
 
@@ -547,20 +583,27 @@ struct BoxSink {
 // The wavefront's waypoints in groups that share a box: `ok` lanes on slice
 // k with corners (x, y) .. (x + 1, y + 1).  The lanes of the first waiting
 // lane's slice, from it on, form a group; while their box does not fit, the
-// group is cut to half its reach.  Groups of fewer than eight lanes would
-// spend most of the wavefront on one window after another: those waypoints
-// are taken one by one, the whole wavefront on each.  A group whose box lies
-// in the one staged already (the next profile on the same walk) keeps it,
-// with the gradients summed there; SUMS: the box sums ground gradients
-// (fixed point), which leave with the box.  Radius at most kBoxR, and a map
-// more than one cell wide and tall.
+// group is cut to half its reach.  A group whose box lies in the one staged
+// already (the next profile on the same walk) keeps it, with the gradients
+// summed there; SUMS: the box sums ground gradients (fixed point), which leave
+// with the box.  WIDE (wide_radius): a group that would be cut below
+// 32 lanes, and any above kBoxR, takes a box of c^init alone for as many
+// lanes as that holds, and its gradients go out one by one (256 walks x 256
+// waypoints, radius 8: 2.02 ms with staged boxes of fewer than eight lanes
+// and single waypoints, 0.38 so; radius 14: 8.06 ms by walks over the map, 1.30
+// so).
+// Groups of fewer than eight lanes would spend most of the wavefront on one
+// window after another: those waypoints are taken one by one, the whole
+// wavefront on each.  The weights of p are in place, and the map is more than
+// one cell wide and tall.
 // body(wm, detail, sink) runs once per lane, where detail(wm[c]) is the
 // c^init of the maximising cell with what its adjoint needs.
-template <bool SUMS, class Body>
+template <bool SUMS, bool WIDE, class Body>
 __device__ __forceinline__ void for_box_groups(Box& b, BoxLds& lds, const float* __restrict__ ground,
                                                const float* __restrict__ ceil, const EvalParams& p, bool ok, int k,
                                                int x, int y, bool taps, const Sink& s, Body body) {
-    const int lane = threadIdx.x & 63, R = p.R;
+    const int lane = threadIdx.x & 63, R = p.R, room = WIDE ? box_room(R) : kBoxFloats;
+    const float* sK = lds.v + room;
     unsigned long long rem = __ballot(ok);
     while (rem != 0ull) {
         const int l0 = (int)__builtin_ctzll(rem);
@@ -568,26 +611,45 @@ __device__ __forceinline__ void for_box_groups(Box& b, BoxLds& lds, const float*
         const float* gk = ground + (long long)kb * p.plane;
         const float* ck = ceil + (long long)kb * p.plane;
         const bool cand = ((rem >> lane) & 1ull) != 0ull && k == kb;
-        bool mine = false, fits = false;
-        int xlo = 0, ylo = 0, w = 0, h = 0;
-        for (int reach = 64; reach >= 8 && !fits; reach >>= 1) {
-            mine = cand && lane < l0 + reach;
-            xlo = wave_min_i(mine ? x : INT_MAX) - R;
-            ylo = wave_min_i(mine ? y : INT_MAX) - R;
-            w = wave_max_i(mine ? x : INT_MIN) + 2 + R - xlo;
-            h = wave_max_i(mine ? y : INT_MIN) + 2 + R - ylo;
-            fits = box_fits(w, h, p.rp + 1, SUMS);
+        bool mine = false, fits = false, bare = false;
+        int x0 = 0, y0 = 0, w = 0, h = 0;
+        if constexpr (!WIDE) {
+            for (int reach = 64; reach >= 8 && !fits; reach >>= 1) {
+                mine = cand && lane < l0 + reach;
+                x0 = wave_min_i(mine ? x : INT_MAX) - R;
+                y0 = wave_min_i(mine ? y : INT_MAX) - R;
+                w = wave_max_i(mine ? x : INT_MIN) + 2 + R - x0;
+                h = wave_max_i(mine ? y : INT_MIN) + 2 + R - y0;
+                fits = box_fits(w, h, p.rp + 1, SUMS);
+            }
+        } else {
+            auto group = [&](int reach) {
+                mine = cand && lane < l0 + reach;
+                x0 = wave_min_i(mine ? x : INT_MAX) - R;
+                y0 = wave_min_i(mine ? y : INT_MAX) - R;
+                w = wave_max_i(mine ? x : INT_MIN) + 2 + R - x0;
+                h = wave_max_i(mine ? y : INT_MIN) + 2 + R - y0;
+            };
+            for (int reach = 64; reach >= 32 && !fits && R <= kBoxR; reach >>= 1) {
+                group(reach);
+                fits = box_fits(w, h, p.rp + 1, SUMS);
+            }
+            for (int reach = 64; reach >= 8 && !fits && !bare; reach >>= 1) {
+                group(reach);
+                bare = w <= room && h <= room && w * h <= room;
+            }
         }
         WinMax wm[4];
-        if (fits) {
-            const bool staged = b.k == kb && b.halo == p.rp + 1 && xlo >= b.x0 && ylo >= b.y0 &&
-                                xlo + w <= b.x0 + b.w && ylo + h <= b.y0 + b.h;
+        if (fits || bare) {   // bare: WIDE only
+            const bool staged = fits && b.k == kb && b.halo == p.rp + 1 && x0 >= b.x0 && y0 >= b.y0 &&
+                                x0 + w <= b.x0 + b.w && y0 + h <= b.y0 + b.h;
             if (!staged) {
                 if (SUMS) flush_box(b, s, p.plane, p.nx);
-                stage_box(b, lds, gk, kb, xlo, ylo, w, h, p, SUMS);
+                if (!WIDE || fits) stage_box(b, lds, gk, kb, x0, y0, w, h, p, SUMS);
+                else bare_box(b, lds, gk, ck, x0, y0, w, h, p);
             }
-            fill_cinit(b, ck, p);
-            if (mine) window_max_any<2>(b, lds.K, x, y, p, taps, wm);
+            if (!WIDE || fits) fill_cinit(b, ck, p);
+            if (mine) window_max_any<2, !WIDE, WIDE>(b, sK, x, y, p, taps, wm);
         } else {
             if (SUMS) flush_box(b, s, p.plane, p.nx);
             unsigned long long left = __ballot(mine);
@@ -596,10 +658,14 @@ __device__ __forceinline__ void for_box_groups(Box& b, BoxLds& lds, const float*
             while (left != 0ull) {
                 const int l = (int)__builtin_ctzll(left);
                 WinMax one[4];
-                stage_box(b, lds, gk, kb, __builtin_amdgcn_readlane(x, l) - R, __builtin_amdgcn_readlane(y, l) - R,
-                          2 + 2 * R, 2 + 2 * R, p, false);
-                fill_cinit(b, ck, p);
-                window_max4_one(b, lds.K, p, taps, one);
+                const int xl = __builtin_amdgcn_readlane(x, l) - R, yl = __builtin_amdgcn_readlane(y, l) - R;
+                if (!WIDE || R <= kBoxR) {
+                    stage_box(b, lds, gk, kb, xl, yl, 2 + 2 * R, 2 + 2 * R, p, false);
+                    fill_cinit(b, ck, p);
+                } else {
+                    bare_box(b, lds, gk, ck, xl, yl, 2 + 2 * R, 2 + 2 * R, p);
+                }
+                window_max4_one(b, sK, p, taps, one);
                 wave_lds_sync();
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
@@ -789,10 +855,10 @@ __global__ __launch_bounds__(kBlock) void k_sample_fwd(const float* __restrict__
 // Per waypoint: dL/dwp (written), the bilinear scatter of dL/dC to c^T
 // (dense gcost) or, with EVAL, straight through the traversability adjoint
 // into the sink, and of the height term to e^G.  With EVAL = kBoxes a
-// wavefront's 64 waypoints share boxes of c^init as in k_traj_value_grad;
-// kWindows walks each corner's window over the map (radii and maps that
-// boxes do not take).
-enum { kDense, kBoxes, kWindows };
+// wavefront's 64 waypoints share boxes of c^init as in k_traj_value_grad
+// (kWideBoxes for wide radii); kWindows walks each corner's window over the map (maps that boxes do
+// not take).
+enum { kDense, kBoxes, kWideBoxes, kWindows };
 template <int EVAL>
 __global__ __launch_bounds__(kBlock, 4) void k_sample_bwd(const float* __restrict__ cost, const float* __restrict__ ground,
                                                        const float* __restrict__ ceil, const float* __restrict__ wp,
@@ -847,7 +913,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_sample_bwd(const float* __restric
         gwp[3 * i + 1] = gy;
         gwp[3 * i + 2] = gzw;
     }
-    if constexpr (EVAL == kBoxes) {
+    if constexpr (EVAL == kBoxes || EVAL == kWideBoxes) {
         __shared__ BoxLds s_box[kBlock / 64];
         BoxLds& lds = s_box[threadIdx.x / 64];
         fill_weights(lds, ep);
@@ -863,10 +929,10 @@ __global__ __launch_bounds__(kBlock, 4) void k_sample_bwd(const float* __restric
         };
         const bool ok = b.ok && g != 0.0f;
         if (s.fixed) {
-            for_box_groups<true>(box, lds, ground, ceil, ep, ok, k, b.i0, b.j0, true, s, body);
+            for_box_groups<true, EVAL == kWideBoxes>(box, lds, ground, ceil, ep, ok, k, b.i0, b.j0, true, s, body);
             flush_box(box, s, a.plane, a.nx);
         } else {
-            for_box_groups<false>(box, lds, ground, ceil, ep, ok, k, b.i0, b.j0, true, s, body);
+            for_box_groups<false, EVAL == kWideBoxes>(box, lds, ground, ceil, ep, ok, k, b.i0, b.j0, true, s, body);
         }
     }
 }
@@ -905,6 +971,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_eval_bwd_tiles(const float* __res
     __shared__ BoxLds s_box[kBlock / 64];
     BoxLds& lds = s_box[threadIdx.x / 64];
     fill_weights(lds, p);
+    const float* sK = lds.v + kBoxFloats;
     const int lane = threadIdx.x & 63, R = p.R;
     const long long n_work = (long long)nbx * nby * p.N;
     const long long stride = (long long)gridDim.x * (kBlock / 64);
@@ -938,7 +1005,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_eval_bwd_tiles(const float* __res
                     const float gc = x < p.nx && y < p.ny ? qk[(long long)y * p.nx + x] : 0.0f;
                     if (gc == 0.0f) continue;
                     WinMax m[1];
-                    window_max_any<1>(b, lds.K, x, y, p, true, m);
+                    window_max_any<1, true, true>(b, sK, x, y, p, true, m);
                     const float C = ck[(long long)m[0].qy * p.nx + m[0].qx];
                     const BoxSink to{&s, SUMS ? &b : nullptr, (long long)k * p.plane, p.nx};
                     cinit_adjoint(cinit_of(b, m[0].qx, m[0].qy, b.G(m[0].qx, m[0].qy), C, p), m[0].qx, m[0].qy,
@@ -1016,11 +1083,17 @@ int grid_for(long long n) { return (int)std::max<long long>(1, std::min<long lon
 // materialised map, and the maximising taps found for the value feed the
 // traversability adjoint directly.
 // SUMS: fixed-point gradient sums with a ground or point output.
-// BOX false: windows walked over the map, one profile per wavefront (radii
-// and maps that boxes do not take).
+// BOX: kWideBoxes takes the profiles of wide radii, kBoxes the others (a call
+// with both launches both); kWindows walks the windows of all over
+// the map, one profile per wavefront (maps that boxes do not take).
 constexpr int kTrajProfiles = 8;
 
-template <bool BOX, bool SUMS>
+template <int BOX>
+__device__ __forceinline__ bool takes_radius(int R) {
+    return BOX == kWindows || wide_radius(R) == (BOX == kWideBoxes);
+}
+
+template <int BOX, bool SUMS>
 __global__ __launch_bounds__(kBlock, 4) void k_traj_value_grad(const float* __restrict__ ground,
                                                                const float* __restrict__ ceil,
                                                                const EvalParams* __restrict__ robots, SampleArgs a,
@@ -1034,8 +1107,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_traj_value_grad(const float* __re
     if (p0 >= n_profiles) return;
     const int np = min(run, n_profiles - p0);
     const int lane = threadIdx.x & 63;
-    __shared__ BoxLds s_box[BOX ? kBlock / 64 : 1];
-    BoxLds& lds = s_box[BOX ? threadIdx.x / 64 : 0];
+    __shared__ BoxLds s_box[BOX != kWindows ? kBlock / 64 : 1];
+    BoxLds& lds = s_box[BOX != kWindows ? threadIdx.x / 64 : 0];
     Box box{};
     box.k = -1;
     int weights_of = -1;
@@ -1045,6 +1118,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_traj_value_grad(const float* __re
     for (int w0 = 0; w0 < a.W; w0 += 64) {
         for (int pi = 0; pi < np; ++pi) {
             const EvalParams& p = robots[p0 + pi];
+            if (!takes_radius<BOX>(p.R)) continue;   // uniform
             const long long row = (long long)(p0 + pi) * a.T + t;
             const int w = w0 + lane;
             const bool act = w < a.W;
@@ -1098,12 +1172,16 @@ __global__ __launch_bounds__(kBlock, 4) void k_traj_value_grad(const float* __re
                     cinit_adjoint(detail(wm[c]), wm[c].qx, wm[c].qy, wm[c].k * gc, p, to);
                 }
             };
-            if constexpr (BOX) {
+            if constexpr (BOX != kWindows) {
                 if (weights_of != pi) {
+                    if (BOX == kWideBoxes && p.R > kBoxR) {
+                        if (SUMS) flush_box(box, s, a.plane, a.nx);
+                        box.k = -1;
+                    }
                     fill_weights(lds, p);
                     weights_of = pi;
                 }
-                for_box_groups<SUMS>(box, lds, ground, ceil, p, b.ok, k, b.i0, b.j0, gf != nullptr, s, body);
+                for_box_groups<SUMS, BOX == kWideBoxes>(box, lds, ground, ceil, p, b.ok, k, b.i0, b.j0, gf != nullptr, s, body);
             } else if (b.ok) {
                 const float* gk = ground + (long long)k * a.plane;
                 const float* ck = ceil + (long long)k * a.plane;
@@ -1123,10 +1201,11 @@ __global__ __launch_bounds__(kBlock, 4) void k_traj_value_grad(const float* __re
             for (int q = 0; q < kTrajProfiles; ++q) accs[q] = q == pi ? acc : accs[q];
         }
     }
-    if constexpr (BOX && SUMS) flush_box(box, s, a.plane, a.nx);
+    if constexpr (BOX != kWindows && SUMS) flush_box(box, s, a.plane, a.nx);
 #pragma unroll
     for (int q = 0; q < kTrajProfiles; ++q) {
         if (q >= np) break;
+        if (!takes_radius<BOX>(robots[p0 + q].R)) continue;
         float v = accs[q];
         for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
         if (lane == 0) f[(long long)(p0 + q) * a.T + t] = v;
@@ -1135,10 +1214,9 @@ __global__ __launch_bounds__(kBlock, 4) void k_traj_value_grad(const float* __re
 
 }  // namespace
 
-// Boxes hold windows of at most this radius, and waypoints with four distinct
-// corners; k_traj_value_grad and k_sample_bwd take other radii and maps one
-// cell wide through walks over the map.
-bool boxes_apply(const EvalParams& p) { return p.R <= kBoxR && p.nx > 1 && p.ny > 1; }
+// Boxes take waypoints with four distinct corners; maps one cell wide or tall
+// are taken through walks over the map.
+int box_kind(const EvalParams& p) { return p.nx > 1 && p.ny > 1 ? (wide_radius(p.R) ? 2 : 1) : 0; }
 
 void mark_zero_taps(EvalParams& p) {
     for (auto& row : p.K)
@@ -1196,9 +1274,13 @@ pct_status launch_sample_bwd(const float* cost, const float* ground, const float
     const long long n = (long long)T * W;
     if (n == 0) return PCT_OK;
     const dim3 blocks((unsigned)((n + kBlock - 1) / kBlock));
-    if (ep && boxes_apply(p)) {
+    if (ep && box_kind(p) != 0) {
         mark_zero_taps(p);
-        hipLaunchKernelGGL(k_sample_bwd<kBoxes>, blocks, dim3(kBlock), 0, s, cost, ground, ceil, wp, slice, a, gf, gwp,
+        if (wide_radius(p.R))
+            hipLaunchKernelGGL(k_sample_bwd<kWideBoxes>, blocks, dim3(kBlock), 0, s, cost, ground, ceil, wp, slice, a,
+                               gf, gwp, gcost, p, sk);
+        else
+            hipLaunchKernelGGL(k_sample_bwd<kBoxes>, blocks, dim3(kBlock), 0, s, cost, ground, ceil, wp, slice, a, gf, gwp,
                            gcost, p, sk);
     } else if (ep) {
         hipLaunchKernelGGL(k_sample_bwd<kWindows>, blocks, dim3(kBlock), 0, s, cost, ground, ceil, wp, slice, a, gf,
@@ -1259,7 +1341,7 @@ pct_status launch_traj_value_grad(const float* ground, const float* ceil, const 
                                   const pct_grid& g, int N, const EvalParams* d_robots, int n_profiles, float w_z,
                                   const float* wp, const int* slice, int T, int W, const float* gf, float* f,
                                   float* gwp, float* gground, float* gceil, float* gz, long long n_points,
-                                  bool fixed, bool boxes, hipStream_t s) {
+                                  bool fixed, int kinds, hipStream_t s) {
     const SampleArgs a = make_sample_args(g, N, 0.0f, w_z, T, W);
     Sink sk{};
     sk.fixed = fixed;
@@ -1275,21 +1357,27 @@ pct_status launch_traj_value_grad(const float* ground, const float* ceil, const 
     // profiles per wavefront: as many as leave 16384 wavefronts, four rounds
     // of the chip (64 profiles x 1024 walks on the building: 2.80 ms, at
     // 8192 3.08 ms); one where the windows are walked over the map
+    const bool boxes = kinds != 0;
     const int run = boxes ? (int)std::min<long long>(kTrajProfiles, std::max<long long>(1, (long long)n_profiles * T / 16384))
                           : 1;
     const long long waves = (long long)((n_profiles + run - 1) / run) * T;
     const unsigned blocks = (unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64));
     const bool sums = fixed && (sk.gG || sk.gz);
     float* gw = gf ? gwp : nullptr;
-    if (boxes && sums)
-        hipLaunchKernelGGL((k_traj_value_grad<true, true>), dim3(blocks), dim3(kBlock), 0, s, ground, ceil, d_robots, a,
-                           n_profiles, run, wp, slice, gf, f, gw, sk);
-    else if (boxes)
-        hipLaunchKernelGGL((k_traj_value_grad<true, false>), dim3(blocks), dim3(kBlock), 0, s, ground, ceil, d_robots,
-                           a, n_profiles, run, wp, slice, gf, f, gw, sk);
-    else
-        hipLaunchKernelGGL((k_traj_value_grad<false, false>), dim3(blocks), dim3(kBlock), 0, s, ground, ceil, d_robots,
-                           a, n_profiles, run, wp, slice, gf, f, gw, sk);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, s, ground, ceil, d_robots, a, n_profiles, run, wp, slice,
+                           gf, f, gw, sk);
+    };
+    if (!boxes) launch(k_traj_value_grad<kWindows, false>);
+    if (kinds & 1) {
+        if (sums) launch(k_traj_value_grad<kBoxes, true>);
+        else launch(k_traj_value_grad<kBoxes, false>);
+        PCT_LAUNCH_CHECK();
+    }
+    if (kinds & 2) {
+        if (sums) launch(k_traj_value_grad<kWideBoxes, true>);
+        else launch(k_traj_value_grad<kWideBoxes, false>);
+    }
     PCT_LAUNCH_CHECK();
     return PCT_OK;
 }

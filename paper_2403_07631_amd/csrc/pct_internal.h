@@ -155,7 +155,9 @@ pct_status make_eval_params(const pct_robot& r, const pct_grid& g, int N, EvalPa
 // The weights that are zero become NaN: the adjoints' window maxima pass
 // over the products of such taps without a test per tap.
 void mark_zero_taps(EvalParams& p);
-bool boxes_apply(const EvalParams& p);   // whether the adjoints may share c^init in boxes
+// How the adjoints share c^init in boxes: 0 not at all, 1 or 2 by the radius
+// (a call's kinds are or-ed).
+int box_kind(const EvalParams& p);
 
 // ---------------------------------------------------------------- launchers
 pct_status launch_extent(const float* xyz, int64_t n, const GridDev& g, void* ws, ExtentDev* d_out,
@@ -255,7 +257,7 @@ pct_status launch_traj_value_grad(const float* ground, const float* ceil, const 
                                   const pct_grid& g, int N, const EvalParams* d_robots, int n_profiles, float w_z,
                                   const float* wp, const int* slice, int T, int W, const float* gf, float* f,
                                   float* gwp, float* gground, float* gceil, float* gz, long long n_points,
-                                  bool fixed, bool boxes, hipStream_t s);
+                                  bool fixed, int kinds, hipStream_t s);
 pct_status launch_route(const float* gG, const float* gC, const int* aG, const int* aC, long long plane, int N,
                         long long n_points, float* gz, bool fixed, hipStream_t s);
 pct_status launch_fixed_to_float(const int64_t* q, long long n, float* out, hipStream_t s);

@@ -317,3 +317,16 @@ def test_eval_bwd_tiles(P, oracle_lib, world, d_inf, d_sm, rp, dense):
                                                deterministic=det)
         close(gG.cpu().numpy(), rG, ~unc)
         close(gC.cpu().numpy(), rC, ~unc)
+
+
+@pytest.mark.parametrize("d_inf,d_sm,layout", [(0.0, 0.25, "walks"), (0.05, 0.4, "walks"), (0.05, 0.4, "spread"),
+                                               (0.15, 0.4, "scattered"), (0.25, 0.4, "spread"), (0.35, 0.4, "walks"),
+                                               (0.35, 0.4, "scattered"), (0.45, 0.4, "spread"), (0.55, 0.4, "walks"),
+                                               (0.55, 0.4, "scattered"), (0.65, 0.4, "spread"), (0.95, 0.4, "walks"),
+                                               (1.15, 0.4, "walks"), (1.15, 0.4, "spread"), (1.35, 0.4, "walks"),
+                                               (1.35, 0.4, "scattered"), (1.35, 0.4, "column")])
+def test_window_boxes_of_every_kind(P, oracle_lib, world, d_inf, d_sm, layout):
+    """The same at radii 1 to 16: windows walked whole, by rows and by run-time
+    loops, boxes with and without staged ground, single waypoints, and calls
+    whose profiles' radii go to different kernels (the third's is 1)."""
+    test_window_boxes(P, oracle_lib, world, d_inf, d_sm, layout)
