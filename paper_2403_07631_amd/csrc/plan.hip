@@ -36,6 +36,7 @@
 // (30 layers of 1000 x 1000): 23.5 ms; with capped sweeps 18.9 ms, with a
 // visit's loads in two unbroken runs 15.6 ms, and with the old distances
 // read again at the end instead of held in 128 registers 14.6 ms.
+#include <limits.h>
 #include <math.h>
 #include <string.h>
 
@@ -56,7 +57,12 @@ __device__ __forceinline__ int cidx(int r, int c) { return r * kCS + c; }
 // (with its neighbours' news).  Distance field of the building, 119 rounds:
 // 4 / 6 / 8 / 10 / 12 / any number of sweeps 20.8 / 19.9 / 18.9 / 19.8 / 20.6
 // / 22.5 ms.
+// On graphs of at most kFewTiles tiles no other tile waits for a long visit,
+// and every round is two launches: any number of sweeps.  Fields of 2 / 8 / 27
+// / 48 tiles, capped and not: 189 / 437 / 500 / 497 us and 112 / 470 / 633 /
+// 590 us.
 constexpr int kMaxSweeps = 8;
+constexpr int kFewTiles = 4;
 constexpr double kSqrt2 = 1.4142135623730951;   // sqrt(2) rounded to double
 
 // gateway bits of a node (l, cell)
@@ -229,7 +235,7 @@ __global__ __launch_bounds__(64) void k_plan_relax(PlanGeom g, const float* __re
                                                    const uint8_t* __restrict__ gw, double* __restrict__ dist,
                                                    const unsigned* __restrict__ list, unsigned* __restrict__ flag,
                                                    unsigned long long* __restrict__ key, long long src,
-                                                   PlanStatus* __restrict__ st) {
+                                                   int max_sweeps, PlanStatus* __restrict__ st) {
     if (blockIdx.x >= min(st->n_list, (unsigned)kListCap)) return;
     __shared__ double sd[kPT * kPS];
     __shared__ double hz[4][kPT + 2];
@@ -383,7 +389,7 @@ __global__ __launch_bounds__(64) void k_plan_relax(PlanGeom g, const float* __re
     // direction holds, so the tile is at its fixed point when all four are
     // clean.
     unsigned dirty = 0xFu;
-    int left = kMaxSweeps;
+    int left = max_sweeps;
     for (int d = 0; dirty && left > 0; d = (d + 1) & 3) {
         if (!(dirty & (1u << d))) continue;
         --left;
@@ -698,7 +704,7 @@ pct_status launch_plan(const float* cost, const float* ground, int nx, int ny, c
                                delta, goal >= 0 ? dist + goal : nullptr, w.list, prev, cur, next);
             PCT_LAUNCH_CHECK();
             hipLaunchKernelGGL(k_plan_relax, dim3((unsigned)blocks), dim3(64), 0, s, g, w.cn, w.gw, dist, w.list, w.flag,
-                               w.key, src, cur);
+                               w.key, src, nt <= kFewTiles ? INT_MAX : kMaxSweeps, cur);
             PCT_LAUNCH_CHECK();
         }
         PCT_HIP(hipMemcpyAsync(&hs, &w.st[(r + 2) % 3], sizeof hs, hipMemcpyDeviceToHost, s));

@@ -679,7 +679,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
     double phi = evaluate<false, true>(s, a, lpp, slice, xt, nullptr);
     double alpha = step;
     int done = 0;
-    if (isfinite(phi)) {
+    if (isfinite(phi) && iters > 0) {
         // the first gradient, like that of every accepted point, at the knot
         // states in place
         evaluate<true, false>(s, a, lpp, slice, xt, nullptr);
