@@ -32,10 +32,13 @@
 // the adjacent layer.  Rounds repeat until no tile is active.
 //
 // Latency bounds a round: three tiles fit a CU's LDS, each a wavefront whose
-// loads and sweep steps wait for one another.  Distance field of the building
-// (30 layers of 1000 x 1000): 23.5 ms; with capped sweeps 18.9 ms, with a
-// visit's loads in two unbroken runs 15.6 ms, and with the old distances
-// read again at the end instead of held in 128 registers 14.6 ms.
+// loads and sweep steps wait for one another.  Distance field of the
+// six-storey building (30 layers of 1000 x 1000), step by step on one card:
+// 23.5 ms; with capped sweeps 18.9 ms, with a visit's loads in two unbroken
+// runs 15.6 ms, and with the old distances read again at the end instead of
+// held in 128 registers 14.6 ms; since, node costs and first distances in one
+// pass and rounds enqueued ahead.  From the first state to the present one,
+// timed in turn: 21.6 and 11.9 ms.
 #include <limits.h>
 #include <math.h>
 #include <string.h>
@@ -54,9 +57,9 @@ constexpr int kCS = kPT + 1;       // LDS row stride of the node-cost tile (floa
 __device__ __forceinline__ int cidx(int r, int c) { return r * kCS + c; }
 // Sweeps of one visit: a round lasts as long as its slowest tile, so a tile
 // that is not at its fixed point after this many goes on in the next round
-// (with its neighbours' news).  Distance field of the building, 119 rounds:
-// 4 / 6 / 8 / 10 / 12 / any number of sweeps 20.8 / 19.9 / 18.9 / 19.8 / 20.6
-// / 22.5 ms.
+// (with its neighbours' news).  The field above, other steps not yet taken: 4 /
+// 6 / 8 / 10 / 12 / any number of sweeps 20.8 / 19.9 / 18.9 / 19.8 / 20.6 /
+// 22.5 ms.
 // On graphs of at most kFewTiles tiles no other tile waits for a long visit,
 // and every round is two launches: any number of sweeps.  Fields of 2 / 8 / 27
 // / 48 tiles, capped and not: 189 / 437 / 500 / 497 us and 112 / 470 / 633 /
@@ -694,7 +697,7 @@ pct_status launch_plan(const float* cost, const float* ground, int nx, int ny, c
     // the list and the end of the search, so the host enqueues rounds ahead
     // (rounds after the end do nothing: 5 us each) and looks after 2, then 4,
     // then every 8: with one look per round the distance field of the
-    // 4-storey building took 13.9 ms and a query 2.20 ms, now 12.2 and 1.99.
+    // building took 13.9 ms and a query 2.20 ms, so 12.2 and 1.99 (one card).
     const int blocks = std::min(nt, kListCap);
     PlanStatus hs;
     for (int r = 0, ahead = 2;; ahead = std::min(2 * ahead, kRoundsAhead)) {
