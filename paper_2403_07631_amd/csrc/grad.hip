@@ -961,9 +961,19 @@ __global__ __launch_bounds__(kBlock) void k_eval_bwd(const float* __restrict__ g
 // gradient step through 1024 walks on 500 x 500 x 57 cell-slices took 1.54
 // ms, of which 0.72 ms there, against 0.86 ms with tiles and k_route's wider
 // loads.
+// KIND: kWideTiles takes wide radii, kLoneTiles those up to kEvalWalkR, kTiles
+// the others.  kLoneTiles: where a strip of 64 columns holds at most kEvalWalk
+// gradients, no two in one column, each lane walks the nine cells of its
+// window over the map instead: a box of 180 values for each lone cell took
+// longer.  400 x 400 x 51 cell-slices at radius 1, walked throughout / boxes
+// throughout / this rule: a gradient at 0.3 % of the cells 168 / 214 / 175 us,
+// at 1 % 270 / 278 / 241, at 3 % 374 / 320 / 320, at all 1123 / 352 / 350.
+// At radius 2 the boxes are level at 0.1 % and faster above it.
 constexpr int kEvalLook = 8;
+constexpr int kEvalWalkR = 1, kEvalWalk = 10;
+enum { kTiles, kWideTiles, kLoneTiles };
 
-template <bool SUMS>
+template <bool SUMS, int KIND>
 __global__ __launch_bounds__(kBlock, 4) void k_eval_bwd_tiles(const float* __restrict__ ground,
                                                               const float* __restrict__ ceil,
                                                               const float* __restrict__ gcost, const EvalParams p,
@@ -991,6 +1001,14 @@ __global__ __launch_bounds__(kBlock, 4) void k_eval_bwd_tiles(const float* __res
         unsigned rows = 0u;   // rows in which this lane's column has a gradient (NaN included)
 #pragma unroll
         for (int e = 0; e < kEvalLook; ++e) rows |= v[e] != 0.0f ? 1u << e : 0u;
+        if (KIND == kLoneTiles && __popcll(__ballot(rows != 0u)) <= kEvalWalk &&
+            __ballot((rows & (rows - 1u)) != 0u) == 0ull) {
+            if (rows != 0u) {
+                const int y = Y0 + __builtin_ctz(rows);
+                eval_adjoint_cell(ground, ceil, k, X0 + lane, y, qk[(long long)y * p.nx + X0 + lane], p, s);
+            }
+            continue;
+        }
         for (int ty = 0; ty < kEvalLook; ty += th) {
             unsigned long long cols = __ballot(((rows >> ty) & ((1u << th) - 1u)) != 0u);
             while (cols != 0ull) {
@@ -1005,7 +1023,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_eval_bwd_tiles(const float* __res
                     const float gc = x < p.nx && y < p.ny ? qk[(long long)y * p.nx + x] : 0.0f;
                     if (gc == 0.0f) continue;
                     WinMax m[1];
-                    window_max_any<1, true, true>(b, sK, x, y, p, true, m);
+                    window_max_any<1, KIND != kWideTiles, KIND == kWideTiles>(b, sK, x, y, p, true, m);
                     const float C = ck[(long long)m[0].qy * p.nx + m[0].qx];
                     const BoxSink to{&s, SUMS ? &b : nullptr, (long long)k * p.plane, p.nx};
                     cinit_adjoint(cinit_of(b, m[0].qx, m[0].qy, b.G(m[0].qx, m[0].qy), C, p), m[0].qx, m[0].qy,
@@ -1308,12 +1326,10 @@ pct_status launch_eval_bwd(const float* ground, const float* ceil, const float* 
         const int nbx = (p.nx + 63) / 64, nby = (p.ny + kEvalLook - 1) / kEvalLook;
         const long long work = (long long)nbx * nby * p.N;
         const dim3 blocks((unsigned)std::min<long long>((work + kBlock / 64 - 1) / (kBlock / 64), 4096));
-        if (fixed)
-            hipLaunchKernelGGL(k_eval_bwd_tiles<true>, blocks, dim3(kBlock), 0, s, ground, ceil, gcost, q, t.first,
-                               t.second, nbx, nby, sk);
-        else
-            hipLaunchKernelGGL(k_eval_bwd_tiles<false>, blocks, dim3(kBlock), 0, s, ground, ceil, gcost, q, t.first,
-                               t.second, nbx, nby, sk);
+        auto* tiles = fixed ? k_eval_bwd_tiles<true, kTiles> : k_eval_bwd_tiles<false, kTiles>;
+        if (wide_radius(p.R)) tiles = fixed ? k_eval_bwd_tiles<true, kWideTiles> : k_eval_bwd_tiles<false, kWideTiles>;
+        if (p.R <= kEvalWalkR) tiles = fixed ? k_eval_bwd_tiles<true, kLoneTiles> : k_eval_bwd_tiles<false, kLoneTiles>;
+        hipLaunchKernelGGL(tiles, blocks, dim3(kBlock), 0, s, ground, ceil, gcost, q, t.first, t.second, nbx, nby, sk);
         PCT_LAUNCH_CHECK();
         return PCT_OK;
     }

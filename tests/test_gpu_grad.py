@@ -319,6 +319,31 @@ def test_eval_bwd_tiles(P, oracle_lib, world, d_inf, d_sm, rp, dense):
         close(gC.cpu().numpy(), rC, ~unc)
 
 
+@pytest.mark.parametrize("d_inf,d_sm,rp", [(0.0, 0.15, 1), (0.05, 0.2, 1), (0.05, 0.2, 3), (0.1, 0.2, 1)])
+@pytest.mark.parametrize("columns,rows", [(1, 1), (10, 1), (11, 1), (10, 2)])
+def test_eval_bwd_lone_cells(P, oracle_lib, world, d_inf, d_sm, rp, columns, rows):
+    """Radii 0 and 1 with few gradients in a strip of 64 x 8 cells, up to and past
+    the number whose windows are walked over the map, one and two in a column,
+    in the first, an inner and the last strip of the map."""
+    import torch
+    w, rng = world, np.random.default_rng(4)
+    r = dict(w["r"], d_inf=d_inf, d_sm=d_sm, patch_radius=rp)
+    N, ny, nx = w["tm"]["ground"].shape
+    gc = np.zeros((N, ny, nx), np.float32)
+    for k in range(N):
+        for x0, y0 in ((0, 0), (0, (ny // 2) // 8 * 8), ((nx - 1) // 64 * 64, (ny - 1) // 8 * 8)):
+            xs = rng.permutation(min(64, nx - x0))[:columns]
+            for x in xs:
+                gc[k, y0 + rng.permutation(min(8, ny - y0))[:rows], x0 + x] = rng.normal()
+        gc[k, ny - 1, nx - 1] = 1.0
+    rG, rC, unc = oracle_lib.eval_bwd(w["tm"]["ground"], w["tm"]["ceil"], w["g"]["res"], r, gc.astype(np.float64))
+    for det in (True, False):
+        gG, gC = P.pct_eval_traversability_bwd(w["G"], w["C"], w["g"], w["ext"], r, torch.from_numpy(gc).cuda(),
+                                               deterministic=det)
+        close(gG.cpu().numpy(), rG, ~unc)
+        close(gC.cpu().numpy(), rC, ~unc)
+
+
 @pytest.mark.parametrize("d_inf,d_sm,layout", [(0.0, 0.25, "walks"), (0.05, 0.4, "walks"), (0.05, 0.4, "spread"),
                                                (0.15, 0.4, "scattered"), (0.25, 0.4, "spread"), (0.35, 0.4, "walks"),
                                                (0.35, 0.4, "scattered"), (0.45, 0.4, "spread"), (0.55, 0.4, "walks"),
